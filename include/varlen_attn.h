@@ -65,7 +65,7 @@ typedef struct va_segments {
   int32_t *seg_id;        /* [N]  index of the example holding token t                                   */
   int32_t *seg_start;     /* [N]  first token of that example  (= cu[seg_id[t]])                         */
   int32_t *seg_end;       /* [N]  one past its last token      (= cu[seg_id[t] + 1])                     */
-  int32_t *meta;          /* [8]  meta[0] = n (examples), meta[1] = max_seqlen; rest reserved            */
+  int32_t *meta;          /* [8]  meta[0] = n (examples), meta[1] = max_seqlen; rest internal            */
   int32_t *q_tile_order;  /* [R * ceil(T / VA_TILE)] query tiles in launch order: tiles of the longest examples  */
   int32_t *kv_tile_order; /* first, tiles of one example adjacent, heaviest first; tiles of examples of at most   */
                           /* VA_TILE tokens last, in stream order.  Key tiles likewise.  Entry: tile index in    */
@@ -171,7 +171,8 @@ va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *
  * large entries of P and dS through the matrix units in two 16-bit parts.
  *   grad_dt   : element type of dQ, dK, dV: VA_F32, or the 16-bit type of the inputs (VA_BF16 also
  *               with fp32 inputs); other pairs: VA_ERR_UNSUPPORTED.
- *   workspace : >= va_attn_workspace_bytes(..., 1) bytes (holds D, [Hq, N] float).
+ *   workspace : >= va_attn_workspace_bytes(..., 1) bytes (holds D, [Hq, N] float, and 64 MiB for the
+ *               partial sums of key tiles whose work is shared by several workgroups).
  */
 va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const void *V,
                              const void *O, const float *LSE, void *dQ, void *dK, void *dV,
@@ -183,8 +184,8 @@ va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const
 /*
  * The backward above for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
- * and errors as va_varlen_attn_bwd, without `workspace`: D lives in a device array inside the library
- * (VA_NOALLOC_SCRATCH_BYTES per GPU, held until the process ends).  Calls no hipMalloc / hipFree and no
+ * and errors as va_varlen_attn_bwd, without `workspace`: it lives in a device array inside the library
+ * (VA_NOALLOC_SCRATCH_BYTES for D and 64 MiB for partial sums per GPU, held until the process ends).  Calls no hipMalloc / hipFree and no
  * allocating routine; the first call on a device looks the array's address up once (make that call
  * outside stream capture).
  *   Limit: rows * tokens_per_row * hq * 4 <= VA_NOALLOC_SCRATCH_BYTES, else VA_ERR_WORKSPACE and

@@ -9,6 +9,8 @@ namespace {
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+// D = rowsum(dO * O), [Hq, N] float: the first part of the backward's workspace
+inline size_t d_bytes(int32_t n_tokens, int32_t hq) { return align_up((size_t)n_tokens * (size_t)hq * sizeof(float)); }
 
 struct PlanLayout {
   size_t cu, seg_id, seg_start, seg_end, meta, q_order, kv_order, scratch, total;
@@ -135,7 +137,7 @@ va_status va_rope_apply(const void *x, void *y, va_dtype dt, const void *positio
 size_t va_attn_workspace_bytes(int32_t n_tokens, int32_t hq, int32_t hkv, int32_t d, int is_bwd) {
   if (n_tokens <= 0 || hq <= 0 || hkv <= 0 || d <= 0) return 0;
   if (!is_bwd) return 0;
-  return align_up((size_t)n_tokens * (size_t)hq * sizeof(float));  // D = rowsum(dO * O), [Hq, N]
+  return d_bytes(n_tokens, hq) + va::kDkdvSplitBytes;
 }
 
 va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
@@ -200,7 +202,7 @@ va_status va_varlen_attn_bwd_stages(const void *dO, const void *Q, const void *K
   if (e != hipSuccess) return VA_ERR_HIP;
   if (mfma_stages)
     e = va::launch_mfma_bwd(dO, Q, K, V, O, LSE, delta, dQ, dK, dV, grad_dt, *seg, rows, tokens_per_row, hq, hkv,
-                            d, dt, scale, st, mfma_stages | hints);
+                            d, dt, scale, (float *)((char *)workspace + d_bytes(N, hq)), st, mfma_stages | hints);
   if (e != hipSuccess) return VA_ERR_HIP;
   if (plain_stages)
     e = va::launch_generic_bwd(dO, Q, K, V, LSE, delta, dQ, dK, dV, grad_dt, *seg, N, hq, hkv, d, dt, scale, st,
@@ -220,11 +222,11 @@ va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const
 }
 
 // ---- the backward for callers that cannot allocate ------------------------------------------
-// Its workspace (D = rowsum(dO * O), [Hq, N] float) is this file-scope device array instead of a
+// Its workspace (D, and the sums of cut dK/dV tiles) is this file-scope device array instead of a
 // caller's buffer.  Every GPU holds its own copy at its own address: the address is looked up once
 // per device (hipGetSymbolAddress with that device current) and only that pointer is ever handed to
 // a kernel - the array's name is a host-side stand-in, not a device address.
-static __device__ __align__(256) unsigned char scratch[VA_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[VA_NOALLOC_SCRATCH_BYTES + va::kDkdvSplitBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -253,14 +255,13 @@ va_status va_varlen_attn_bwd_noalloc(const void *dO, const void *Q, const void *
   const va_status s = check_bwd(dO, Q, K, V, O, LSE, dQ, dK, dV, grad_dt, seg, rows, tokens_per_row, hq, hkv, d, dt,
                                  VA_STAGE_D | VA_STAGE_DKDV | VA_STAGE_DQ);
   if (s != VA_OK) return s;  // before anything touches the GPU
-  const size_t need = va_attn_workspace_bytes(rows * tokens_per_row, hq, hkv, d, 1);
-  if (need == 0 || need > (size_t)VA_NOALLOC_SCRATCH_BYTES) return VA_ERR_WORKSPACE;  // beyond the static array
+  if (d_bytes(rows * tokens_per_row, hq) > (size_t)VA_NOALLOC_SCRATCH_BYTES) return VA_ERR_WORKSPACE;  // beyond the static array
   void *ws = scratch_on_current_device();
   if (!ws) return VA_ERR_HIP;
   // every byte of D that the dK/dV kernel reads is written by the dQ (or D) kernel of the same call,
   // so nothing of the previous call's contents has to be cleared
   return va_varlen_attn_bwd(dO, Q, K, V, O, LSE, dQ, dK, dV, grad_dt, seg, rows, tokens_per_row, hq, hkv, d, dt,
-                            softmax_scale, ws, (size_t)VA_NOALLOC_SCRATCH_BYTES, stream);
+                            softmax_scale, ws, sizeof(scratch), stream);
 }
 
 const char *va_status_string(va_status s) {

@@ -444,6 +444,37 @@ template <int kDh, bool kSmall> struct DkdvShape {
   static constexpr int kSubTiles = VA_TILE / kKeys;     // workgroup tiles per schedule tile
 };
 
+// ---- cutting a key tile's work over several workgroups --------------------------------------------
+// A tile's trips (64-query blocks x query heads of the group) form one serial chain.  With few tiles or
+// many query heads per KV head the chip then sits idle while the longest chains run (16 heads on one KV
+// head, 6141 tokens: 96 workgroups of up to 208 trips, 315 us).  The chain is cut into chunks of whole
+// trips, one workgroup each; the chunks of a cut tile leave their fp32 accumulators in the workspace and
+// dkdv_merge_kernel adds them, always in the order of the chunks (no atomics): 315 -> 90 us there, 370 ->
+// 303 us for one example of 4096 tokens with 4 query heads per KV head.
+//   host  : how many chunks a tile may have follows from the number of tiles and the workspace
+//           (plan_split below); with many tiles it is one, and no merge kernel is launched.
+//   device: how many it gets follows from its own trips and the batch's total.
+struct DkdvSplit {
+  float *partial;   // [limit * max_chunks] slots of 2 * kKeys * kDh floats
+  int limit;        // (tile, KV head) pairs that may be cut, counted in launch order (0: none)
+  int max_chunks;
+};
+constexpr int kMaxChunks = 32;
+// Trips of a chunk: at least kMinTrips (writing and adding a chunk's 64 KB costs about 5 trips), and so many
+// that the batch makes kChunksPerSlot chunks per resident workgroup, for balance.  Measured on six shapes
+// with 1..16 heads per KV head: 8 per slot 0...25 % faster than 4, 4 twice as fast as 1; at least 6, 8 or 12
+// trips within 5 % of each other where total work is small.
+constexpr int kMinTrips = 8;
+constexpr int kChunksPerSlot = 8;
+// Chunks of a tile of n_it trips.  total_blocks: 64-query blocks over all schedule tiles (meta[2], left by
+// the boundary scan); tiles_x_heads: workgroup tiles per schedule tile x query heads; slots: workgroups the
+// chip holds.
+__device__ __forceinline__ int dkdv_chunks(int n_it, int total_blocks, int tiles_x_heads, int slots, int max_chunks) {
+  const float total = (float)total_blocks * (float)tiles_x_heads;
+  const int trips = max(kMinTrips, (int)(total / (float)(slots * kChunksPerSlot)) + 1);
+  return max(1, min(max_chunks, n_it / trips));
+}
+
 __device__ __forceinline__ void lds_barrier() {  // LDS traffic of this wave done, then workgroup barrier
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
@@ -457,7 +488,8 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
                   const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK,
                   void *__restrict__ dV, const int32_t *__restrict__ seg_end,
                   const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, int select,
-                  int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2, float scale) {
+                  DkdvSplit split, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2,
+                  float scale) {
   if (select != 0 && (((long long)N < (long long)kDkdvSmallBelow * meta[0]) != (select == 2))) return;  // workgroup-uniform
   constexpr int kKs = kDh / 16, kCb = kDh / 32;
   constexpr int kHf = kDh > 128 ? 2 : 1;  // 128-column sub-blocks per block
@@ -493,10 +525,19 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   const int kg = wave % kKg;
   const bool k_side = wave >= kKg;
   const int l32 = lane & 31, half = lane >> 5;
-  const int entry = uniform(kv_tile_order[blockIdx.x / (hkv * kSubTiles)]);
+  // workgroup -> (tile, KV head) pair `pair` in launch order, chunk `chunk` of its trips
+  int pair = blockIdx.x, chunk = 0;
+  const bool may_split = pair < split.limit * split.max_chunks;
+  if (may_split) {
+    chunk = (pair / hkv) % split.max_chunks;
+    pair = pair / (hkv * split.max_chunks) * hkv + pair % hkv;
+  } else {
+    pair -= split.limit * (split.max_chunks - 1);
+  }
+  const int entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
   const int tile = order_tile(entry);
-  const int sub = (blockIdx.x / hkv) % kSubTiles;
-  const int g = (blockIdx.x % hkv + head_rotation(entry)) % hkv;
+  const int sub = (pair / hkv) % kSubTiles;
+  const int g = (pair % hkv + head_rotation(entry)) % hkv;
   const int G = hq / hkv;
   const int r = tile / tiles_per_row, m = tile % tiles_per_row;
   const int row_end = (r + 1) * T;
@@ -504,6 +545,10 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   if (t0 >= row_end) return;  // workgroup-uniform: the schedule tile is ragged
   const int t_last = min(t0 + kKeys, row_end) - 1;
   const int ib_lo = t0 / kBS;
+  auto chunks_of = [&](int n_trips) {
+    return dkdv_chunks(n_trips, meta[2], kSubTiles * hq, 256 * Shape::kWgPerCu, split.max_chunks);
+  };
+  if (chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G)) return;  // workgroup-uniform
 
   const size_t row_bytes = (size_t)hq * d * 2;
   const size_t base_off = (size_t)ib_lo * kBS * row_bytes;
@@ -544,7 +589,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   auto put_stats = [&](uint16_t *dst) {
     if (threadIdx.x < 2 * kBS) ((float *)(dst + 2 * kBlkT))[threadIdx.x] = rstat * stat_mul;
   };
-  copy_block(S0, 0, ib_lo);  // needs nothing but the tile: in flight while the bounds arrive
+  if (chunk == 0) copy_block(S0, 0, ib_lo);  // needs nothing but the tile: in flight while the bounds arrive
 
   // Everything else the prologue needs depends on the tile only: all of it is requested before any
   // of it is looked at (a value made wave-uniform right after its load would hold the next load
@@ -579,8 +624,13 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   }
 
   const int ib_hi = (uniform(se_last_v) - 1) / kBS;  // query blocks end with the example of the tile's last key
-  const int nb = ib_hi - ib_lo + 1;
-  const int n_it = nb * G;
+  int n_it = (ib_hi - ib_lo + 1) * G;
+  int n_chunks = 1, it0 = 0;
+  if (may_split) {  // workgroup-uniform
+    n_chunks = chunks_of(n_it);
+    it0 = (int)((long long)n_it * chunk / n_chunks);
+    n_it = (int)((long long)n_it * (chunk + 1) / n_chunks) - it0;
+  }
   const int se_min = uniform(se_min_v), se_max = uniform(se_max_v);
   const int se_j = row_ok ? se_j_v : 0;  // queries j_abs <= i < se_j see key j_abs
 
@@ -604,7 +654,14 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   // stream the same block at about the same time, whereas ascending they would run 2 G steps apart per
   // tile and the blocks would have left the L2 (measured traffic of the kernel with 5 query heads per KV
   // head and examples of thousands of tokens: 3.8 GB ascending, 2.9 GB this way; the same run time).
-  int ib_cur = ib_lo, ib_nxt = ib_lo, hh_nxt = 0;
+  int ib_nxt = ib_lo, hh_nxt = 0;
+  if (chunk > 0) {  // the chunk's first trip in that order
+    const int b = it0 / G;
+    hh_nxt = it0 - b * G;
+    ib_nxt = G == 1 ? ib_lo + b : b == 0 ? ib_lo : ib_hi + 1 - b;
+    copy_block(S0, hh_nxt, ib_nxt);
+  }
+  int ib_cur = ib_nxt;
   // The K side runs one sub-block behind the V side: in step k the V side computes S(k), P(k) (left in
   // LDS) and dV(k), the K side computes dP(k) and, with the P(k-1) published by the previous barrier,
   // dS(k-1) and dK(k-1).  No wave waits for another inside a step; one barrier ends each step.  The
@@ -753,6 +810,20 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
     }
     if (act_b) k_finish(xb, tyb, 1);  // the last sub-block's dK
   }
+  if (n_chunks > 1) {  // leave the accumulators to the merge kernel: [wave][4-register group][lane] x 16 B
+    float *out = split.partial + ((size_t)pair * split.max_chunks + chunk) * (2 * kKeys * kDh) +
+                 ((kg * 2 + (k_side ? 1 : 0)) * kCb * 4 * 64 + lane) * 4;
+#pragma unroll
+    for (int cb = 0; cb < kCb; ++cb)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        f32x4 x;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) x[b] = acc[cb][4 * q4 + b];
+        *(f32x4 *)(out + (cb * 4 + q4) * 256) = x;
+      }
+    return;
+  }
   float *stage = (float *)stages + wave * kStageFloatsPerWave;
   const int nrows = wave_ok ? jw1 - jw0 + 1 : 0;
   if (k_side)
@@ -761,13 +832,82 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
     store_transposed_tile<EOut, kCb>(acc, 1.f, stage, dV, jw0, nrows, hkv, g, d);
 }
 
+// dK, dV of the tiles whose trips were cut into chunks: the sum of the chunks' accumulators.  One workgroup
+// per (schedule tile, KV head, 32-key group): waves 0, 1 add dV, waves 2, 3 dK, each 64 columns at a time, the
+// chunks in ascending order.  key_groups: 32-key groups per workgroup tile of the dK/dV kernel that ran (its
+// shape, `small` / `large`, is chosen by the same test as there).  Bound: the partial sums, written once and
+// read once, mostly from the last-level cache.
+template <class EOut, int kDh>
+__global__ void __launch_bounds__(256)
+dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *__restrict__ seg_end,
+                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, int select,
+                  DkdvSplit small, DkdvSplit large, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale) {
+  constexpr int kCb = kDh / 32;
+  __shared__ __attribute__((aligned(16))) float lds[4 * kStageFloatsPerWave];
+  const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && (long long)N < (long long)kDkdvSmallBelow * meta[0]));
+  const DkdvSplit split = is_small ? small : large;
+  const int key_groups = is_small || kDh > 128 ? 2 : 4;
+  const int wg_per_cu = is_small ? 2 : 1;
+  const int sub_tiles = VA_TILE / 32 / key_groups;
+  const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+  const int kgi = blockIdx.x % (VA_TILE / 32), head_slot = blockIdx.x / (VA_TILE / 32) % hkv;
+  const int rank = blockIdx.x / (VA_TILE / 32 * hkv);
+  const int sub = kgi / key_groups, kg = kgi % key_groups;
+  const int pair = (rank * sub_tiles + sub) * hkv + head_slot;
+  if (pair >= split.limit) return;
+  const int entry = uniform(kv_tile_order[rank]);
+  const int tile = order_tile(entry), g = (head_slot + head_rotation(entry)) % hkv;
+  const int r = tile / tiles_per_row, m = tile % tiles_per_row;
+  const int row_end = (r + 1) * T;
+  const int keys = 32 * key_groups, t0 = r * T + m * VA_TILE + sub * keys;
+  if (t0 + kg * 32 >= row_end) return;
+  const int t_last = min(t0 + keys, row_end) - 1;
+  const int n_it = ((uniform(seg_end[t_last]) - 1) / kBS - t0 / kBS + 1) * (hq / hkv);
+  const int n_chunks = dkdv_chunks(n_it, meta[2], sub_tiles * hq, 256 * wg_per_cu, split.max_chunks);
+  if (n_chunks == 1) return;  // stored by its only workgroup
+  const int side = wave >> 1;
+  const int nrows = min(32, row_end - (t0 + kg * 32));
+  const size_t slot = (size_t)2 * keys * kDh;
+  const float *src = split.partial + (size_t)pair * split.max_chunks * slot + ((kg * 2 + side) * kCb * 1024 + lane * 4);
+#pragma unroll 1
+  for (int p = wave & 1; p < (kCb + 1) / 2; p += 2) {
+    f32x16 acc[2];
+#pragma unroll
+    for (int cc = 0; cc < 2; ++cc)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[cc][v] = 0.f;
+    const int n4 = min(2, kCb - 2 * p) * 4;  // 4-register groups of this half
+    for (int c = 0; c < n_chunks; ++c) {
+      f32x4 x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = *(const f32x4 *)(src + c * slot + (p * 8 + min(i, n4 - 1)) * 256);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[i >> 2][(i & 3) * 4 + b] += x[i][b];
+    }
+    store_transposed_half<EOut, kCb>(acc, p, side ? scale : 1.f, lds + wave * kStageFloatsPerWave, side ? dK : dV,
+                                     t0 + kg * 32, nrows, hkv, g, d);
+  }
+}
+
 }  // namespace
+
+// How the (tile, KV head) pairs of one workgroup shape may be cut (see DkdvSplit): as far as the workspace
+// reaches, if it holds at least two chunks of every pair, and not where no row is long enough for three
+// chunks (the merge launch, about 4 us, would buy nothing).
+static DkdvSplit plan_split(float *partial, size_t slot_floats, long long n_pairs, long long max_trips) {
+  const long long slots = (long long)(kDkdvSplitBytes / 4 / slot_floats);
+  const long long chunks = slots / n_pairs < kMaxChunks ? slots / n_pairs : kMaxChunks;
+  if (chunks < 2 || max_trips < 3 * kMinTrips) return {partial, 0, 1};
+  return {partial, (int)n_pairs, (int)chunks};
+}
 
 template <class E, class EOut, int kDh>
 static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k, const uint16_t *v,
                          const uint16_t *o, const float *LSE, float *delta, void *dQ, void *dK, void *dV,
                          const va_segments &seg, int N, int T, int tiles_per_row, int hq, int hkv, int d,
-                         float scale, unsigned gq, unsigned gkv, hipStream_t stream, unsigned stages) {
+                         float scale, unsigned gq, unsigned gkv, float *partial, hipStream_t stream, unsigned stages) {
   const float scale_log2 = scale * kLog2e;
   if (stages & VA_STAGE_DQ)  // first: it also produces D for the dK/dV kernel
     dq_mfma_kernel<E, EOut, kDh><<<gq, 256, 0, stream>>>(g, q, k, v, o, LSE, delta, dQ, seg.seg_start,
@@ -775,26 +915,31 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
                                                          scale_log2, scale);
   if (stages & VA_STAGE_DKDV) {
     typedef DkdvShape<kDh, false> Large;
-    const unsigned g_large = gkv * (Large::kSubTiles / kSub);
+    typedef DkdvShape<kDh, (kDh <= 128)> Small;  // head_dim above 128 has one shape
+    const long long n_large = (long long)gkv * (Large::kSubTiles / kSub), n_small = (long long)gkv * (Small::kSubTiles / kSub);
+    // Nothing about the lengths is known on the host: both shapes are launched and the device picks, unless
+    // the caller's hint names the shape or no example can reach the mean length that calls for the large one.
+    bool run_large = kDh > 128 || !(stages & VA_HINT_SHORT_EXAMPLES);
+    bool run_small = kDh <= 128 && !(stages & VA_HINT_LONG_EXAMPLES);
+    if (run_small && T < kDkdvSmallBelow) run_large = false;
+    const int select_large = run_small ? 1 : 0, select_small = run_large ? 2 : 0;
+    const long long max_trips = (long long)(T / kBS + 1) * (hq / hkv);
+    const DkdvSplit sl = plan_split(partial, (size_t)2 * Large::kKeys * kDh, n_large, max_trips);
+    const DkdvSplit ss = plan_split(partial, (size_t)2 * Small::kKeys * kDh, n_small, max_trips);
+    if (run_large)
+      dkdv_mfma_kernel<E, EOut, kDh, false><<<(unsigned)(n_large + (long long)sl.limit * (sl.max_chunks - 1)), Large::kThreads, 0, stream>>>(
+          g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, select_large, sl, N, T,
+          tiles_per_row, hq, hkv, d, scale_log2, scale);
     if constexpr (kDh <= 128) {
-      typedef DkdvShape<kDh, true> Small;
-      const unsigned g_small = gkv * (Small::kSubTiles / kSub);
-      // nothing about the lengths is known on the host: both are launched and the device picks,
-      // unless the caller's hint names the shape (select 0 = run unconditionally)
-      const bool only_large = stages & VA_HINT_LONG_EXAMPLES, only_small = stages & VA_HINT_SHORT_EXAMPLES;
-      if (!only_small)
-        dkdv_mfma_kernel<E, EOut, kDh, false><<<g_large, Large::kThreads, 0, stream>>>(
-            g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, only_large ? 0 : 1, N, T,
+      if (run_small)
+        dkdv_mfma_kernel<E, EOut, kDh, true><<<(unsigned)(n_small + (long long)ss.limit * (ss.max_chunks - 1)), Small::kThreads, 0, stream>>>(
+            g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, select_small, ss, N, T,
             tiles_per_row, hq, hkv, d, scale_log2, scale);
-      if (!only_large)
-        dkdv_mfma_kernel<E, EOut, kDh, true><<<g_small, Small::kThreads, 0, stream>>>(
-            g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, only_small ? 0 : 2, N, T,
-            tiles_per_row, hq, hkv, d, scale_log2, scale);
-    } else {
-      dkdv_mfma_kernel<E, EOut, kDh, false><<<g_large, Large::kThreads, 0, stream>>>(
-          g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, 0, N, T, tiles_per_row, hq, hkv, d,
-          scale_log2, scale);
     }
+    if ((run_large && sl.limit) || (run_small && ss.limit))
+      dkdv_merge_kernel<EOut, kDh><<<(unsigned)(gkv / kSub * (VA_TILE / 32)), 256, 0, stream>>>(
+          dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, run_large && run_small ? 0 : run_small ? 2 : 1, ss, sl, N, T,
+          tiles_per_row, hq, hkv, d, scale);
   }
 }
 
@@ -809,7 +954,7 @@ static void launch_bwd_d(int d, A... a) {
 hipError_t launch_mfma_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                            const float *LSE, float *delta, void *dQ, void *dK, void *dV,
                            va_dtype grad_dt, const va_segments &seg, int rows, int T, int hq,
-                           int hkv, int d, va_dtype dt, float scale, hipStream_t stream, unsigned stages) {
+                           int hkv, int d, va_dtype dt, float scale, float *partial, hipStream_t stream, unsigned stages) {
   const int tiles_per_row = ceil_div(T, VA_TILE);
   const long long ntiles = (long long)rows * tiles_per_row * kSub;
   if (ntiles * hq > 0x7fffffffll) return hipErrorInvalidValue;
@@ -820,17 +965,17 @@ hipError_t launch_mfma_bwd(const void *dO, const void *Q, const void *K, const v
   if (dt == VA_F16) {
     if (grad_dt == VA_F32)
       launch_bwd_d<F16, float>(d, g, q, k, v, o, LSE, delta, dQ, dK, dV, seg, N, T, tiles_per_row, hq, hkv, d, scale,
-                               gq, gkv, stream, stages);
+                               gq, gkv, partial, stream, stages);
     else
       launch_bwd_d<F16, F16>(d, g, q, k, v, o, LSE, delta, dQ, dK, dV, seg, N, T, tiles_per_row, hq, hkv, d, scale,
-                             gq, gkv, stream, stages);
+                             gq, gkv, partial, stream, stages);
   } else {
     if (grad_dt == VA_F32)
       launch_bwd_d<Bf16, float>(d, g, q, k, v, o, LSE, delta, dQ, dK, dV, seg, N, T, tiles_per_row, hq, hkv, d, scale,
-                                gq, gkv, stream, stages);
+                                gq, gkv, partial, stream, stages);
     else
       launch_bwd_d<Bf16, Bf16>(d, g, q, k, v, o, LSE, delta, dQ, dK, dV, seg, N, T, tiles_per_row, hq, hkv, d, scale,
-                               gq, gkv, stream, stages);
+                               gq, gkv, partial, stream, stages);
   }
   return hipGetLastError();
 }

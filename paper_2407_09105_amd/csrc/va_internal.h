@@ -43,6 +43,9 @@ hipError_t launch_mfma_fwd(const void *Q, const void *K, const void *V, void *O,
 hipError_t launch_mfma_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                            const float *LSE, float *delta, void *dQ, void *dK, void *dV,
                            va_dtype grad_dt, const va_segments &seg, int rows, int T, int hq,
-                           int hkv, int d, va_dtype dt, float scale, hipStream_t stream, unsigned stages);
+                           int hkv, int d, va_dtype dt, float scale, float *partial, hipStream_t stream,
+                           unsigned stages);
+// Workspace of the MFMA dK/dV kernel's cut tiles (`partial`), beside D: 1024 chunks of 64 keys at head_dim 128.
+constexpr size_t kDkdvSplitBytes = (size_t)64 << 20;
 
 }  // namespace va

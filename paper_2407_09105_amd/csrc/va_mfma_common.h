@@ -236,43 +236,52 @@ template <class EOut> struct OutPack<EOut, true> {
   static __device__ __forceinline__ uint32_t two(float, float) { return 0u; }
 };
 
+// Columns 64 p .. 64 p + 63 of the tile; acc[cc] holds column block 2 p + cc.
+template <class EOut, int kCb>
+__device__ __forceinline__ void store_transposed_half(const f32x16 (&acc)[2], int p, float mul, float *stage,
+                                                      void *out, long long row0, int nrows, int H,
+                                                      int head, int d) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+  wave_lds_fence();  // the reads of the previous half (or tile) are done before it is overwritten
+#pragma unroll
+  for (int cc = 0; cc < 2; ++cc) {
+    if (2 * p + cc >= kCb) continue;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      f32x4 w;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) w[b] = acc[cc][4 * q4 + b] * mul;
+      *(f32x4 *)(stage + l32 * kStageStride + cc * 32 + q4 * 8 + half * 4) = w;
+    }
+  }
+  wave_lds_fence();
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int rr = it * 4 + (lane >> 4), c4 = lane & 15;
+    const int col = p * 64 + c4 * 4;
+    if (rr < nrows && col < d && col < kCb * 32) {
+      const f32x4 x = *(const f32x4 *)(stage + rr * kStageStride + c4 * 4);
+      const size_t off = ((size_t)(row0 + rr) * H + head) * d + col;
+      if (is_f32_out<EOut>::value) {
+        __builtin_nontemporal_store(x, (f32x4 *)((float *)out + off));
+      } else {
+        u32x2 w;
+        w.x = OutPack<EOut>::two(x[0], x[1]);
+        w.y = OutPack<EOut>::two(x[2], x[3]);
+        __builtin_nontemporal_store(w, (u32x2 *)((uint16_t *)out + off));
+      }
+    }
+  }
+}
+
 template <class EOut, int kCb>
 __device__ __forceinline__ void store_transposed_tile(const f32x16 (&acc)[kCb], float mul, float *stage,
                                                       void *out, long long row0, int nrows, int H,
                                                       int head, int d) {
-  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
 #pragma unroll
   for (int p = 0; p < (kCb + 1) / 2; ++p) {
-    wave_lds_fence();  // the reads of the previous half (or tile) are done before it is overwritten
-#pragma unroll
-    for (int cc = 0; cc < 2; ++cc) {
-      if (2 * p + cc >= kCb) continue;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        f32x4 w;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) w[b] = acc[2 * p + cc][4 * q4 + b] * mul;
-        *(f32x4 *)(stage + l32 * kStageStride + cc * 32 + q4 * 8 + half * 4) = w;
-      }
-    }
-    wave_lds_fence();
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int rr = it * 4 + (lane >> 4), c4 = lane & 15;
-      const int col = p * 64 + c4 * 4;
-      if (rr < nrows && col < d && col < kCb * 32) {
-        const f32x4 x = *(const f32x4 *)(stage + rr * kStageStride + c4 * 4);
-        const size_t off = ((size_t)(row0 + rr) * H + head) * d + col;
-        if (is_f32_out<EOut>::value) {
-          __builtin_nontemporal_store(x, (f32x4 *)((float *)out + off));
-        } else {
-          u32x2 w;
-          w.x = OutPack<EOut>::two(x[0], x[1]);
-          w.y = OutPack<EOut>::two(x[2], x[3]);
-          __builtin_nontemporal_store(w, (u32x2 *)((uint16_t *)out + off));
-        }
-      }
-    }
+    const f32x16 half[2] = {acc[2 * p], acc[2 * p + 1 < kCb ? 2 * p + 1 : 2 * p]};
+    store_transposed_half<EOut, kCb>(half, p, mul, stage, out, row0, nrows, H, head, d);
   }
 }
 

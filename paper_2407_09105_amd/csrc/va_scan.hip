@@ -391,13 +391,18 @@ tile_order_fused_kernel(const int32_t *__restrict__ seg_start, const int32_t *__
                         int32_t *__restrict__ meta, int32_t *__restrict__ order_q,
                         int32_t *__restrict__ order_kv) {
   __shared__ unsigned long long s_q[kFusedMaxTiles], s_kv[kFusedMaxTiles];
+  __shared__ int s_blocks;
+  if (threadIdx.x == 0) s_blocks = 0;
+  __syncthreads();
   for (int tile = threadIdx.x; tile < ntiles; tile += 256) {
     const int r = tile / tiles_per_row, m = tile % tiles_per_row;
     const int t0 = r * T + m * kTile;
     const int t1 = min(t0 + kTile, (r + 1) * T) - 1;
     const int ss0 = seg_start[t0], se0 = seg_end[t0], ss1 = seg_start[t1], se1 = seg_end[t1];
     s_q[tile] = tile_key(se0 - ss0, ss0, (t1 >> 6) - (ss0 >> 6) + 1);
-    s_kv[tile] = tile_key(se1 - ss1, ss1, ((se1 - 1) >> 6) - (t0 >> 6) + 1);
+    const int blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
+    s_kv[tile] = tile_key(se1 - ss1, ss1, blocks);
+    atomicAdd(&s_blocks, blocks);
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && nchunks > 0) {  // nchunks == 0: max_seqlen is already in meta
     int longest = 0;
@@ -405,6 +410,7 @@ tile_order_fused_kernel(const int32_t *__restrict__ seg_start, const int32_t *__
     meta[1] = longest;
   }
   __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) meta[2] = s_blocks;
   const int tile = blockIdx.x * 256 + threadIdx.x;
   if (tile >= ntiles) return;
   const unsigned long long cq = s_q[tile], ckv = s_kv[tile];
@@ -439,7 +445,9 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
   __shared__ int32_t s_ss[kSingleMaxTokens], s_se[kSingleMaxTokens], s_id[kSingleMaxTokens];
   __shared__ __attribute__((aligned(8))) uint8_t s_flag[kSingleMaxTokens];
   __shared__ unsigned long long s_q[kSingleMaxTiles], s_kv[kSingleMaxTiles];
+  __shared__ int s_blocks;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (threadIdx.x == 0) s_blocks = 0;
   {  // start flags, coalesced; all loads in flight together
     IdT id[kPerThread];
 #pragma unroll
@@ -499,7 +507,7 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
   if (lane == 0) s_cnt[w] = longest;
   if (threadIdx.x == (N - 1) / kPerThread) {  // the thread holding the last token knows the number of examples
     meta[0] = c;
-    for (int i = 2; i < 8; ++i) meta[i] = 0;
+    for (int i = 3; i < 8; ++i) meta[i] = 0;
     cu[c] = N;
   }
 #pragma unroll
@@ -515,12 +523,15 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
     const int t1 = min(t0 + kTile, (r + 1) * T) - 1;
     const int ss0 = s_ss[t0], se0 = s_se[t0], ss1 = s_ss[t1], se1 = s_se[t1];
     s_q[tile] = tile_key(se0 - ss0, ss0, (t1 >> 6) - (ss0 >> 6) + 1);
-    s_kv[tile] = tile_key(se1 - ss1, ss1, ((se1 - 1) >> 6) - (t0 >> 6) + 1);
+    const int blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
+    s_kv[tile] = tile_key(se1 - ss1, ss1, blocks);
+    atomicAdd(&s_blocks, blocks);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int i = 1; i < kWaves; ++i) longest = max(longest, s_cnt[i]);
     meta[1] = longest;
+    meta[2] = s_blocks;
   }
   if ((int)threadIdx.x < ntiles) {
     const int tile = threadIdx.x;
