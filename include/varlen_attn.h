@@ -150,8 +150,8 @@ size_t va_attn_workspace_bytes(int32_t n_tokens, int32_t hq, int32_t hkv, int32_
  * causal triangle are visited.
  *   dt            : element type of Q, K, V, O.  VA_BF16 and VA_F16 with d a multiple of 8 up to 256
  *                   run the MFMA kernels (unrolled for d = 64, 96, 128, 256; a smaller d is padded
- *                   with zero columns on the fly); other (dt, d <= 256) combinations run a plain
- *                   fp32-arithmetic kernel.
+ *                   with zero columns on the fly); other (dt, d <= 256) combinations run kernels
+ *                   in fp32 arithmetic (fp32 matrix instructions).
  *   softmax_scale : <= 0 means 1 / sqrt(d).
  *   workspace     : >= va_attn_workspace_bytes(..., 0) bytes (may be NULL when that is 0).
  */
@@ -204,11 +204,11 @@ va_status va_varlen_attn_bwd_noalloc(const void *dO, const void *Q, const void *
  * The backward in parts, so that a caller can time its kernels one by one with events on `stream`:
  * `stages` is an OR of the flags below.
  *   VA_STAGE_D    D = rowsum(dO * O) into `workspace`.
- *   VA_STAGE_DQ   dQ.  The plain kernels read D from `workspace`; the MFMA kernel forms D for its
- *                 own rows and (re)writes `workspace` with it - refined by the row sums of dS, which
- *                 take out the rounding of the stored O (so dK/dV are most accurate after this stage).
+ *   VA_STAGE_DQ   dQ.  The kernel forms D for its own rows and (re)writes `workspace` with it - the 16-bit
+ *                 one refined by the row sums of dS, which take out the rounding of the stored O (so
+ *                 dK/dV are most accurate after this stage).
  *   VA_STAGE_DKDV dK, dV; reads the D that an earlier VA_STAGE_D or VA_STAGE_DQ left in `workspace`.
- * Within one call the order is D (skipped when the MFMA dQ kernel makes it redundant), dQ, dK/dV;
+ * Within one call the order is D (skipped when dQ makes it redundant), dQ, dK/dV;
  * all three flags give exactly va_varlen_attn_bwd.
  * The MFMA dK/dV kernel has two workgroup shapes (head_dim <= 128): 128-key tiles for batches of long
  * examples, 64-key tiles otherwise.  By default both are enqueued and the device picks by the batch's

@@ -37,7 +37,7 @@ bool plan_layout(int32_t rows, int32_t T, PlanLayout *L) {
 }
 
 // The MFMA kernels take bf16 / fp16 tensors whose head_dim is a multiple of 8: the forward up to
-// 256, the backward kernels up to kMfmaDqMaxD / kMfmaDkdvMaxD; everything else runs on the plain kernels.
+// 256, the backward kernels up to kMfmaDqMaxD / kMfmaDkdvMaxD; everything else runs on the fp32-arithmetic kernels.
 constexpr int kMfmaFwdMaxD = 256, kMfmaDqMaxD = 256, kMfmaDkdvMaxD = 256;
 bool use_mfma(va_dtype dt, int d, int max_d) {
   static const bool force_generic = [] {
@@ -155,7 +155,7 @@ va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *
   if (use_mfma(dt, d, kMfmaFwdMaxD))
     e = va::launch_mfma_fwd(Q, K, V, O, LSE, *seg, rows, tokens_per_row, hq, hkv, d, dt, scale, (hipStream_t)stream);
   else
-    e = va::launch_generic_fwd(Q, K, V, O, LSE, *seg, N, hq, hkv, d, dt, scale, (hipStream_t)stream);
+    e = va::launch_f32_fwd(Q, K, V, O, LSE, *seg, N, hq, hkv, d, dt, scale, (hipStream_t)stream);
   return e == hipSuccess ? VA_OK : VA_ERR_HIP;
 }
 
@@ -190,23 +190,23 @@ va_status va_varlen_attn_bwd_stages(const void *dO, const void *Q, const void *K
   if (!workspace) return VA_ERR_NULL;
   if (workspace_bytes < need) return VA_ERR_WORKSPACE;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d);
-  float *delta = (float *)workspace;
+  float *delta = (float *)workspace, *partial = (float *)((char *)workspace + d_bytes(N, hq));
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const unsigned hints = stages & (VA_HINT_LONG_EXAMPLES | VA_HINT_SHORT_EXAMPLES);
   const unsigned mfma_stages = ((use_mfma(dt, d, kMfmaDqMaxD) ? VA_STAGE_DQ : 0u) |
                                 (use_mfma(dt, d, kMfmaDkdvMaxD) ? VA_STAGE_DKDV : 0u)) & stages;
   const unsigned plain_stages = stages & (VA_STAGE_DKDV | VA_STAGE_DQ) & ~mfma_stages;
-  // the MFMA dQ kernel forms D itself (and stores it for the dK/dV kernel, which it precedes)
-  if ((stages & VA_STAGE_D) && !(mfma_stages & VA_STAGE_DQ)) e = va::launch_delta(dO, O, delta, N, hq, d, dt, st);
+  // every dQ kernel forms D itself (and stores it for the dK/dV kernel, which it precedes)
+  if ((stages & VA_STAGE_D) && !(stages & VA_STAGE_DQ)) e = va::launch_delta(dO, O, delta, N, hq, d, dt, st);
   if (e != hipSuccess) return VA_ERR_HIP;
   if (mfma_stages)
     e = va::launch_mfma_bwd(dO, Q, K, V, O, LSE, delta, dQ, dK, dV, grad_dt, *seg, rows, tokens_per_row, hq, hkv,
-                            d, dt, scale, (float *)((char *)workspace + d_bytes(N, hq)), st, mfma_stages | hints);
+                            d, dt, scale, partial, st, mfma_stages | hints);
   if (e != hipSuccess) return VA_ERR_HIP;
   if (plain_stages)
-    e = va::launch_generic_bwd(dO, Q, K, V, LSE, delta, dQ, dK, dV, grad_dt, *seg, N, hq, hkv, d, dt, scale, st,
-                               plain_stages);
+    e = va::launch_f32_bwd(dO, Q, K, V, O, LSE, delta, dQ, dK, dV, grad_dt, *seg, rows, tokens_per_row, hq, hkv, d, dt,
+                           scale, partial, st, plain_stages);
   return e == hipSuccess ? VA_OK : VA_ERR_HIP;
 }
 

@@ -10,6 +10,10 @@ constexpr int kTile = VA_TILE;       // tokens per schedule tile
 constexpr int kScanChunk = 2048;     // tokens per workgroup in the boundary scan
 constexpr int kScanThreads = 256;
 
+// Workspace of the backward beside D (`partial`): fp32 sums of dK/dV tiles whose work is shared by several
+// workgroups; 1024 chunks of 64 keys at head_dim 128.
+constexpr size_t kDkdvSplitBytes = (size_t)64 << 20;
+
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // va_scan.hip
@@ -25,16 +29,16 @@ hipError_t launch_collate(const void *ids, const void *labels_in, va_itype it, c
 hipError_t launch_rope(const void *x, void *y, va_dtype dt, const void *pos, va_itype it, long long N,
                        int H, int d, double base, int inverse, hipStream_t stream);
 
-// va_generic.hip : plain fp32-arithmetic kernels, any head_dim <= 256
-hipError_t launch_generic_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
-                              const va_segments &seg, int N, int hq, int hkv, int d, va_dtype dt,
-                              float scale, hipStream_t stream);
+// va_f32.hip : fp32 arithmetic, any element type, any head_dim <= 256; the dQ kernel leaves D in `delta`
+hipError_t launch_f32_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
+                          const va_segments &seg, int N, int hq, int hkv, int d, va_dtype dt,
+                          float scale, hipStream_t stream);
+hipError_t launch_f32_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
+                          const float *LSE, float *delta, void *dQ, void *dK, void *dV, va_dtype grad_dt,
+                          const va_segments &seg, int rows, int T, int hq, int hkv, int d, va_dtype dt, float scale,
+                          float *partial, hipStream_t stream, unsigned stages);
 hipError_t launch_delta(const void *dO, const void *O, float *delta, int N, int hq, int d,
                         va_dtype dt, hipStream_t stream);
-hipError_t launch_generic_bwd(const void *dO, const void *Q, const void *K, const void *V,
-                              const float *LSE, const float *delta, void *dQ, void *dK, void *dV,
-                              va_dtype grad_dt, const va_segments &seg, int N, int hq, int hkv,
-                              int d, va_dtype dt, float scale, hipStream_t stream, unsigned stages);
 
 // va_fwd_mfma.hip / va_bwd_mfma.hip : bf16 / fp16, head_dim a multiple of 8 up to 256
 hipError_t launch_mfma_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
@@ -45,7 +49,5 @@ hipError_t launch_mfma_bwd(const void *dO, const void *Q, const void *K, const v
                            va_dtype grad_dt, const va_segments &seg, int rows, int T, int hq,
                            int hkv, int d, va_dtype dt, float scale, float *partial, hipStream_t stream,
                            unsigned stages);
-// Workspace of the MFMA dK/dV kernel's cut tiles (`partial`), beside D: 1024 chunks of 64 keys at head_dim 128.
-constexpr size_t kDkdvSplitBytes = (size_t)64 << 20;
 
 }  // namespace va

@@ -1,0 +1,45 @@
+"""The kernels in fp32 arithmetic at the edges of their tiles: 16-token tiles, 32-token blocks over four waves,
+head dims at the ends of each unrolling, dK/dV shared by several workgroups per tile, unaligned tensors."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2407_09105_amd import binding, workloads as wl
+from tests.gpu_util import DEV, assert_close, rel_l2, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,dtype", [
+    ([[1]], 1, 1, 1, "f32"),                       # one token, one column
+    ([[15]], 2, 1, 16, "f32"),                        # one short of a tile
+    ([[17, 31, 33]], 4, 4, 17, "f32"),             # element-wise loads, one past the smallest unrolling
+    ([[129, 3, 128], [260]], 6, 2, 32, "f32"),     # five blocks over four waves
+    ([[700, 41]], 8, 1, 64, "f32"),                # 8 heads on one KV head: dK/dV in parts
+    ([[300, 45]], 4, 2, 100, "f32"),               # padded to 128
+    ([[90, 70]], 2, 1, 132, "f32"),                # padded to 256
+    ([[90, 70]], 4, 1, 20, "bf16"),                # 16-bit head dims that are not a multiple of 8
+    ([[333]], 4, 1, 129, "f16"),
+])
+def test_f32_kernels(lengths, hq, hkv, d, dtype):
+    w = wl.make_custom(lengths, hq, hkv, d, dtype, seed=91)
+    print(f"case: {lengths} {hq}/{hkv} d={d} {dtype}", flush=True)
+    assert_close(run_gpu(w, grad_dtype=torch.float32, nan_fill=True), run_oracle(w), dtype)
+
+
+def test_unaligned_fp32_tensors():
+    # tensors that start 4 bytes off a 16-byte boundary take the element-wise loads and stores
+    w = wl.make_custom([[70, 33]], 2, 2, 64, "f32", seed=92)
+
+    def shifted(a):
+        t = torch.empty(a.size + 1, device=DEV)[1:].view(a.shape)
+        return t.copy_(torch.from_numpy(a))
+
+    q, k, v, do = (shifted(a) for a in (w.q, w.k, w.v, w.do))
+    seg = binding.pack_to_cu_seqlens(torch.from_numpy(w.position_ids).to(DEV))
+    o, lse = binding.varlen_attn_fwd(q, k, v, seg, out=shifted(np.zeros_like(w.q)))
+    dq, dk, dv = binding.varlen_attn_bwd(do, q, k, v, o, lse, seg, dq=shifted(np.zeros_like(w.q)))
+    cu = oracle.pack(w.position_ids)["cu_seqlens"]
+    for got, ref in zip((o, dq, dk, dv), (oracle.fwd(w.q, w.k, w.v, cu)[0], *oracle.bwd(w.do, w.q, w.k, w.v, cu))):
+        assert rel_l2(got.cpu().numpy(), ref) <= 1e-5   # fp32 sums of at most 70 products: 70 x 2^-24 = 4e-6, with room
