@@ -4,11 +4,17 @@
 // them; Section 3.1: ids restart at 0 at each example.  A token starts an example iff it
 // is the first of its row or its id is 0.  Integer work only, exact.
 //
-// Three passes over chunks of kScanChunk tokens (no cross-workgroup waiting):
+// Streams of up to 8192 tokens: one launch (pack_single_kernel).  Longer ones: three, over chunks of
+// kScanChunk tokens, without any waiting between workgroups:
 //   1. per-chunk aggregates: number of starts, last start, first start
-//   2. one workgroup scans the aggregates into per-chunk carries
-//   3. per-chunk final scan with carries -> seg_id, seg_start, seg_end, cu_seqlens, max_seqlen
-// then the tile schedule: a cost per query tile / key tile and a rank sort (heaviest first).
+//   2. per-chunk final scan, its carries taken from the aggregates -> seg_id, seg_start, seg_end,
+//      cu_seqlens, max_seqlen, and a sort key per schedule tile
+//   3. the tile order: a rank sort of the keys (heaviest first)
+// Bound: launch latency (4 to 6 us each, less when they follow each other closely).  65536 tokens in 256 tiles:
+// 15.9 us; 16384 tokens in 64: 12.5 us (with the carries in a launch of their own and each workgroup of the
+// ranking making the keys of all tiles: 26.3 and 15.7 us).
+#include <type_traits>
+
 #include "va_internal.h"
 
 namespace va {
@@ -62,10 +68,10 @@ __device__ __forceinline__ int wave_suffix_min(int x) {
 
 struct ChunkAgg { int count, last, first; };
 
-// pass 1
+// pass 1 (of more than 8192 tokens)
 template <typename IdT>
 __global__ void __launch_bounds__(kScanThreads)
-scan_aggregate_kernel(const IdT *__restrict__ pos, int N, int T, int32_t *__restrict__ agg) {
+scan_aggregate_kernel(const IdT *__restrict__ pos, int N, int T, int32_t *__restrict__ agg, int32_t *__restrict__ meta) {
   __shared__ int s_cnt[kScanThreads / 64], s_last[kScanThreads / 64], s_first[kScanThreads / 64];
   const int base = blockIdx.x * kScanChunk + threadIdx.x * kPerThread;
   bool flag[kPerThread];
@@ -96,13 +102,14 @@ scan_aggregate_kernel(const IdT *__restrict__ pos, int N, int T, int32_t *__rest
     agg[3 * blockIdx.x + 1] = last;
     agg[3 * blockIdx.x + 2] = first;
   }
+  // meta[1] (max_seqlen) and meta[2] (64-query blocks over all key tiles) are accumulated by the last pass
+  if (blockIdx.x == 0 && threadIdx.x < 8) meta[threadIdx.x] = 0;
 }
 
-// pass 2: carries[3*b] = starts before chunk b, [3*b+1] = last start before it, [3*b+2] = first
-// start after it (N if none).  Also meta[0] = n, meta[1] = 0 (max_seqlen accumulator), cu[n] = N.
+// only for streams of more than kFoldedCarryChunks chunks: carries[3*b] = starts before chunk b,
+// [3*b+1] = last start before it, [3*b+2] = first start after it (N if none).
 __global__ void __launch_bounds__(64)
-scan_carry_kernel(const int32_t *__restrict__ agg, int nchunks, int N, int32_t *__restrict__ carry,
-                  int32_t *__restrict__ meta, int32_t *__restrict__ cu) {
+scan_carry_kernel(const int32_t *__restrict__ agg, int nchunks, int N, int32_t *__restrict__ carry) {
   const int lane = threadIdx.x;
   int run_cnt = 0, run_last = -1;
   for (int b0 = 0; b0 < nchunks; b0 += 64) {
@@ -131,70 +138,6 @@ scan_carry_kernel(const int32_t *__restrict__ agg, int nchunks, int N, int32_t *
     if (b < nchunks) carry[3 * b + 2] = min(run_first, ef);
     run_first = min(run_first, __shfl(sf, 0, 64));
   }
-  if (lane == 0) {
-    meta[0] = run_cnt;
-    meta[1] = 0;
-    for (int i = 2; i < 8; ++i) meta[i] = 0;
-    cu[run_cnt] = N;
-  }
-}
-
-// pass 3
-template <typename IdT>
-__global__ void __launch_bounds__(kScanThreads)
-scan_finalize_kernel(const IdT *__restrict__ pos, int N, int T, const int32_t *__restrict__ carry,
-                     int32_t *__restrict__ cu, int32_t *__restrict__ seg_id,
-                     int32_t *__restrict__ seg_start, int32_t *__restrict__ seg_end,
-                     int32_t *__restrict__ meta) {
-  __shared__ int s_cnt[kScanThreads / 64], s_last[kScanThreads / 64], s_first[kScanThreads / 64];
-  const int base = blockIdx.x * kScanChunk + threadIdx.x * kPerThread;
-  bool flag[kPerThread];
-  start_flags(pos, base, N, T, flag);
-  int cnt = 0, last = -1, first = N;
-#pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
-    const int t = base + e;
-    if (flag[e]) { ++cnt; last = t; first = min(first, t); }
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int icnt = wave_incl_add(cnt), ilast = wave_incl_max(last), sfirst = wave_suffix_min(first);
-  if (lane == 63) { s_cnt[w] = icnt; s_last[w] = ilast; }
-  if (lane == 0) s_first[w] = sfirst;
-  __syncthreads();
-  // exclusive values for this thread: wave-exclusive + earlier waves + chunk carry
-  int ecnt = __shfl_up(icnt, 1, 64), elast = __shfl_up(ilast, 1, 64), efirst = __shfl_down(sfirst, 1, 64);
-  if (lane == 0) { ecnt = 0; elast = -1; }
-  if (lane == 63) efirst = N;
-  for (int i = 0; i < w; ++i) { ecnt += s_cnt[i]; elast = max(elast, s_last[i]); }
-  for (int i = w + 1; i < kScanThreads / 64; ++i) efirst = min(efirst, s_first[i]);
-  ecnt += carry[3 * blockIdx.x];
-  elast = max(elast, carry[3 * blockIdx.x + 1]);
-  efirst = min(efirst, carry[3 * blockIdx.x + 2]);
-  // next start strictly after each of this thread's tokens (right to left)
-  int nxt[kPerThread];
-  int run = efirst;
-#pragma unroll
-  for (int e = kPerThread - 1; e >= 0; --e) {
-    nxt[e] = run;
-    if (flag[e]) run = base + e;
-  }
-  int c = ecnt, l = elast, longest = 0;
-#pragma unroll
-  for (int e = 0; e < kPerThread; ++e) {
-    const int t = base + e;
-    if (t >= N) break;
-    if (flag[e]) {
-      cu[c] = t;
-      ++c;
-      l = t;
-      longest = max(longest, nxt[e] - t);
-    }
-    seg_id[t] = c - 1;
-    seg_start[t] = l;
-    seg_end[t] = nxt[e];
-  }
-  for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o, 64));
-  if (lane == 0 && longest > 0) atomicMax(&meta[1], longest);
 }
 
 // ---- tile schedule -------------------------------------------------------------------------
@@ -234,106 +177,41 @@ __device__ __forceinline__ int32_t order_entry(int tile, unsigned long long key,
   return (int32_t)((unsigned)tile | ((rot & 127u) << 24));
 }
 
-__global__ void __launch_bounds__(256)
-tile_cost_kernel(const int32_t *__restrict__ seg_start, const int32_t *__restrict__ seg_end, int T,
-                 int tiles_per_row, int ntiles, unsigned long long *__restrict__ key_q,
-                 unsigned long long *__restrict__ key_kv) {
-  const int tile = blockIdx.x * blockDim.x + threadIdx.x;
-  if (tile >= ntiles) return;
-  const int r = tile / tiles_per_row, m = tile % tiles_per_row;
-  const int t0 = r * T + m * kTile;
-  const int t1 = min(t0 + kTile, (r + 1) * T) - 1;  // last token of the tile
-  key_q[tile] = tile_key(seg_end[t0] - seg_start[t0], seg_start[t0], (t1 >> 6) - (seg_start[t0] >> 6) + 1);
-  key_kv[tile] = tile_key(seg_end[t1] - seg_start[t1], seg_start[t1], ((seg_end[t1] - 1) >> 6) - (t0 >> 6) + 1);
-}
-
-// order[rank] = tile, rank = number of tiles with a larger key (ties: lower index first)
-__global__ void __launch_bounds__(256)
-tile_rank_kernel(const unsigned long long *__restrict__ cost_q, const unsigned long long *__restrict__ cost_kv,
-                 int ntiles, int32_t *__restrict__ order_q, int32_t *__restrict__ order_kv) {
-  __shared__ unsigned long long s_q[256], s_kv[256];
-  const int tile = blockIdx.x * blockDim.x + threadIdx.x;
-  const unsigned long long cq = tile < ntiles ? cost_q[tile] : 0, ckv = tile < ntiles ? cost_kv[tile] : 0;
-  int rq = 0, rkv = 0;
-  for (int b0 = 0; b0 < ntiles; b0 += 256) {
-    const int o = b0 + threadIdx.x;
-    s_q[threadIdx.x] = o < ntiles ? cost_q[o] : 0;
-    s_kv[threadIdx.x] = o < ntiles ? cost_kv[o] : 0;
-    __syncthreads();
-    const int lim = min(256, ntiles - b0);
-    for (int i = 0; i < lim; ++i) {
-      const int other = b0 + i;
-      rq += (s_q[i] > cq) || (s_q[i] == cq && other < tile);
-      rkv += (s_kv[i] > ckv) || (s_kv[i] == ckv && other < tile);
-    }
-    __syncthreads();
-  }
-  if (tile < ntiles) { order_q[rq] = order_entry(tile, cq, rq); order_kv[rkv] = order_entry(tile, ckv, rkv); }
-}
-
-// ---- two-launch path for streams of up to kOnePassMaxChunks chunks --------------------------------
-// Launch 1: every chunk's workgroup derives its own carries by reading the ids of all other chunks
-// (count and last start before it, first start after it) -- redundant reads that stay in L2, in
-// exchange for no inter-workgroup dependency and no separate carry kernel.  Launch 2: sort keys of
-// all tiles into LDS, ranks of this workgroup's tiles, and max_seqlen from the per-chunk maxima.
-constexpr int kOnePassMaxChunks = 4;  // 8192 tokens: beyond that the redundant reads cost more than two launches
-constexpr int kFusedMaxTiles = 2048;
-
-template <typename IdT>
+// pass 2.  kFoldCarry: the workgroup derives its carries from all chunks' aggregates by itself (a launch less);
+// otherwise `agg` holds the carries made by scan_carry_kernel.  The sort keys of the schedule tiles are
+// written here too: the key of a query tile needs its first token's example, that of a key tile its last's.
+constexpr int kFoldedCarryChunks = 4096;  // 8 M tokens: beyond that re-reading the aggregates costs more than a launch
+template <typename IdT, bool kFoldCarry>
 __global__ void __launch_bounds__(kScanThreads)
-scan_onepass_kernel(const IdT *__restrict__ pos, int N, int T, int32_t *__restrict__ cu,
-                    int32_t *__restrict__ seg_id, int32_t *__restrict__ seg_start,
-                    int32_t *__restrict__ seg_end, int32_t *__restrict__ meta,
-                    int32_t *__restrict__ chunk_longest) {
-  __shared__ int s_cnt[kScanThreads / 64], s_last[kScanThreads / 64], s_first[kScanThreads / 64];
-  __shared__ int c_cnt, c_last, c_first;
+scan_finalize_kernel(const IdT *__restrict__ pos, int N, int T, const int32_t *__restrict__ agg, int nchunks,
+                     int tiles_per_row, bool wide, int32_t *__restrict__ cu, int32_t *__restrict__ seg_id,
+                     int32_t *__restrict__ seg_start, int32_t *__restrict__ seg_end, int32_t *__restrict__ meta,
+                     unsigned long long *__restrict__ key_q, unsigned long long *__restrict__ key_kv) {
+  constexpr int kWaves = kScanThreads / 64;
+  __shared__ int s_cnt[kWaves], s_last[kWaves], s_first[kWaves];
+  __shared__ int c_cnt[kWaves], c_last[kWaves], c_first[kWaves];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int chunk0 = blockIdx.x * kScanChunk;
-  // this thread's own tokens: their loads go out together with the sweep's below
-  const int base = chunk0 + threadIdx.x * kPerThread;
+  const int base = blockIdx.x * kScanChunk + threadIdx.x * kPerThread;
   bool flag[kPerThread];
   start_flags(pos, base, N, T, flag);
-  // Carries from the rest of the stream in one sweep: every id outside this chunk is read once, all
-  // loads of a thread issued together (the stream has at most kOnePassMaxChunks chunks), giving the
-  // number of starts and the last start before the chunk and the first start after it.
-  {
-    constexpr int kSweep = kOnePassMaxChunks * kScanChunk / kScanThreads;
-    const int chunk1 = chunk0 + kScanChunk;
-    IdT id[kSweep];  // unconditional loads (index clamped), so that they are all in flight together
-#pragma unroll
-    for (int u = 0; u < kSweep; ++u) id[u] = pos[min(u * kScanThreads + (int)threadIdx.x, N - 1)];
-    int cnt = 0, last = -1, first = N;
-    int r = threadIdx.x % T;  // position inside the packed row, advanced without further divisions
-    const int step = kScanThreads % T;
-#pragma unroll
-    for (int u = 0; u < kSweep; ++u) {
-      const int t = u * kScanThreads + threadIdx.x;
-      if (t < N && (t < chunk0 || t >= chunk1) && (id[u] == 0 || r == 0)) {
-        if (t < chunk0) { ++cnt; last = t; } else first = min(first, t);
-      }
-      r += step;
-      if (r >= T) r -= T;
+  if (kFoldCarry) {
+    int bc = 0, bl = -1, bf = N;
+    for (int b = threadIdx.x; b < nchunks; b += kScanThreads) {
+      const int ac = agg[3 * b], al = agg[3 * b + 1], af = agg[3 * b + 2];
+      if (b < (int)blockIdx.x) { bc += ac; bl = max(bl, al); }
+      if (b > (int)blockIdx.x) bf = min(bf, af);
     }
     for (int o = 32; o > 0; o >>= 1) {
-      cnt += __shfl_xor(cnt, o, 64);
-      last = max(last, __shfl_xor(last, o, 64));
-      first = min(first, __shfl_xor(first, o, 64));
+      bc += __shfl_xor(bc, o, 64);
+      bl = max(bl, __shfl_xor(bl, o, 64));
+      bf = min(bf, __shfl_xor(bf, o, 64));
     }
-    if (lane == 0) { s_cnt[w] = cnt; s_last[w] = last; s_first[w] = first; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int i = 1; i < kScanThreads / 64; ++i) {
-        cnt += s_cnt[i];
-        last = max(last, s_last[i]);
-        first = min(first, s_first[i]);
-      }
-      c_cnt = cnt;
-      c_last = last;
-      c_first = first;
-    }
+    if (lane == 0) { c_cnt[w] = bc; c_last[w] = bl; c_first[w] = bf; }
+  } else if (lane == 0) {  // one wave brings the carries, the others what leaves them as they are
+    c_cnt[w] = w == 0 ? agg[3 * blockIdx.x] : 0;
+    c_last[w] = w == 0 ? agg[3 * blockIdx.x + 1] : -1;
+    c_first[w] = w == 0 ? agg[3 * blockIdx.x + 2] : N;
   }
-  __syncthreads();
-  // local scan, as in scan_finalize_kernel
   int cnt = 0, last = -1, first = N;
 #pragma unroll
   for (int e = 0; e < kPerThread; ++e) {
@@ -344,14 +222,18 @@ scan_onepass_kernel(const IdT *__restrict__ pos, int N, int T, int32_t *__restri
   if (lane == 63) { s_cnt[w] = icnt; s_last[w] = ilast; }
   if (lane == 0) s_first[w] = sfirst;
   __syncthreads();
+  // exclusive values for this thread: wave-exclusive + earlier waves + chunk carry
   int ecnt = __shfl_up(icnt, 1, 64), elast = __shfl_up(ilast, 1, 64), efirst = __shfl_down(sfirst, 1, 64);
   if (lane == 0) { ecnt = 0; elast = -1; }
   if (lane == 63) efirst = N;
   for (int i = 0; i < w; ++i) { ecnt += s_cnt[i]; elast = max(elast, s_last[i]); }
-  for (int i = w + 1; i < kScanThreads / 64; ++i) efirst = min(efirst, s_first[i]);
-  ecnt += c_cnt;
-  elast = max(elast, c_last);
-  efirst = min(efirst, c_first);
+  for (int i = w + 1; i < kWaves; ++i) efirst = min(efirst, s_first[i]);
+  for (int i = 0; i < kWaves; ++i) {
+    ecnt += c_cnt[i];
+    elast = max(elast, c_last[i]);
+    efirst = min(efirst, c_first[i]);
+  }
+  // next start strictly after each of this thread's tokens (right to left)
   int nxt[kPerThread];
   int run = efirst;
 #pragma unroll
@@ -359,68 +241,81 @@ scan_onepass_kernel(const IdT *__restrict__ pos, int N, int T, int32_t *__restri
     nxt[e] = run;
     if (flag[e]) run = base + e;
   }
-  int c = ecnt, l = elast, longest = 0;
+  int c = ecnt, l = elast, longest = 0, blocks = 0;
+  int row = base / T, x = base - row * T;  // packed row and position in it, advanced without further divisions
+  int id8[kPerThread], ss8[kPerThread];
 #pragma unroll
   for (int e = 0; e < kPerThread; ++e) {
     const int t = base + e;
-    if (t >= N) break;
-    if (flag[e]) { cu[c] = t; ++c; l = t; longest = max(longest, nxt[e] - t); }
-    seg_id[t] = c - 1;
-    seg_start[t] = l;
-    seg_end[t] = nxt[e];
+    if (t < N) {
+      if (flag[e]) {
+        cu[c] = t;
+        ++c;
+        l = t;
+        longest = max(longest, nxt[e] - t);
+      }
+      const int row_last = t - x + T - 1, m = x / kTile;
+      if (x % kTile == 0)  // first token of a schedule tile
+        key_q[row * tiles_per_row + m] = tile_key(nxt[e] - l, l, ((t + min(kTile - 1, row_last - t)) >> 6) - (l >> 6) + 1);
+      if (x % kTile == kTile - 1 || t == row_last) {  // last token of one
+        const int n_blocks = ((nxt[e] - 1) >> 6) - ((t - x % kTile) >> 6) + 1;
+        key_kv[row * tiles_per_row + m] = tile_key(nxt[e] - l, l, n_blocks);
+        blocks += n_blocks;
+      }
+      if (t == N - 1) { meta[0] = c; cu[c] = N; }
+    }
+    id8[e] = c - 1;
+    ss8[e] = l;
+    if (++x == T) { x = 0; ++row; }
   }
-  for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o, 64));
-  __syncthreads();  // s_cnt free
-  if (lane == 0) s_cnt[w] = longest;
-  // the last thread of the last chunk knows the total number of examples
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) {
-    meta[0] = c;
-    for (int i = 2; i < 8; ++i) meta[i] = 0;
-    cu[c] = N;
+  if (wide && base <= N - kPerThread) {  // wide: the arrays are 16-byte aligned; `base` is a multiple of 8
+#pragma unroll
+    for (int e = 0; e < kPerThread; e += 4) {
+      *(int4 *)(seg_id + base + e) = make_int4(id8[e], id8[e + 1], id8[e + 2], id8[e + 3]);
+      *(int4 *)(seg_start + base + e) = make_int4(ss8[e], ss8[e + 1], ss8[e + 2], ss8[e + 3]);
+      *(int4 *)(seg_end + base + e) = make_int4(nxt[e], nxt[e + 1], nxt[e + 2], nxt[e + 3]);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < kPerThread; ++e)
+      if (base + e < N) { seg_id[base + e] = id8[e]; seg_start[base + e] = ss8[e]; seg_end[base + e] = nxt[e]; }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < kScanThreads / 64; ++i) longest = max(longest, s_cnt[i]);
-    chunk_longest[blockIdx.x] = longest;
+  for (int o = 32; o > 0; o >>= 1) {
+    longest = max(longest, __shfl_xor(longest, o, 64));
+    blocks += __shfl_xor(blocks, o, 64);
   }
+  if (lane == 0 && longest > 0) atomicMax(&meta[1], longest);
+  if (lane == 0 && blocks > 0) atomicAdd(&meta[2], blocks);
 }
 
+// order[rank] = tile, rank = number of tiles with a larger key (ties: lower index first).  32 tiles per
+// workgroup, 8 threads to a tile, each of which compares it with every eighth key of a slab in LDS: one
+// thread per tile took 17 us for 272 tiles (a chain of 272 reads and compares, after making all keys), this takes 5.4.
+constexpr int kRankTiles = 32;
+constexpr int kRankSlab = 512;
 __global__ void __launch_bounds__(256)
-tile_order_fused_kernel(const int32_t *__restrict__ seg_start, const int32_t *__restrict__ seg_end, int T,
-                        int tiles_per_row, int ntiles, const int32_t *__restrict__ chunk_longest, int nchunks,
-                        int32_t *__restrict__ meta, int32_t *__restrict__ order_q,
-                        int32_t *__restrict__ order_kv) {
-  __shared__ unsigned long long s_q[kFusedMaxTiles], s_kv[kFusedMaxTiles];
-  __shared__ int s_blocks;
-  if (threadIdx.x == 0) s_blocks = 0;
-  __syncthreads();
-  for (int tile = threadIdx.x; tile < ntiles; tile += 256) {
-    const int r = tile / tiles_per_row, m = tile % tiles_per_row;
-    const int t0 = r * T + m * kTile;
-    const int t1 = min(t0 + kTile, (r + 1) * T) - 1;
-    const int ss0 = seg_start[t0], se0 = seg_end[t0], ss1 = seg_start[t1], se1 = seg_end[t1];
-    s_q[tile] = tile_key(se0 - ss0, ss0, (t1 >> 6) - (ss0 >> 6) + 1);
-    const int blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
-    s_kv[tile] = tile_key(se1 - ss1, ss1, blocks);
-    atomicAdd(&s_blocks, blocks);
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && nchunks > 0) {  // nchunks == 0: max_seqlen is already in meta
-    int longest = 0;
-    for (int i = 0; i < nchunks; ++i) longest = max(longest, chunk_longest[i]);
-    meta[1] = longest;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0) meta[2] = s_blocks;
-  const int tile = blockIdx.x * 256 + threadIdx.x;
-  if (tile >= ntiles) return;
-  const unsigned long long cq = s_q[tile], ckv = s_kv[tile];
+tile_rank_kernel(const unsigned long long *__restrict__ key_q, const unsigned long long *__restrict__ key_kv,
+                 int ntiles, int32_t *__restrict__ order_q, int32_t *__restrict__ order_kv) {
+  __shared__ unsigned long long s_q[kRankSlab], s_kv[kRankSlab];
+  const int part = threadIdx.x & 7, tile = blockIdx.x * kRankTiles + ((int)threadIdx.x >> 3);
+  const unsigned long long cq = key_q[min(tile, ntiles - 1)], ckv = key_kv[min(tile, ntiles - 1)];
   int rq = 0, rkv = 0;
-  for (int o = 0; o < ntiles; ++o) {
-    rq += (s_q[o] > cq) || (s_q[o] == cq && o < tile);
-    rkv += (s_kv[o] > ckv) || (s_kv[o] == ckv && o < tile);
+  for (int b0 = 0; b0 < ntiles; b0 += kRankSlab) {
+    const int lim = min(kRankSlab, ntiles - b0);
+    for (int i = threadIdx.x; i < lim; i += 256) { s_q[i] = key_q[b0 + i]; s_kv[i] = key_kv[b0 + i]; }
+    __syncthreads();
+    for (int i = part; i < lim; i += 8) {
+      const int other = b0 + i;
+      rq += (s_q[i] > cq) || (s_q[i] == cq && other < tile);
+      rkv += (s_kv[i] > ckv) || (s_kv[i] == ckv && other < tile);
+    }
+    __syncthreads();
   }
-  order_q[rq] = order_entry(tile, cq, rq);
-  order_kv[rkv] = order_entry(tile, ckv, rkv);
+  for (int o = 1; o < 8; o <<= 1) {
+    rq += __shfl_xor(rq, o, 64);
+    rkv += __shfl_xor(rkv, o, 64);
+  }
+  if (part == 0 && tile < ntiles) { order_q[rq] = order_entry(tile, cq, rq); order_kv[rkv] = order_entry(tile, ckv, rkv); }
 }
 
 // ---- one launch for streams of up to kSingleMaxTokens tokens -----------------------------------
@@ -442,12 +337,11 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
                    int32_t *__restrict__ order_kv) {
   constexpr int kWaves = kSingleThreads / 64;
   __shared__ int s_cnt[kWaves], s_last[kWaves], s_first[kWaves];
-  __shared__ int32_t s_ss[kSingleMaxTokens], s_se[kSingleMaxTokens], s_id[kSingleMaxTokens];
+  __shared__ __attribute__((aligned(16))) int32_t s_ss[kSingleMaxTokens], s_se[kSingleMaxTokens], s_id[kSingleMaxTokens];
   __shared__ __attribute__((aligned(8))) uint8_t s_flag[kSingleMaxTokens];
   __shared__ unsigned long long s_q[kSingleMaxTiles], s_kv[kSingleMaxTiles];
-  __shared__ int s_blocks;
+  __shared__ int s_blocks[kSingleMaxTiles / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (threadIdx.x == 0) s_blocks = 0;
   {  // start flags, coalesced; all loads in flight together
     IdT id[kPerThread];
 #pragma unroll
@@ -493,19 +387,26 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
     if (flag[e]) run = base + e;
   }
   int c = ecnt, l = elast, longest = 0;
+  int id8[kPerThread], ss8[kPerThread];
 #pragma unroll
   for (int e = 0; e < kPerThread; ++e) {
     const int t = base + e;
-    if (t >= N) break;
-    if (flag[e]) { cu[c] = t; ++c; l = t; longest = max(longest, nxt[e] - t); }
-    s_id[t] = c - 1;
-    s_ss[t] = l;
-    s_se[t] = nxt[e];
+    if (flag[e]) { cu[c] = t; ++c; l = t; longest = max(longest, nxt[e] - t); }  // never set at t >= N
+    id8[e] = c - 1;
+    ss8[e] = l;
+  }
+  // 16-byte LDS stores (a 4-byte store per token, 32 bytes apart over the lanes, is an 8-way bank conflict:
+  // 9.8 -> 8.6 us for 8192 tokens); what lies beyond N is never read
+#pragma unroll
+  for (int e = 0; e < kPerThread; e += 4) {
+    *(int4 *)(s_id + base + e) = make_int4(id8[e], id8[e + 1], id8[e + 2], id8[e + 3]);
+    *(int4 *)(s_ss + base + e) = make_int4(ss8[e], ss8[e + 1], ss8[e + 2], ss8[e + 3]);
+    *(int4 *)(s_se + base + e) = make_int4(nxt[e], nxt[e + 1], nxt[e + 2], nxt[e + 3]);
   }
   for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o, 64));
   __syncthreads();  // s_cnt free; s_id / s_ss / s_se complete
   if (lane == 0) s_cnt[w] = longest;
-  if (threadIdx.x == (N - 1) / kPerThread) {  // the thread holding the last token knows the number of examples
+  if ((int)threadIdx.x == (N - 1) / kPerThread) {  // the thread holding the last token knows the number of examples
     meta[0] = c;
     for (int i = 3; i < 8; ++i) meta[i] = 0;
     cu[c] = N;
@@ -516,6 +417,7 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
     if (t < N) { seg_id[t] = s_id[t]; seg_start[t] = s_ss[t]; seg_end[t] = s_se[t]; }
   }
   // tile keys
+  int blocks = 0;
   if ((int)threadIdx.x < ntiles) {
     const int tile = threadIdx.x;
     const int r = tile / tiles_per_row, m = tile % tiles_per_row;
@@ -523,15 +425,18 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
     const int t1 = min(t0 + kTile, (r + 1) * T) - 1;
     const int ss0 = s_ss[t0], se0 = s_se[t0], ss1 = s_ss[t1], se1 = s_se[t1];
     s_q[tile] = tile_key(se0 - ss0, ss0, (t1 >> 6) - (ss0 >> 6) + 1);
-    const int blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
+    blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
     s_kv[tile] = tile_key(se1 - ss1, ss1, blocks);
-    atomicAdd(&s_blocks, blocks);
+  }
+  if (w < kSingleMaxTiles / 64) {
+    for (int o = 32; o > 0; o >>= 1) blocks += __shfl_xor(blocks, o, 64);
+    if (lane == 0) s_blocks[w] = blocks;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int i = 1; i < kWaves; ++i) longest = max(longest, s_cnt[i]);
     meta[1] = longest;
-    meta[2] = s_blocks;
+    meta[2] = s_blocks[0] + s_blocks[1] + s_blocks[2] + s_blocks[3];
   }
   if ((int)threadIdx.x < ntiles) {
     const int tile = threadIdx.x;
@@ -564,42 +469,23 @@ hipError_t launch_pack(const void *pos, va_itype it, int rows, int T, const va_s
           seg.meta, seg.q_tile_order, seg.kv_tile_order);
     return hipGetLastError();
   }
-  if (nchunks <= kOnePassMaxChunks && ntiles <= kFusedMaxTiles) {
-    int32_t *chunk_longest = seg.scratch;  // [nchunks]
-    if (it == VA_I64)
-      scan_onepass_kernel<int64_t><<<nchunks, kScanThreads, 0, stream>>>(
-          (const int64_t *)pos, N, T, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end, seg.meta, chunk_longest);
-    else
-      scan_onepass_kernel<int32_t><<<nchunks, kScanThreads, 0, stream>>>(
-          (const int32_t *)pos, N, T, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end, seg.meta, chunk_longest);
-    tile_order_fused_kernel<<<ceil_div(ntiles, 256), 256, 0, stream>>>(
-        seg.seg_start, seg.seg_end, T, tiles_per_row, ntiles, chunk_longest, nchunks, seg.meta, seg.q_tile_order,
-        seg.kv_tile_order);
-    return hipGetLastError();
-  }
+  const bool fold = nchunks <= kFoldedCarryChunks;
   int32_t *agg = seg.scratch;                  // [3 * nchunks]
   int32_t *carry = seg.scratch + 3 * nchunks;  // [3 * nchunks]
-  unsigned long long *cost_q = (unsigned long long *)(seg.scratch + 8 * nchunks);  // [ntiles] sort keys
-  unsigned long long *cost_kv = cost_q + ntiles;                                   // [ntiles]
-  if (it == VA_I64)
-    scan_aggregate_kernel<int64_t><<<nchunks, kScanThreads, 0, stream>>>((const int64_t *)pos, N, T, agg);
-  else
-    scan_aggregate_kernel<int32_t><<<nchunks, kScanThreads, 0, stream>>>((const int32_t *)pos, N, T, agg);
-  scan_carry_kernel<<<1, 64, 0, stream>>>(agg, nchunks, N, carry, seg.meta, seg.cu_seqlens);
-  if (it == VA_I64)
-    scan_finalize_kernel<int64_t><<<nchunks, kScanThreads, 0, stream>>>(
-        (const int64_t *)pos, N, T, carry, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end, seg.meta);
-  else
-    scan_finalize_kernel<int32_t><<<nchunks, kScanThreads, 0, stream>>>(
-        (const int32_t *)pos, N, T, carry, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end, seg.meta);
-  const int tb = ceil_div(ntiles, 256);
-  if (ntiles <= kFusedMaxTiles) {  // keys of all tiles fit in LDS: keys and ranks in one launch
-    tile_order_fused_kernel<<<tb, 256, 0, stream>>>(seg.seg_start, seg.seg_end, T, tiles_per_row, ntiles, nullptr, 0,
-                                                    seg.meta, seg.q_tile_order, seg.kv_tile_order);
-    return hipGetLastError();
-  }
-  tile_cost_kernel<<<tb, 256, 0, stream>>>(seg.seg_start, seg.seg_end, T, tiles_per_row, ntiles, cost_q, cost_kv);
-  tile_rank_kernel<<<tb, 256, 0, stream>>>(cost_q, cost_kv, ntiles, seg.q_tile_order, seg.kv_tile_order);
+  unsigned long long *key_q = (unsigned long long *)(seg.scratch + 8 * nchunks);  // [ntiles] sort keys
+  unsigned long long *key_kv = key_q + ntiles;                                    // [ntiles]
+  const bool wide = (((uintptr_t)seg.seg_id | (uintptr_t)seg.seg_start | (uintptr_t)seg.seg_end) & 15) == 0;
+  auto scan = [&](auto *ids) {
+    typedef std::remove_cv_t<std::remove_pointer_t<decltype(ids)>> IdT;
+    scan_aggregate_kernel<IdT><<<nchunks, kScanThreads, 0, stream>>>(ids, N, T, agg, seg.meta);
+    if (!fold) scan_carry_kernel<<<1, 64, 0, stream>>>(agg, nchunks, N, carry);
+    auto *finalize = fold ? scan_finalize_kernel<IdT, true> : scan_finalize_kernel<IdT, false>;
+    finalize<<<nchunks, kScanThreads, 0, stream>>>(ids, N, T, fold ? agg : carry, nchunks, tiles_per_row, wide, seg.cu_seqlens,
+                                                   seg.seg_id, seg.seg_start, seg.seg_end, seg.meta, key_q, key_kv);
+  };
+  if (it == VA_I64) scan((const int64_t *)pos);
+  else scan((const int32_t *)pos);
+  tile_rank_kernel<<<ceil_div(ntiles, kRankTiles), 256, 0, stream>>>(key_q, key_kv, ntiles, seg.q_tile_order, seg.kv_tile_order);
   return hipGetLastError();
 }
 

@@ -1,13 +1,34 @@
-"""Rotary embedding at the sizes where their launch rules and remainders lie."""
+"""Boundary scan and rotary embedding at the sizes where their launch rules and remainders lie."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import oracle
 from paper_2407_09105_amd import workloads as wl
+from tests.gpu_util import assert_seg_equal
+from tests.test_gpu_pack import _check_orders, _gpu_pack
 from tests.test_gpu_rope import _rel_l2, _run
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R,T,maxlen", [
+    (8193, 1, 1),          # a tile per token
+    (1, 10240, 10240),     # whole chunks of 2048 tokens, one example
+    (33, 257, 257),        # tiles of one token
+    (5, 4099, 700),        # rows that straddle chunks, tiles that straddle chunks
+    (9, 1000003, 5000),    # more chunks than a workgroup folds into its own carries
+])
+def test_pack(R, T, maxlen):
+    rng = np.random.default_rng(R + T)
+    pos = np.empty((R, T), dtype=np.int64)
+    for r in range(R):
+        starts = np.unique(np.concatenate([[0], rng.integers(0, T, size=max(1, 2 * T // maxlen))]))
+        pos[r] = np.arange(T) - np.repeat(starts, np.diff(np.concatenate([starts, [T]])))
+    got = _gpu_pack(pos)
+    assert_seg_equal(got, oracle.pack(pos))
+    if R * T < 100000:
+        _check_orders(got, pos)
 
 
 @pytest.mark.parametrize("shape", [(4099, 1, 16), (1027, 7, 128), (3, 200, 128), (700, 5, 80), (259, 3, 6), (2, 130, 256)])
