@@ -1,4 +1,4 @@
-"""Boundary scan and rotary embedding at the sizes where their launch rules and remainders lie."""
+"""Boundary scan, collator and rotary embedding at the sizes where their launch rules and remainders lie."""
 import numpy as np
 import pytest
 import torch
@@ -6,6 +6,7 @@ import torch
 from oracle import oracle
 from paper_2407_09105_amd import workloads as wl
 from tests.gpu_util import assert_seg_equal
+from tests.test_gpu_collate import _compare
 from tests.test_gpu_pack import _check_orders, _gpu_pack
 from tests.test_gpu_rope import _rel_l2, _run
 
@@ -29,6 +30,17 @@ def test_pack(R, T, maxlen):
     assert_seg_equal(got, oracle.pack(pos))
     if R * T < 100000:
         _check_orders(got, pos)
+
+
+@pytest.mark.parametrize("n", [1, 255, 2047, 2048, 2049])  # up to 2048 examples run in one launch
+@pytest.mark.parametrize("cut", [0, 5, -7])
+def test_collate(n, cut):
+    rng = np.random.default_rng(n)
+    lengths = rng.integers(0, 9, size=n).astype(np.int32)
+    lengths[0] = 8
+    ids = rng.integers(0, 1000, size=(n, 8))
+    total = int(np.minimum(lengths, 8).sum())
+    _compare(ids, lengths, 0 if cut == 5 else total - cut, pad_id=3)
 
 
 @pytest.mark.parametrize("shape", [(4099, 1, 16), (1027, 7, 128), (3, 200, 128), (700, 5, 80), (259, 3, 6), (2, 130, 256)])
