@@ -16,6 +16,8 @@
 //                      dV^T += dO^T P, dK^T += Q^T dS; the dV and the dK halves run on different waves.
 // In both, the streamed index lies on the accumulator's register axis and feeds the last
 // contraction as a B operand straight from registers (see va_mfma_common.h).
+#include <type_traits>
+
 #include "va_internal.h"
 #include "va_mfma_common.h"
 
@@ -877,15 +879,25 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[cc][v] = 0.f;
     const int n4 = min(2, kCb - 2 * p) * 4;  // 4-register groups of this half
-    for (int c = 0; c < n_chunks; ++c) {
-      f32x4 x[8];
+    // kFly chunks are requested together (8 KB each): one at a time is a chain of memory round trips
+    auto add = [&](int c0, auto fly) {
+      constexpr int kFly = decltype(fly)::value;
+      f32x4 x[kFly][8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = *(const f32x4 *)(src + c * slot + (p * 8 + min(i, n4 - 1)) * 256);
+      for (int f = 0; f < kFly; ++f)
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 8; ++i) x[f][i] = *(const f32x4 *)(src + (c0 + f) * slot + (p * 8 + min(i, n4 - 1)) * 256);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[i >> 2][(i & 3) * 4 + b] += x[i][b];
-    }
+      for (int f = 0; f < kFly; ++f)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) acc[i >> 2][(i & 3) * 4 + b] += x[f][i][b];
+    };
+    int c = 0;
+    for (; c + 4 <= n_chunks; c += 4) add(c, std::integral_constant<int, 4>());
+    if (c + 2 <= n_chunks) { add(c, std::integral_constant<int, 2>()); c += 2; }
+    if (c < n_chunks) add(c, std::integral_constant<int, 1>());
     store_transposed_half<EOut, kCb>(acc, p, side ? scale : 1.f, lds + wave * kStageFloatsPerWave, side ? dK : dV,
                                      t0 + kg * 32, nrows, hkv, g, d);
   }
