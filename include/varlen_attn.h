@@ -171,8 +171,9 @@ va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *
  * large entries of P and dS through the matrix units in two 16-bit parts.
  *   grad_dt   : element type of dQ, dK, dV: VA_F32, or the 16-bit type of the inputs (VA_BF16 also
  *               with fp32 inputs); other pairs: VA_ERR_UNSUPPORTED.
- *   workspace : >= va_attn_workspace_bytes(..., 1) bytes (holds D, [Hq, N] float, and 64 MiB for the
- *               partial sums of key tiles whose work is shared by several workgroups).
+ *   workspace : va_attn_workspace_bytes(..., 1) bytes: D, [Hq, N] float, and 64 MiB for the partial sums
+ *               of key tiles whose work is shared by several workgroups.  At least D has to fit (its size
+ *               rounded up to 256 bytes); with less room behind it fewer tiles, or none, are shared.
  */
 va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const void *V,
                              const void *O, const float *LSE, void *dQ, void *dK, void *dV,

@@ -305,7 +305,7 @@ def varlen_attn_bwd(do, q, k, v, o, lse, seg: Segments, softmax_scale: float = 0
     else:
         ws = workspace
         _need_cuda(ws)
-        need = lib().va_attn_workspace_bytes(N, hq, hkv, d, 1)
+        need = (N * hq * 4 + 255) // 256 * 256  # D; what bwd_workspace adds lets more workgroups share a key tile
         if ws.dtype != torch.float32 or ws.numel() * 4 < need or ws.device != q.device:
             raise ValueError(f"workspace must be a contiguous float32 tensor of at least {need} bytes on {q.device}")
     args = [do.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),

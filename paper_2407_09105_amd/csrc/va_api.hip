@@ -186,11 +186,13 @@ va_status va_varlen_attn_bwd_stages(const void *dO, const void *Q, const void *K
   va_status s = check_bwd(dO, Q, K, V, O, LSE, dQ, dK, dV, grad_dt, seg, rows, tokens_per_row, hq, hkv, d, dt, stages);
   if (s != VA_OK) return s;
   const int N = rows * tokens_per_row;
-  const size_t need = va_attn_workspace_bytes(N, hq, hkv, d, 1);
   if (!workspace) return VA_ERR_NULL;
-  if (workspace_bytes < need) return VA_ERR_WORKSPACE;
+  if (workspace_bytes < d_bytes(N, hq)) return VA_ERR_WORKSPACE;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d);
-  float *delta = (float *)workspace, *partial = (float *)((char *)workspace + d_bytes(N, hq));
+  float *delta = (float *)workspace;
+  const uintptr_t behind = align_up((uintptr_t)workspace + d_bytes(N, hq)), end = (uintptr_t)workspace + workspace_bytes;
+  va::Partials partial = {(float *)behind, end > behind ? end - behind : 0};
+  if (partial.bytes > va::kDkdvSplitBytes) partial.bytes = va::kDkdvSplitBytes;
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const unsigned hints = stages & (VA_HINT_LONG_EXAMPLES | VA_HINT_SHORT_EXAMPLES);

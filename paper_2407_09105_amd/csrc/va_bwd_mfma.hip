@@ -457,9 +457,8 @@ template <int kDh, bool kSmall> struct DkdvShape {
 //           (plan_split below); with many tiles it is one, and no merge kernel is launched.
 //   device: how many it gets follows from its own trips and the batch's total.
 struct DkdvSplit {
-  float *partial;   // [limit * max_chunks] slots of 2 * kKeys * kDh floats
-  int limit;        // (tile, KV head) pairs that may be cut, counted in launch order (0: none)
-  int max_chunks;
+  float *partial;   // [pairs * max_chunks] slots of 2 * kKeys * kDh floats
+  int max_chunks;   // per (tile, KV head) pair; 1: no tile is cut
 };
 constexpr int kMaxChunks = 32;
 // Trips of a chunk: at least kMinTrips (writing and adding a chunk's 64 KB costs about 5 trips), and so many
@@ -483,7 +482,9 @@ __device__ __forceinline__ void lds_barrier() {  // LDS traffic of this wave don
 
 // select: 0 = run; 1 = run only if the examples have kDkdvSmallBelow tokens or more on average; 2 =
 // only if they have fewer (meta[0] is the number of examples, left there by the boundary scan).
-template <class E, class EOut, int kDh, bool kSmall>
+// kCut: tiles may be cut (split.max_chunks > 1).  Without it the chunk arithmetic is not compiled in: it costs
+// scalar registers, in the head_dim 256 shape 29 spilled ones and 1.5 % of the time.
+template <class E, class EOut, int kDh, bool kSmall, bool kCut>
 __global__ void __launch_bounds__((DkdvShape<kDh, kSmall>::kThreads), (DkdvShape<kDh, kSmall>::kWgPerCu))
 dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
                   const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
@@ -529,12 +530,9 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   const int l32 = lane & 31, half = lane >> 5;
   // workgroup -> (tile, KV head) pair `pair` in launch order, chunk `chunk` of its trips
   int pair = blockIdx.x, chunk = 0;
-  const bool may_split = pair < split.limit * split.max_chunks;
-  if (may_split) {
+  if constexpr (kCut) {
     chunk = (pair / hkv) % split.max_chunks;
     pair = pair / (hkv * split.max_chunks) * hkv + pair % hkv;
-  } else {
-    pair -= split.limit * (split.max_chunks - 1);
   }
   const int entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
   const int tile = order_tile(entry);
@@ -550,7 +548,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   auto chunks_of = [&](int n_trips) {
     return dkdv_chunks(n_trips, meta[2], kSubTiles * hq, 256 * Shape::kWgPerCu, split.max_chunks);
   };
-  if (chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G)) return;  // workgroup-uniform
+  if (kCut && chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G)) return;  // workgroup-uniform
 
   const size_t row_bytes = (size_t)hq * d * 2;
   const size_t base_off = (size_t)ib_lo * kBS * row_bytes;
@@ -591,7 +589,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   auto put_stats = [&](uint16_t *dst) {
     if (threadIdx.x < 2 * kBS) ((float *)(dst + 2 * kBlkT))[threadIdx.x] = rstat * stat_mul;
   };
-  if (chunk == 0) copy_block(S0, 0, ib_lo);  // needs nothing but the tile: in flight while the bounds arrive
+  if (!kCut || chunk == 0) copy_block(S0, 0, ib_lo);  // needs nothing but the tile: in flight while the bounds arrive
 
   // Everything else the prologue needs depends on the tile only: all of it is requested before any
   // of it is looked at (a value made wave-uniform right after its load would hold the next load
@@ -628,7 +626,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   const int ib_hi = (uniform(se_last_v) - 1) / kBS;  // query blocks end with the example of the tile's last key
   int n_it = (ib_hi - ib_lo + 1) * G;
   int n_chunks = 1, it0 = 0;
-  if (may_split) {  // workgroup-uniform
+  if constexpr (kCut) {
     n_chunks = chunks_of(n_it);
     it0 = (int)((long long)n_it * chunk / n_chunks);
     n_it = (int)((long long)n_it * (chunk + 1) / n_chunks) - it0;
@@ -657,7 +655,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   // tile and the blocks would have left the L2 (measured traffic of the kernel with 5 query heads per KV
   // head and examples of thousands of tokens: 3.8 GB ascending, 2.9 GB this way; the same run time).
   int ib_nxt = ib_lo, hh_nxt = 0;
-  if (chunk > 0) {  // the chunk's first trip in that order
+  if (kCut && chunk > 0) {  // the chunk's first trip in that order
     const int b = it0 / G;
     hh_nxt = it0 - b * G;
     ib_nxt = G == 1 ? ib_lo + b : b == 0 ? ib_lo : ib_hi + 1 - b;
@@ -812,7 +810,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
     }
     if (act_b) k_finish(xb, tyb, 1);  // the last sub-block's dK
   }
-  if (n_chunks > 1) {  // leave the accumulators to the merge kernel: [wave][4-register group][lane] x 16 B
+  if (kCut && n_chunks > 1) {  // leave the accumulators to the merge kernel: [wave][4-register group][lane] x 16 B
     float *out = split.partial + ((size_t)pair * split.max_chunks + chunk) * (2 * kKeys * kDh) +
                  ((kg * 2 + (k_side ? 1 : 0)) * kCb * 4 * 64 + lane) * 4;
 #pragma unroll
@@ -856,7 +854,6 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
   const int rank = blockIdx.x / (VA_TILE / 32 * hkv);
   const int sub = kgi / key_groups, kg = kgi % key_groups;
   const int pair = (rank * sub_tiles + sub) * hkv + head_slot;
-  if (pair >= split.limit) return;
   const int entry = uniform(kv_tile_order[rank]);
   const int tile = order_tile(entry), g = (head_slot + head_rotation(entry)) % hkv;
   const int r = tile / tiles_per_row, m = tile % tiles_per_row;
@@ -908,18 +905,17 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
 // How the (tile, KV head) pairs of one workgroup shape may be cut (see DkdvSplit): as far as the workspace
 // reaches, if it holds at least two chunks of every pair, and not where no row is long enough for three
 // chunks (the merge launch, about 4 us, would buy nothing).
-static DkdvSplit plan_split(float *partial, size_t slot_floats, long long n_pairs, long long max_trips) {
-  const long long slots = (long long)(kDkdvSplitBytes / 4 / slot_floats);
+static DkdvSplit plan_split(const Partials &partial, size_t slot_floats, long long n_pairs, long long max_trips) {
+  const long long slots = (long long)(partial.bytes / 4 / slot_floats);
   const long long chunks = slots / n_pairs < kMaxChunks ? slots / n_pairs : kMaxChunks;
-  if (chunks < 2 || max_trips < 3 * kMinTrips) return {partial, 0, 1};
-  return {partial, (int)n_pairs, (int)chunks};
+  return {partial.p, chunks < 2 || max_trips < 3 * kMinTrips ? 1 : (int)chunks};
 }
 
 template <class E, class EOut, int kDh>
 static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k, const uint16_t *v,
                          const uint16_t *o, const float *LSE, float *delta, void *dQ, void *dK, void *dV,
                          const va_segments &seg, int N, int T, int tiles_per_row, int hq, int hkv, int d,
-                         float scale, unsigned gq, unsigned gkv, float *partial, hipStream_t stream, unsigned stages) {
+                         float scale, unsigned gq, unsigned gkv, const Partials &partial, hipStream_t stream, unsigned stages) {
   const float scale_log2 = scale * kLog2e;
   if (stages & VA_STAGE_DQ)  // first: it also produces D for the dK/dV kernel
     dq_mfma_kernel<E, EOut, kDh><<<gq, 256, 0, stream>>>(g, q, k, v, o, LSE, delta, dQ, seg.seg_start,
@@ -938,17 +934,19 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     const long long max_trips = (long long)(T / kBS + 1) * (hq / hkv);
     const DkdvSplit sl = plan_split(partial, (size_t)2 * Large::kKeys * kDh, n_large, max_trips);
     const DkdvSplit ss = plan_split(partial, (size_t)2 * Small::kKeys * kDh, n_small, max_trips);
+    auto launch = [&](auto *kernel, long long pairs, int threads, int select, const DkdvSplit &split) {
+      kernel<<<(unsigned)(pairs * split.max_chunks), threads, 0, stream>>>(g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta,
+                                                                           select, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
+    };
     if (run_large)
-      dkdv_mfma_kernel<E, EOut, kDh, false><<<(unsigned)(n_large + (long long)sl.limit * (sl.max_chunks - 1)), Large::kThreads, 0, stream>>>(
-          g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, select_large, sl, N, T,
-          tiles_per_row, hq, hkv, d, scale_log2, scale);
+      launch(sl.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, false, true> : dkdv_mfma_kernel<E, EOut, kDh, false, false>, n_large,
+             Large::kThreads, select_large, sl);
     if constexpr (kDh <= 128) {
       if (run_small)
-        dkdv_mfma_kernel<E, EOut, kDh, true><<<(unsigned)(n_small + (long long)ss.limit * (ss.max_chunks - 1)), Small::kThreads, 0, stream>>>(
-            g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, select_small, ss, N, T,
-            tiles_per_row, hq, hkv, d, scale_log2, scale);
+        launch(ss.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, true, true> : dkdv_mfma_kernel<E, EOut, kDh, true, false>, n_small,
+               Small::kThreads, select_small, ss);
     }
-    if ((run_large && sl.limit) || (run_small && ss.limit))
+    if ((run_large && sl.max_chunks > 1) || (run_small && ss.max_chunks > 1))
       dkdv_merge_kernel<EOut, kDh><<<(unsigned)(gkv / kSub * (VA_TILE / 32)), 256, 0, stream>>>(
           dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, run_large && run_small ? 0 : run_small ? 2 : 1, ss, sl, N, T,
           tiles_per_row, hq, hkv, d, scale);
@@ -966,7 +964,7 @@ static void launch_bwd_d(int d, A... a) {
 hipError_t launch_mfma_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                            const float *LSE, float *delta, void *dQ, void *dK, void *dV,
                            va_dtype grad_dt, const va_segments &seg, int rows, int T, int hq,
-                           int hkv, int d, va_dtype dt, float scale, float *partial, hipStream_t stream, unsigned stages) {
+                           int hkv, int d, va_dtype dt, float scale, const Partials &partial, hipStream_t stream, unsigned stages) {
   const int tiles_per_row = ceil_div(T, VA_TILE);
   const long long ntiles = (long long)rows * tiles_per_row * kSub;
   if (ntiles * hq > 0x7fffffffll) return hipErrorInvalidValue;

@@ -483,7 +483,7 @@ struct Args {  // one call's tensors and sizes; unused ones stay null
   float scale;
   hipStream_t stream;
   unsigned stages;
-  float *partial;  // kDkdvSplitBytes
+  Partials partial;
 };
 
 template <typename T, bool kVec, int kDh> hipError_t run_fwd(const Args &a) {
@@ -507,12 +507,12 @@ template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
     // a row allows, and as far as the workspace reaches.
     const size_t n = (size_t)a.N * a.hkv * a.d;
     const long long rounds = (long long)ceil_div(a.T, kStep) * (a.hq / a.hkv) / kWaves;
-    const long long parts = std::max(1ll, std::min({512 / gkv, rounds / 2, (long long)(kDkdvSplitBytes / 8 / n)}));
+    const long long parts = std::max(1ll, std::min({512 / gkv, rounds / 2, (long long)(a.partial.bytes / 8 / n)}));
     f32_dkdv_kernel<T, kVec, kDh><<<dim3((unsigned)gkv, (unsigned)parts), 64 * kWaves, 0, a.stream>>>(
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
-        a.partial, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, scale_log2, a.scale);
+        a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, scale_log2, a.scale);
     if (parts > 1)
-      f32_add_parts_kernel<<<(unsigned)((2 * n + 255) / 256), 256, 0, a.stream>>>(a.partial, (int)parts, n, a.dK, a.dV, a.out_dt);
+      f32_add_parts_kernel<<<(unsigned)((2 * n + 255) / 256), 256, 0, a.stream>>>(a.partial.p, (int)parts, n, a.dK, a.dV, a.out_dt);
   }
   return hipGetLastError();
 }
@@ -541,14 +541,14 @@ template <bool kFwd> hipError_t by_type(va_dtype dt, const Args &a) {
 hipError_t launch_f32_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
                           const va_segments &seg, int N, int hq, int hkv, int d, va_dtype dt,
                           float scale, hipStream_t stream) {
-  Args a = {Q, K, V, nullptr, nullptr, O, nullptr, nullptr, LSE, nullptr, &seg, N, 0, hq, hkv, d, dt, scale, stream, 0, nullptr};
+  Args a = {Q, K, V, nullptr, nullptr, O, nullptr, nullptr, LSE, nullptr, &seg, N, 0, hq, hkv, d, dt, scale, stream, 0, {nullptr, 0}};
   return by_type<true>(dt, a);
 }
 
 hipError_t launch_f32_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                           const float *LSE, float *delta, void *dQ, void *dK, void *dV, va_dtype grad_dt,
                           const va_segments &seg, int rows, int T, int hq, int hkv, int d, va_dtype dt, float scale,
-                          float *partial, hipStream_t stream, unsigned stages) {
+                          const Partials &partial, hipStream_t stream, unsigned stages) {
   Args a = {Q, K, V, O, dO, dQ, dK, dV, const_cast<float *>(LSE), delta, &seg, rows * T, T, hq, hkv, d, grad_dt, scale,
             stream, stages, partial};
   return by_type<false>(dt, a);

@@ -10,9 +10,15 @@ constexpr int kTile = VA_TILE;       // tokens per schedule tile
 constexpr int kScanChunk = 2048;     // tokens per workgroup in the boundary scan
 constexpr int kScanThreads = 256;
 
-// Workspace of the backward beside D (`partial`): fp32 sums of dK/dV tiles whose work is shared by several
+// Workspace of the backward beside D: fp32 sums of dK/dV tiles whose work is shared by several
 // workgroups; 1024 chunks of 64 keys at head_dim 128.
 constexpr size_t kDkdvSplitBytes = (size_t)64 << 20;
+
+// The part of a caller's workspace behind D, at most kDkdvSplitBytes; may be empty (then no tile is shared).
+struct Partials {
+  float *p;
+  size_t bytes;
+};
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -36,7 +42,7 @@ hipError_t launch_f32_fwd(const void *Q, const void *K, const void *V, void *O, 
 hipError_t launch_f32_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                           const float *LSE, float *delta, void *dQ, void *dK, void *dV, va_dtype grad_dt,
                           const va_segments &seg, int rows, int T, int hq, int hkv, int d, va_dtype dt, float scale,
-                          float *partial, hipStream_t stream, unsigned stages);
+                          const Partials &partial, hipStream_t stream, unsigned stages);
 hipError_t launch_delta(const void *dO, const void *O, float *delta, int N, int hq, int d,
                         va_dtype dt, hipStream_t stream);
 
@@ -47,7 +53,7 @@ hipError_t launch_mfma_fwd(const void *Q, const void *K, const void *V, void *O,
 hipError_t launch_mfma_bwd(const void *dO, const void *Q, const void *K, const void *V, const void *O,
                            const float *LSE, float *delta, void *dQ, void *dK, void *dV,
                            va_dtype grad_dt, const va_segments &seg, int rows, int T, int hq,
-                           int hkv, int d, va_dtype dt, float scale, float *partial, hipStream_t stream,
+                           int hkv, int d, va_dtype dt, float scale, const Partials &partial, hipStream_t stream,
                            unsigned stages);
 
 }  // namespace va

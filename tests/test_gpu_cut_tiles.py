@@ -5,7 +5,8 @@ import pytest
 import torch
 
 from paper_2407_09105_amd import binding, workloads as wl
-from tests.gpu_util import assert_close, run_gpu, run_oracle
+from tests.gpu_util import DEV, assert_close, run_gpu, run_oracle, to_dev
+from tests.test_gpu_guards import _guarded
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,19 @@ def test_cut_tiles(lengths, hq, hkv, d, dtype, hint):
     again = run_gpu(w, grad_dtype=torch.float32, nan_fill=True, hint=hint)
     for key in ("dQ", "dK", "dV"):
         assert np.array_equal(got[key], again[key]), key   # the chunks are added in a fixed order
+
+
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "f32")])
+@pytest.mark.parametrize("room", [0, 1, 3 << 20])   # bytes behind D: none, too little for a chunk, for some chunks only
+def test_workspace_of_any_size(d, dtype, room):
+    w = wl.make_custom([[640]], 4, 1, d, dtype, seed=72)
+    N, hq, hkv = 640, 4, 1
+    q, k, v, do = (to_dev(a, dtype) for a in (w.q, w.k, w.v, w.do))
+    seg = binding.pack_to_cu_seqlens(torch.from_numpy(w.position_ids).to(DEV))
+    o, lse = binding.varlen_attn_fwd(q, k, v, seg)
+    (ws,), check = _guarded([(((N * hq * 4 + 255) // 256 * 64 + (room + 3) // 4,), torch.float32)])
+    dq, dk, dv = binding.varlen_attn_bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float32, workspace=ws)
+    check()
+    ref = run_oracle(w)
+    f = lambda t: t.float().cpu().numpy().astype(np.float64)
+    assert_close({"O": f(o), "LSE": f(lse), "dQ": f(dq), "dK": f(dk), "dV": f(dv)}, ref, dtype)
