@@ -53,16 +53,30 @@ def flops(cfg, pairs):
     return f, b
 
 
+def mean_blocks(pos_np):
+    """64-query blocks that a 256-key tile streams, on average over the batch."""
+    rows, T = pos_np.shape
+    start = pos_np.reshape(-1) == 0
+    start[::T] = True
+    starts = np.flatnonzero(start)
+    end = np.repeat(np.append(starts[1:], rows * T), np.diff(np.append(starts, rows * T)))
+    t0 = (np.arange(rows)[:, None] * T + np.arange(0, T, 256)[None, :])
+    t1 = np.minimum(t0 + 256, (np.arange(rows)[:, None] + 1) * T) - 1
+    return float(np.mean((end[t1] - 1) // 64 - t0 // 64 + 1))
+
+
 class GpuRun:
     """Device buffers + one `step()` of the path; stage events for per-kernel timing."""
 
     def __init__(self, torch, binding, pos_np, q, k, v, do, n_examples=None):
         self.torch, self.b = torch, binding
         # the host made these lengths, so it can name the dK/dV kernel's shape instead of having the
-        # device pick between two launches (the device's own rule: mean example length >= 1024 tokens)
+        # device pick between two launches (the device's own rule: mean example length >= 1024 tokens, or
+        # an average of 12 or more 64-query blocks per 256-key tile)
         self.hint = 0
         if n_examples:
-            self.hint = binding.HINT_LONG_EXAMPLES if pos_np.size >= 1024 * n_examples else binding.HINT_SHORT_EXAMPLES
+            long_ = pos_np.size >= 1024 * n_examples or mean_blocks(pos_np) >= 12
+            self.hint = binding.HINT_LONG_EXAMPLES if long_ else binding.HINT_SHORT_EXAMPLES
         self.pos = torch.from_numpy(pos_np).cuda()
         self.q, self.k, self.v, self.do = q, k, v, do
         self.seg = binding.Segments(pos_np.shape[0], pos_np.shape[1], "cuda")

@@ -171,8 +171,9 @@ va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *
  * large entries of P and dS through the matrix units in two 16-bit parts.
  *   grad_dt   : element type of dQ, dK, dV: VA_F32, or the 16-bit type of the inputs (VA_BF16 also
  *               with fp32 inputs); other pairs: VA_ERR_UNSUPPORTED.
- *   workspace : va_attn_workspace_bytes(..., 1) bytes: D, [Hq, N] float, and 64 MiB for the partial sums
- *               of key tiles whose work is shared by several workgroups.  At least D has to fit (its size
+ *   workspace : va_attn_workspace_bytes(..., 1) bytes: D, [Hq, N] float, and 64 or (Hq > Hkv and
+ *               24576 < N * Hkv <= 98304) 192 MiB for the partial sums of key tiles whose work is shared by
+ *               several workgroups.  At least D has to fit (its size
  *               rounded up to 256 bytes); with less room behind it fewer tiles, or none, are shared.
  */
 va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const void *V,
@@ -213,10 +214,11 @@ va_status va_varlen_attn_bwd_noalloc(const void *dO, const void *Q, const void *
  * all three flags give exactly va_varlen_attn_bwd.
  * The MFMA dK/dV kernel has two workgroup shapes (head_dim <= 128): 128-key tiles for batches of long
  * examples, 64-key tiles otherwise.  By default both are enqueued and the device picks by the batch's
- * mean example length (the host never sees the lengths); the other's workgroups leave at once.  A
- * caller that knows its lengths can add ONE of
- *   VA_HINT_LONG_EXAMPLES   mean example length >= 1024 tokens: only the 128-key shape is enqueued
- *   VA_HINT_SHORT_EXAMPLES  otherwise: only the 64-key shape
+ * lengths (the host never sees them): the 128-key shape where the mean example has 1024 tokens or more, or
+ * where examples that long do most of the work.  The other's workgroups leave at once.  A caller that knows
+ * its lengths can add ONE of
+ *   VA_HINT_LONG_EXAMPLES   only the 128-key shape is enqueued
+ *   VA_HINT_SHORT_EXAMPLES  only the 64-key shape
  * Either shape computes every result whatever the lengths; a wrong hint costs speed only.
  * Arguments, validation and errors as va_varlen_attn_bwd; no stage bit, both hints or unknown bits:
  * VA_ERR_UNSUPPORTED.

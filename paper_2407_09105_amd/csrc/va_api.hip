@@ -137,7 +137,9 @@ va_status va_rope_apply(const void *x, void *y, va_dtype dt, const void *positio
 size_t va_attn_workspace_bytes(int32_t n_tokens, int32_t hq, int32_t hkv, int32_t d, int is_bwd) {
   if (n_tokens <= 0 || hq <= 0 || hkv <= 0 || d <= 0) return 0;
   if (!is_bwd) return 0;
-  return d_bytes(n_tokens, hq) + va::kDkdvSplitBytes;
+  const long long rows = (long long)n_tokens * hkv;
+  const bool more = hkv < hq && d <= 256 && rows > va::kMoreSplitRows / 4 && rows <= va::kMoreSplitRows;
+  return d_bytes(n_tokens, hq) + (more ? va::kMoreSplitBytes : va::kDkdvSplitBytes);
 }
 
 va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
@@ -192,7 +194,7 @@ va_status va_varlen_attn_bwd_stages(const void *dO, const void *Q, const void *K
   float *delta = (float *)workspace;
   const uintptr_t behind = align_up((uintptr_t)workspace + d_bytes(N, hq)), end = (uintptr_t)workspace + workspace_bytes;
   va::Partials partial = {(float *)behind, end > behind ? end - behind : 0};
-  if (partial.bytes > va::kDkdvSplitBytes) partial.bytes = va::kDkdvSplitBytes;
+  if (partial.bytes > va::kMoreSplitBytes) partial.bytes = va::kMoreSplitBytes;
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const unsigned hints = stages & (VA_HINT_LONG_EXAMPLES | VA_HINT_SHORT_EXAMPLES);

@@ -428,14 +428,27 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
 // head_dim above 128 (kDh = 256): operand and accumulator tiles are twice as large, so a workgroup is
 // 4 waves = (64-key tile, KV head), one wave per SIMD with 512 registers each; blocks are two
 // 128-column halves, and the tile's own K and V rows pass through the memory of the second stage.
-// Two shapes for head_dim <= 128, chosen on the device from the mean example length of the packed
-// batch (both are launched; the workgroups of the one that does not apply leave at once):
+// Two shapes for head_dim <= 128, chosen on the device from the lengths of the packed batch (both are
+// launched; the workgroups of the one that does not apply leave at once):
 //   large: 8 waves on a 128-key tile, one workgroup per CU: each streamed Q/dO block serves 128 keys
 //          (examples of thousands of tokens: 6 % faster than the small shape);
 //   small: 4 waves on a 64-key tile, two workgroups per CU that hide each other's prologue, epilogue
 //          and barriers (examples of 8..128 tokens: 14 % faster), at twice the block copies per
 //          matrix instruction.
-constexpr int kDkdvSmallBelow = 1024;  // mean example length (tokens) below which the small shape runs
+// The large shape runs where the mean example has kDkdvLongMean tokens or more, or where the average
+// schedule tile streams kDkdvLongBlocks blocks or more: a few long examples among many short ones do most of
+// the work, which the mean does not show.  Time of the large over the small shape, 7 head layouts (1 to 16
+// query heads per KV head, d = 64..128), 8192 to 32768 tokens: 5 blocks a tile 0.85...1.30 (mean 1.14), 6.5 to 8
+// blocks 0.93...1.17 (1.08), 10 to 11.5 blocks 0.91...1.12 (1.00), 13 blocks and more 0.86...1.03 (0.94).  Where
+// the small shape's tiles may be cut (below) no long chain is left for the large one to shorten, and 18 blocks
+// give 0.94...1.09: there the mean alone decides (by_mean).
+constexpr int kDkdvLongMean = 1024;
+constexpr int kDkdvLongBlocks = 12;
+__device__ __forceinline__ bool dkdv_small(const int32_t *__restrict__ meta, int N, int T, int tiles_per_row, bool by_mean) {
+  const long long n = meta[0], blocks = meta[2];  // examples; 64-query blocks over all key tiles (left by the scan)
+  return (long long)N < kDkdvLongMean * n &&
+         (by_mean || blocks < (long long)kDkdvLongBlocks * (N / T) * tiles_per_row);
+}
 template <int kDh, bool kSmall> struct DkdvShape {
   static_assert(!(kSmall && kDh > 128), "head_dim above 128 has one shape");
   static constexpr int kKg = (kDh > 128 || kSmall) ? 2 : 4;  // key groups (of 32 keys) per workgroup
@@ -454,34 +467,48 @@ template <int kDh, bool kSmall> struct DkdvShape {
 // dkdv_merge_kernel adds them, always in the order of the chunks (no atomics): 315 -> 90 us there, 370 ->
 // 303 us for one example of 4096 tokens with 4 query heads per KV head.
 //   host  : how many chunks a tile may have follows from the number of tiles and the workspace
-//           (plan_split below); with many tiles it is one, and no merge kernel is launched.
+//           (plan_split below); with many tiles it is one, and no merge kernel is launched.  In between, where
+//           grouped heads make chains longer than a compute unit's share of the work, only those are cut: 3735 and 4034
+//           tokens in three rows, 36/4 heads: step 1300 -> 1095 and 1602 -> 1310 us; 4248 tokens, 40/8: 415 -> 365.
 //   device: how many it gets follows from its own trips and the batch's total.
 struct DkdvSplit {
   float *partial;   // [pairs * max_chunks] slots of 2 * kKeys * kDh floats
   int max_chunks;   // per (tile, KV head) pair; 1: no tile is cut
+  int per_slot;     // chunks of average size per resident workgroup that the batch is cut into
 };
 constexpr int kMaxChunks = 32;
 // Trips of a chunk: at least kMinTrips (writing and adding a chunk's 64 KB costs about 5 trips), and so many
-// that the batch makes kChunksPerSlot chunks per resident workgroup, for balance.  Measured on six shapes
-// with 1..16 heads per KV head: 8 per slot 0...25 % faster than 4, 4 twice as fast as 1; at least 6, 8 or 12
-// trips within 5 % of each other where total work is small.
+// that the batch makes `per_slot` chunks per resident workgroup, for balance.  Measured on six shapes
+// with 1..16 heads per KV head and few tiles: 8 per slot 0...25 % faster than 4, 4 twice as fast as 1; at least 6, 8
+// or 12 trips within 5 % of each other where total work is small.  With more tiles (kMoreSplitBytes) only chains
+// longer than half of a slot's share of the work are worth a cut: 2 per slot.
 constexpr int kMinTrips = 8;
-constexpr int kChunksPerSlot = 8;
-// Chunks of a tile of n_it trips.  total_blocks: 64-query blocks over all schedule tiles (meta[2], left by
-// the boundary scan); tiles_x_heads: workgroup tiles per schedule tile x query heads; slots: workgroups the
-// chip holds.
-__device__ __forceinline__ int dkdv_chunks(int n_it, int total_blocks, int tiles_x_heads, int slots, int max_chunks) {
+constexpr int kChunksPerSlot = 8, kChunksPerSlotMany = 2;
+// Chunks of a tile of n_it trips, and the trips of all but the last.  total_blocks: 64-query blocks over all
+// schedule tiles (meta[2], left by the boundary scan); tiles_x_heads: workgroup tiles per schedule tile x query
+// heads; slots: workgroups the chip holds.  With many tiles the chunks are of one length, whole blocks of G heads:
+// the same chunk of neighbouring tiles of an example then streams the same blocks at about the same time, as uncut
+// tiles do.  With few they share a tile's trips evenly.
+struct DkdvChunks {
+  int n, even;
+  __device__ __forceinline__ int first(int c, int n_it) const { return even ? c * even : (int)((long long)n_it * c / n); }
+  __device__ __forceinline__ int end(int c, int n_it) const { return c + 1 == n ? n_it : first(c + 1, n_it); }
+};
+__device__ __forceinline__ DkdvChunks dkdv_chunks(int n_it, int total_blocks, int tiles_x_heads, int G, int slots, const DkdvSplit &split) {
   const float total = (float)total_blocks * (float)tiles_x_heads;
-  const int trips = max(kMinTrips, (int)(total / (float)(slots * kChunksPerSlot)) + 1);
-  return max(1, min(max_chunks, n_it / trips));
+  int trips = max(kMinTrips, (int)(total / (float)(slots * split.per_slot)) + 1);
+  if (split.per_slot == kChunksPerSlot) return {max(1, min(split.max_chunks, n_it / trips)), 0};
+  trips = max(trips, (n_it + split.max_chunks - 1) / split.max_chunks);
+  trips = (trips + G - 1) / G * G;
+  return {max(1, n_it / trips), trips};
 }
 
 __device__ __forceinline__ void lds_barrier() {  // LDS traffic of this wave done, then workgroup barrier
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// select: 0 = run; 1 = run only if the examples have kDkdvSmallBelow tokens or more on average; 2 =
-// only if they have fewer (meta[0] is the number of examples, left there by the boundary scan).
+// select: 0 = run; 1 = run only where the large shape is the better one, 2 = only where the small one is;
+// by_mean: see dkdv_small.
 // kCut: tiles may be cut (split.max_chunks > 1).  Without it the chunk arithmetic is not compiled in: it costs
 // scalar registers, in the head_dim 256 shape 29 spilled ones and 1.5 % of the time.
 template <class E, class EOut, int kDh, bool kSmall, bool kCut>
@@ -490,10 +517,10 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
                   const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
                   const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK,
                   void *__restrict__ dV, const int32_t *__restrict__ seg_end,
-                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, int select,
+                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, int select, bool by_mean,
                   DkdvSplit split, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2,
                   float scale) {
-  if (select != 0 && (((long long)N < (long long)kDkdvSmallBelow * meta[0]) != (select == 2))) return;  // workgroup-uniform
+  if (select != 0 && dkdv_small(meta, N, T, tiles_per_row, by_mean) != (select == 2)) return;  // workgroup-uniform
   constexpr int kKs = kDh / 16, kCb = kDh / 32;
   constexpr int kHf = kDh > 128 ? 2 : 1;  // 128-column sub-blocks per block
   constexpr int kBlkT = kBlk * kHf;       // elements of one tensor's streamed block
@@ -531,8 +558,17 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   // workgroup -> (tile, KV head) pair `pair` in launch order, chunk `chunk` of its trips
   int pair = blockIdx.x, chunk = 0;
   if constexpr (kCut) {
-    chunk = (pair / hkv) % split.max_chunks;
-    pair = pair / (hkv * split.max_chunks) * hkv + pair % hkv;
+    if (split.per_slot == kChunksPerSlot) {  // most chunks exist: the longest tiles' first (16 heads on one KV head: 4 % faster)
+      chunk = (pair / hkv) % split.max_chunks;
+      pair = pair / (hkv * split.max_chunks) * hkv + pair % hkv;
+    } else {
+      // Few do.  Last chunks first, so that the workgroups without a chunk come in one run: interleaved with the
+      // others they took turns on the shader engines, and with two or four chunks to a tile half of the engines
+      // got the work (12102 tokens, 36/4 heads: step 1860 us, 1310 this way).
+      const int n_pairs = gridDim.x / split.max_chunks;
+      chunk = split.max_chunks - 1 - pair / n_pairs;
+      pair = pair % n_pairs;
+    }
   }
   const int entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
   const int tile = order_tile(entry);
@@ -546,9 +582,9 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   const int t_last = min(t0 + kKeys, row_end) - 1;
   const int ib_lo = t0 / kBS;
   auto chunks_of = [&](int n_trips) {
-    return dkdv_chunks(n_trips, meta[2], kSubTiles * hq, 256 * Shape::kWgPerCu, split.max_chunks);
+    return dkdv_chunks(n_trips, meta[2], kSubTiles * hq, G, 256 * Shape::kWgPerCu, split);
   };
-  if (kCut && chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G)) return;  // workgroup-uniform
+  if (kCut && chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G).n) return;  // workgroup-uniform
 
   const size_t row_bytes = (size_t)hq * d * 2;
   const size_t base_off = (size_t)ib_lo * kBS * row_bytes;
@@ -627,9 +663,10 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   int n_it = (ib_hi - ib_lo + 1) * G;
   int n_chunks = 1, it0 = 0;
   if constexpr (kCut) {
-    n_chunks = chunks_of(n_it);
-    it0 = (int)((long long)n_it * chunk / n_chunks);
-    n_it = (int)((long long)n_it * (chunk + 1) / n_chunks) - it0;
+    const DkdvChunks c = chunks_of(n_it);
+    n_chunks = c.n;
+    it0 = c.first(chunk, n_it);
+    n_it = c.end(chunk, n_it) - it0;
   }
   const int se_min = uniform(se_min_v), se_max = uniform(se_max_v);
   const int se_j = row_ok ? se_j_v : 0;  // queries j_abs <= i < se_j see key j_abs
@@ -844,7 +881,7 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
                   DkdvSplit small, DkdvSplit large, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale) {
   constexpr int kCb = kDh / 32;
   __shared__ __attribute__((aligned(16))) float lds[4 * kStageFloatsPerWave];
-  const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && (long long)N < (long long)kDkdvSmallBelow * meta[0]));
+  const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && dkdv_small(meta, N, T, tiles_per_row, small.per_slot == kChunksPerSlot)));
   const DkdvSplit split = is_small ? small : large;
   const int key_groups = is_small || kDh > 128 ? 2 : 4;
   const int wg_per_cu = is_small ? 2 : 1;
@@ -862,7 +899,7 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
   if (t0 + kg * 32 >= row_end) return;
   const int t_last = min(t0 + keys, row_end) - 1;
   const int n_it = ((uniform(seg_end[t_last]) - 1) / kBS - t0 / kBS + 1) * (hq / hkv);
-  const int n_chunks = dkdv_chunks(n_it, meta[2], sub_tiles * hq, 256 * wg_per_cu, split.max_chunks);
+  const int n_chunks = dkdv_chunks(n_it, meta[2], sub_tiles * hq, hq / hkv, 256 * wg_per_cu, split).n;
   if (n_chunks == 1) return;  // stored by its only workgroup
   const int side = wave >> 1;
   const int nrows = min(32, row_end - (t0 + kg * 32));
@@ -902,13 +939,17 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
 
 }  // namespace
 
-// How the (tile, KV head) pairs of one workgroup shape may be cut (see DkdvSplit): as far as the workspace
-// reaches, if it holds at least two chunks of every pair, and not where no row is long enough for three
-// chunks (the merge launch, about 4 us, would buy nothing).
+// How the (tile, KV head) pairs of one workgroup shape may be cut (see DkdvSplit): finely if kDkdvSplitBytes hold
+// at least two chunks of every pair; else only the longest chains, if the workspace holds two; and not where no row
+// is long enough for three chunks (the merge launch, about 4 us, would buy nothing).
 static DkdvSplit plan_split(const Partials &partial, size_t slot_floats, long long n_pairs, long long max_trips) {
-  const long long slots = (long long)(partial.bytes / 4 / slot_floats);
-  const long long chunks = slots / n_pairs < kMaxChunks ? slots / n_pairs : kMaxChunks;
-  return {partial.p, chunks < 2 || max_trips < 3 * kMinTrips ? 1 : (int)chunks};
+  const auto chunks = [&](size_t bytes) {
+    const long long c = (long long)(bytes / 4 / slot_floats) / n_pairs;
+    return (int)(c < kMaxChunks ? c : kMaxChunks);
+  };
+  const int few = chunks(partial.bytes < kDkdvSplitBytes ? partial.bytes : kDkdvSplitBytes), many = chunks(partial.bytes);
+  if (max_trips < 3 * kMinTrips || many < 2) return {partial.p, 1, 0};
+  return few >= 2 ? DkdvSplit{partial.p, few, kChunksPerSlot} : DkdvSplit{partial.p, many, kChunksPerSlotMany};
 }
 
 template <class E, class EOut, int kDh>
@@ -926,17 +967,18 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     typedef DkdvShape<kDh, (kDh <= 128)> Small;  // head_dim above 128 has one shape
     const long long n_large = (long long)gkv * (Large::kSubTiles / kSub), n_small = (long long)gkv * (Small::kSubTiles / kSub);
     // Nothing about the lengths is known on the host: both shapes are launched and the device picks, unless
-    // the caller's hint names the shape or no example can reach the mean length that calls for the large one.
+    // the caller's hint names the shape or no example can be as long as calls for the large one (a row of fewer than
+    // kDkdvLongMean tokens has at most 10 blocks a tile).
     bool run_large = kDh > 128 || !(stages & VA_HINT_SHORT_EXAMPLES);
     bool run_small = kDh <= 128 && !(stages & VA_HINT_LONG_EXAMPLES);
-    if (run_small && T < kDkdvSmallBelow) run_large = false;
+    if (run_small && T < kDkdvLongMean) run_large = false;
     const int select_large = run_small ? 1 : 0, select_small = run_large ? 2 : 0;
     const long long max_trips = (long long)(T / kBS + 1) * (hq / hkv);
     const DkdvSplit sl = plan_split(partial, (size_t)2 * Large::kKeys * kDh, n_large, max_trips);
     const DkdvSplit ss = plan_split(partial, (size_t)2 * Small::kKeys * kDh, n_small, max_trips);
     auto launch = [&](auto *kernel, long long pairs, int threads, int select, const DkdvSplit &split) {
       kernel<<<(unsigned)(pairs * split.max_chunks), threads, 0, stream>>>(g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta,
-                                                                           select, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
+                                                                           select, ss.per_slot == kChunksPerSlot, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
     };
     if (run_large)
       launch(sl.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, false, true> : dkdv_mfma_kernel<E, EOut, kDh, false, false>, n_large,

@@ -13,8 +13,13 @@ constexpr int kScanThreads = 256;
 // Workspace of the backward beside D: fp32 sums of dK/dV tiles whose work is shared by several
 // workgroups; 1024 chunks of 64 keys at head_dim 128.
 constexpr size_t kDkdvSplitBytes = (size_t)64 << 20;
+// With up to kMoreSplitRows (token, KV head) rows that does not hold two chunks of every tile, but a few examples
+// of thousands of tokens, times the query heads of a KV head, can still be longer chains than a compute unit's share of
+// all work: there the workspace is larger.  Beyond, the share is larger than any chain that matters.
+constexpr size_t kMoreSplitBytes = (size_t)192 << 20;
+constexpr long long kMoreSplitRows = 98304;
 
-// The part of a caller's workspace behind D, at most kDkdvSplitBytes; may be empty (then no tile is shared).
+// The part of a caller's workspace behind D, at most kMoreSplitBytes; may be empty (then no tile is shared).
 struct Partials {
   float *p;
   size_t bytes;

@@ -46,3 +46,18 @@ def test_workspace_of_any_size(d, dtype, room):
     ref = run_oracle(w)
     f = lambda t: t.float().cpu().numpy().astype(np.float64)
     assert_close({"O": f(o), "LSE": f(lse), "dQ": f(dq), "dK": f(dk), "dV": f(dv)}, ref, dtype)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,dtype", [
+    ([[3900, 120]] * 2, 20, 4, 64, "bf16"),      # more tiles than are cut finely: only the long chains are, small shape's mean
+    ([[4100] + [40] * 20], 16, 8, 128, "bf16"),  # one long example among short ones: the large shape by its share of the work
+    ([[3001, 700, 33]], 28, 7, 96, "f16"),       # G = 4, ragged rows, chunks of whole blocks
+])
+def test_long_chains_among_many_tiles(lengths, hq, hkv, d, dtype):
+    w = wl.make_custom(lengths, hq, hkv, d, dtype, seed=73)
+    print(f"case: {hq}/{hkv} d={d} {dtype}", flush=True)
+    got = run_gpu(w, grad_dtype=torch.float32, nan_fill=True)
+    assert_close(got, run_oracle(w), dtype)
+    again = run_gpu(w, grad_dtype=torch.float32, nan_fill=True)
+    for key in ("dQ", "dK", "dV"):
+        assert np.array_equal(got[key], again[key]), key
