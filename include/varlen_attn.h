@@ -187,7 +187,9 @@ va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const
  * The backward above for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and errors as va_varlen_attn_bwd, without `workspace`: it lives in a device array inside the library
- * (VA_NOALLOC_SCRATCH_BYTES for D and 64 MiB for partial sums per GPU, held until the process ends).  Calls no hipMalloc / hipFree and no
+ * (VA_NOALLOC_SCRATCH_BYTES for D and 64 MiB for partial sums per GPU, held until the process ends).  Where
+ * va_attn_workspace_bytes asks for 192 MiB of partial sums the two may differ in the last bits of dK and dV (fewer
+ * key tiles are shared here).  Calls no hipMalloc / hipFree and no
  * allocating routine; the first call on a device looks the array's address up once (make that call
  * outside stream capture).
  *   Limit: rows * tokens_per_row * hq * 4 <= VA_NOALLOC_SCRATCH_BYTES, else VA_ERR_WORKSPACE and
