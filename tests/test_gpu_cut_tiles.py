@@ -48,10 +48,10 @@ def test_workspace_of_any_size(d, dtype, room):
     assert_close({"O": f(o), "LSE": f(lse), "dQ": f(dq), "dK": f(dk), "dV": f(dv)}, ref, dtype)
 
 
-@pytest.mark.parametrize("lengths,hq,hkv,d,dtype", [
-    ([[3900, 120]] * 2, 20, 4, 64, "bf16"),      # more tiles than are cut finely: only the long chains are, small shape's mean
-    ([[4100] + [40] * 20], 16, 8, 128, "bf16"),  # one long example among short ones: the large shape by its share of the work
-    ([[3001, 700, 33]], 28, 7, 96, "f16"),       # G = 4, ragged rows, chunks of whole blocks
+@pytest.mark.parametrize("lengths,hq,hkv,d,dtype", [   # too many tiles to cut all of them finely, G > 1
+    ([[1800] + [20] * 125] * 2, 20, 4, 128, "bf16"),
+    ([[40] * 55 + [2100]], 16, 8, 128, "f16"),
+    ([[33] * 70 + [1500] + [33] * 80], 21, 7, 96, "bf16"),
 ])
 def test_long_chains_among_many_tiles(lengths, hq, hkv, d, dtype):
     w = wl.make_custom(lengths, hq, hkv, d, dtype, seed=73)
