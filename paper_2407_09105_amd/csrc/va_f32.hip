@@ -18,7 +18,9 @@
 // and many workgroups: fp32 runs are checks of a few hundred to a few thousand tokens and few heads.  (Eight waves
 // per workgroup: the dQ kernel 28 instead of 22 us below, one workgroup per CU instead of two.)
 // The mask is "seg_start[i] <= j <= i" (forward, dQ) or "j <= i < seg_end[j]" (dK/dV) -- Table 1's correct
-// cross-attention for contiguous examples.
+// cross-attention for contiguous examples.  Tokens outside it leave no trace, whatever they hold: the matrix products
+// run on whole blocks with a masked factor of 0, and a wave that meets another factor in such a block that is not finite
+// (0 * Inf = NaN) forms its sums again, token by token (`redo`).
 // Measured, 1000 tokens, 8 query / 2 KV heads, d = 64, examples of up to 315 tokens, against one wave per output row
 // on the vector units: forward 257 -> 15 us, dQ (with D) 214 -> 22 us, dK/dV 484 -> 30 us.  Bound there by the
 // matrix instructions of the CUs that hold the longest examples' tiles; one example of 8000 tokens runs the
@@ -126,20 +128,57 @@ __device__ __forceinline__ void put(void *out, va_dtype dt, size_t i, float x) {
   else ((_Float16 *)out)[i] = (_Float16)x;
 }
 
-// Adds the waves' accumulators (each times its factor f[w] of this lane's row) in the order of the waves and
-// stores row `token` of a [N, H, d] tensor.  red: kWaves * (kDh / 4) * 64 floats of LDS.
-template <bool kVec, int kDh>
-__device__ __forceinline__ void merge_store(const f32x4 (&acc)[Cols<kDh>::kGroups][Cols<kDh>::kE], const float (&f)[kWaves],
-                                            float *red, void *out, va_dtype dt, size_t row_off, bool row_ok, int d) {
-  constexpr int kE = Cols<kDh>::kE, kRegs = kDh / 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4;
-  __syncthreads();  // the previous use of `red` is over
+// Adds 0 * x to z: z stays 0 as long as all of x is finite.
+template <int kDh> __device__ __forceinline__ void probe_finite(float &z, const float (&x)[Cols<kDh>::kGroups][Cols<kDh>::kE]) {
 #pragma unroll
   for (int g = 0; g < Cols<kDh>::kGroups; ++g)
 #pragma unroll
-    for (int e = 0; e < kE; ++e)
+    for (int e = 0; e < Cols<kDh>::kE; ++e) z = fmaf(x[g][e], 0.f, z);
+}
+__device__ __forceinline__ bool met_not_finite(float z) { return __any(!(z == 0.f)); }
+// For `redo`: the product of two head vectors, the same in the four lanes of a row, and sums = sums * old + w * row for
+// this lane's columns (sums: LDS in merge_store's order).  Loops stay loops: unrolled they cost the main loop registers.
+template <typename T> __device__ __forceinline__ float dot_token(const T *a, const T *b, int kq, int d) {
+  float x = 0.f;
+#pragma unroll 1
+  for (int c = kq; c < d; c += 4) x = fmaf((float)a[c], (float)b[c], x);
+  return quad_sum(x);
+}
+template <typename T, int kDh>
+__device__ __forceinline__ void add_token(float *sums, const T *row, int kq, int d, float old, float w) {
+  constexpr int kE = Cols<kDh>::kE;
+#pragma unroll 1
+  for (int r = 0; r < kDh / 4; ++r) {
+    const int c = r / (4 * kE) * (16 * kE) + kq * 4 * kE + r % (4 * kE);
+    if (c < d) sums[r * 64] = fmaf(w, (float)row[c], sums[r * 64] * old);
+  }
+}
+template <int kDh> __device__ __forceinline__ void clear_sums(float *sums) {
+#pragma unroll 1
+  for (int r = 0; r < kDh / 4; ++r) sums[r * 64] = 0.f;
+}
+
+// Adds the waves' accumulators (each times its factor f[w] of this lane's row) in the order of the waves and
+// stores row `token` of a [N, H, d] tensor.  red: kWaves * (kDh / 4) * 64 floats of LDS.  redone: this wave's sums
+// are not in acc, redo(sums) leaves them in its part of red.
+template <bool kVec, int kDh, class Redo>
+__device__ __forceinline__ void merge_store(const f32x4 (&acc)[Cols<kDh>::kGroups][Cols<kDh>::kE], const float (&f)[kWaves],
+                                            float *red, void *out, va_dtype dt, size_t row_off, bool row_ok, int d,
+                                            bool redone, Redo redo) {
+  constexpr int kE = Cols<kDh>::kE, kRegs = kDh / 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kq = lane >> 4;
+  __syncthreads();  // the previous use of `red` is over
+  float *const sums = red + wave * kRegs * 64 + lane;
+  if (redone) {
+    redo(sums);
+  } else {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) red[(wave * kRegs + (g * 4 + v) * kE + e) * 64 + lane] = acc[g][e][v];
+    for (int g = 0; g < Cols<kDh>::kGroups; ++g)
+#pragma unroll
+      for (int e = 0; e < kE; ++e)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sums[((g * 4 + v) * kE + e) * 64] = acc[g][e][v];
+  }
   __syncthreads();
   // register r of a lane is column (r / 4kE) * 16 kE + kq * 4 kE + r % 4kE; wave w takes every kWaves-th run of 4
   for (int r0 = wave * 4; r0 < kRegs; r0 += kWaves * 4) {
@@ -176,8 +215,9 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
   load_row<T, kVec, kDh>(Q + ((size_t)i_ld * hq + h) * d, kq, d, qf);
   f32x4 acc[Cols<kDh>::kGroups][Cols<kDh>::kE];
   clear<kDh>(acc);
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f, z = 0.f;
   for (int j0 = lo + kStep * wave; j0 <= hi; j0 += kStep * kWaves) {
+    const bool mixed = __any(j0 < ss_i || j0 + kStep - 1 > i_abs);  // some row of the tile does not see all of the block
     f32x4 s[2];
     float kf[2][kDh / 4], vc[2][4][Cols<kDh>::kGroups][Cols<kDh>::kE];
     auto value_cols = [&](int b, int v) {
@@ -224,7 +264,26 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
         const float p = __builtin_amdgcn_exp2f(fmaf(s[b][v], scale_log2, -base));
         l += p;
         if constexpr (!Ahead<kDh>::value) value_cols(b, v);
+        if (mixed) probe_finite<kDh>(z, vc[b][v]);
         add_outer<kDh>(acc, vc[b][v], p);
+      }
+  }
+  const bool redone = met_not_finite(z);
+  if (redone) {
+    float *const sums = red + wave * (kDh / 4) * 64 + lane;
+    clear_sums<kDh>(sums);
+    m = -INFINITY;
+    l = 0.f;
+    for (int j0 = lo + kStep * wave; j0 <= hi; j0 += kStep * kWaves)
+      for (int j = j0; j <= min(j0 + kStep - 1, hi); ++j) {
+        const float s = dot_token(Q + ((size_t)i_ld * hq + h) * d, Kh + (size_t)j * kv_row, kq, d);
+        if (j < ss_i || j > i_abs) continue;  // the same in the four lanes of a row
+        const float mx = fmaxf(m, s), base = mx == -INFINITY ? 0.f : mx * scale_log2;
+        const float alpha = mx == m ? 1.f : __builtin_amdgcn_exp2f(m * scale_log2 - base);
+        const float p = __builtin_amdgcn_exp2f(fmaf(s, scale_log2, -base));
+        m = mx;
+        l = l * alpha + (kq == 0 ? p : 0.f);
+        add_token<T, kDh>(sums, Vh + (size_t)j * kv_row, kq, d, alpha, p);
       }
   }
   l = quad_sum(l);
@@ -241,7 +300,7 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) f[w] /= l_all;
   if (wave == 0 && kq == 0 && i_abs <= hi) LSE[(size_t)h * N + i_abs] = m_all * scale + __logf(l_all);
-  merge_store<kVec, kDh>(acc, f, red, O, dt, ((size_t)i_ld * hq + h) * d, i_abs <= hi, d);
+  merge_store<kVec, kDh>(acc, f, red, O, dt, ((size_t)i_ld * hq + h) * d, i_abs <= hi, d, redone, [](float *) {});
 }
 
 // dQ; also forms D = dO . O of its rows and leaves it for the dK/dV kernel.
@@ -271,7 +330,9 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
   if (wave == 0 && kq == 0 && i_abs <= hi) delta[(size_t)h * N + i_abs] = dl;
   f32x4 acc[Cols<kDh>::kGroups][Cols<kDh>::kE];
   clear<kDh>(acc);
+  float z = 0.f;
   for (int j0 = lo + kStep * wave; j0 <= hi; j0 += kStep * kWaves) {
+    const bool mixed = __any(j0 < ss_i || j0 + kStep - 1 > i_abs);
     f32x4 s[2];
     float kf[2][kDh / 4], vf[2][kDh / 4], kc[2][4][Cols<kDh>::kGroups][Cols<kDh>::kE];
     auto rows = [&](int b) {
@@ -304,8 +365,8 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int j = j0 + 16 * b + 4 * kq + v;
-        const float p = (j < ss_i || j > i_abs) ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[b][v], scale_log2, -lse2));
-        s[b][v] = p * dp[v];
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[b][v], scale_log2, -lse2));
+        s[b][v] = (j < ss_i || j > i_abs) ? 0.f : p * dp[v];
       }
     }
 #pragma unroll
@@ -313,13 +374,24 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         if constexpr (!Ahead<kDh>::value) key_cols(b, v);
+        if (mixed) probe_finite<kDh>(z, kc[b][v]);
         add_outer<kDh>(acc, kc[b][v], s[b][v]);
       }
   }
   float f[kWaves];
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) f[w] = scale;
-  merge_store<kVec, kDh>(acc, f, red, dQ, gdt, q_off, i_abs <= hi, d);
+  auto redo = [&](float *sums) {
+    clear_sums<kDh>(sums);
+    for (int j0 = lo + kStep * wave; j0 <= hi; j0 += kStep * kWaves)
+      for (int j = j0; j <= min(j0 + kStep - 1, hi); ++j) {
+        const T *Kj = Kh + (size_t)j * kv_row;
+        const float s = dot_token(Q + q_off, Kj, kq, d), dp = dot_token(dO + q_off, Vh + (size_t)j * kv_row, kq, d) - dl;
+        if (j < ss_i || j > i_abs) continue;
+        add_token<T, kDh>(sums, Kj, kq, d, 1.f, __builtin_amdgcn_exp2f(fmaf(s, scale_log2, -lse2)) * dp);
+      }
+  };
+  merge_store<kVec, kDh>(acc, f, red, dQ, gdt, q_off, i_abs <= hi, d, met_not_finite(z), redo);
 }
 
 // dK, dV of 16 keys: the waves share out the (query head of the group, 32-query block) pairs.  With few tiles
@@ -346,10 +418,12 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
   clear<kDh>(acc_k);
   clear<kDh>(acc_v);
   const int nb = (end - t0 + kStep - 1) / kStep;
+  float z = 0.f;
   for (int it = part * kWaves + wave; it < nb * G; it += kWaves * parts) {
     const int h = g * G + it / nb, i0 = t0 + it % nb * kStep;
     const T *Qh = Q + (size_t)h * d, *Gh = dO + (size_t)h * d;
     const float *Lh = LSE + (size_t)h * N, *Dh = delta + (size_t)h * N;
+    const bool mixed = __any(i0 < j_abs || i0 + kStep > se_j);  // some key of the tile is not seen by all of the block
     f32x4 p[2], ds[2];
     float qf[2][kDh / 4], gf[2][kDh / 4], lse[2][4], dl[2][4];
     float qc[2][4][Cols<kDh>::kGroups][Cols<kDh>::kE], gc[2][4][Cols<kDh>::kGroups][Cols<kDh>::kE];
@@ -390,8 +464,9 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = i0 + 16 * b + 4 * kq + v;
-        p[b][v] = (i < j_abs || i >= se_j) ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[v], scale_log2, lse[b][v] * -1.4426950408889634f));
-        ds[b][v] = p[b][v] * dp[v];
+        const bool masked = i < j_abs || i >= se_j;
+        p[b][v] = masked ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[v], scale_log2, lse[b][v] * -1.4426950408889634f));
+        ds[b][v] = masked ? 0.f : p[b][v] * dp[v];
       }
     }
 #pragma unroll
@@ -399,6 +474,10 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         if constexpr (!Ahead<kDh>::value) query_cols(b, v);
+        if (mixed) {
+          probe_finite<kDh>(z, gc[b][v]);
+          probe_finite<kDh>(z, qc[b][v]);
+        }
         add_outer<kDh>(acc_v, gc[b][v], p[b][v]);
         add_outer<kDh>(acc_k, qc[b][v], ds[b][v]);
       }
@@ -412,10 +491,25 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
   float f[kWaves];
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) f[w] = 1.f;
-  merge_store<kVec, kDh>(acc_v, f, red, dV, gdt, kv_off, j_abs <= t_last, d);
+  const bool redone = met_not_finite(z);
+  auto redo = [&](float *sums, bool keys) {
+    clear_sums<kDh>(sums);
+    for (int it = part * kWaves + wave; it < nb * G; it += kWaves * parts) {
+      const int h = g * G + it / nb, i0 = t0 + it % nb * kStep;
+      for (int i = i0; i < min(i0 + kStep, end); ++i) {
+        const T *Qi = Q + (size_t)i * q_row + (size_t)h * d, *Gi = dO + (size_t)i * q_row + (size_t)h * d;
+        const float s = dot_token(K + kv_off, Qi, kq, d);
+        const float dp = dot_token(V + kv_off, Gi, kq, d) - delta[(size_t)h * N + i];
+        if (i < j_abs || i >= se_j) continue;
+        const float p = __builtin_amdgcn_exp2f(fmaf(s, scale_log2, LSE[(size_t)h * N + i] * -1.4426950408889634f));
+        add_token<T, kDh>(sums, keys ? Qi : Gi, kq, d, 1.f, keys ? p * dp : p);
+      }
+    }
+  };
+  merge_store<kVec, kDh>(acc_v, f, red, dV, gdt, kv_off, j_abs <= t_last, d, redone, [&](float *sums) { redo(sums, false); });
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) f[w] = scale;
-  merge_store<kVec, kDh>(acc_k, f, red, dK, gdt, kv_off, j_abs <= t_last, d);
+  merge_store<kVec, kDh>(acc_k, f, red, dK, gdt, kv_off, j_abs <= t_last, d, redone, [&](float *sums) { redo(sums, true); });
 }
 
 __global__ void __launch_bounds__(256)

@@ -43,3 +43,38 @@ def test_unaligned_fp32_tensors():
     cu = oracle.pack(w.position_ids)["cu_seqlens"]
     for got, ref in zip((o, dq, dk, dv), (oracle.fwd(w.q, w.k, w.v, cu)[0], *oracle.bwd(w.do, w.q, w.k, w.v, cu))):
         assert rel_l2(got.cpu().numpy(), ref) <= 1e-5   # fp32 sums of at most 70 products: 70 x 2^-24 = 4e-6, with room
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("lengths,t,hq,hkv,d,dtype", [
+    ([[9, 20, 11]], 15, 4, 2, 64, "f32"),          # three examples in the blocks of one tile
+    ([[70, 45, 30], [145]], 95, 2, 2, 16, "f32"),
+    ([[37, 150, 9]], 100, 8, 1, 128, "f32"),       # columns loaded where they are used; dK/dV in parts
+    ([[37, 50, 9]], 60, 2, 1, 200, "f32"),
+    ([[21, 40, 30]], 44, 4, 1, 20, "bf16"),        # element-wise loads
+])
+def test_not_finite_tokens_stay_in_their_example(lengths, t, hq, hkv, d, dtype, value):
+    # one token of an example is not finite in one tensor: what does not depend on it is as if it were
+    w = wl.make_custom(lengths, hq, hkv, d, dtype, seed=93)
+    ref = run_oracle(w)
+    cu = ref["seg"]["cu_seqlens"]
+    a, b = int(cu[np.searchsorted(cu, t, "right") - 1]), int(cu[np.searchsorted(cu, t, "right")])
+    own, later, earlier, whole, none = range(t, t + 1), range(t, b), range(a, t + 1), range(a, b), range(0)
+    reach = {"q": {"O": own, "LSE": own, "dQ": own, "dK": earlier, "dV": earlier},
+             "k": {"O": later, "LSE": later, "dQ": later, "dK": whole, "dV": whole},
+             "v": {"O": later, "LSE": none, "dQ": later, "dK": whole, "dV": none},
+             "do": {"O": none, "LSE": none, "dQ": own, "dK": earlier, "dV": earlier}}
+    for tensor, rows in reach.items():
+        bad = wl.make_custom(lengths, hq, hkv, d, dtype, seed=93)
+        getattr(bad, tensor)[t] = value
+        got = run_gpu(bad, grad_dtype=torch.float32, nan_fill=True)
+        for key, r in rows.items():
+            view = (lambda x: x[:, list(r)]) if key == "LSE" else (lambda x: x[list(r)])
+            if np.isnan(value):
+                assert np.isnan(view(got[key])).all(), (tensor, key)   # and what depends on it shows it
+            if key == "LSE":
+                got[key][:, list(r)] = ref[key][:, list(r)]
+            else:
+                got[key][list(r)] = ref[key][list(r)]
+        print(f"case: {tensor}[{t}] = {value}", flush=True)
+        assert_close(got, ref, dtype)
