@@ -16,6 +16,7 @@
 //                      dV^T += dO^T P, dK^T += Q^T dS; the dV and the dK halves run on different waves.
 // In both, the streamed index lies on the accumulator's register axis and feeds the last
 // contraction as a B operand straight from registers (see va_mfma_common.h).
+#include <algorithm>
 #include <type_traits>
 
 #include "va_internal.h"
@@ -470,13 +471,17 @@ template <int kDh, bool kSmall> struct DkdvShape {
 //           (plan_split below); with many tiles it is one, and no merge kernel is launched.  In between, where
 //           grouped heads make chains longer than a compute unit's share of the work, only those are cut: 3735 and 4034
 //           tokens in three rows, 36/4 heads: step 1300 -> 1095 and 1602 -> 1310 us; 4248 tokens, 40/8: 415 -> 365.
+//           (Where every example fills its row they gain little or lose: three rows of 4034 tokens, 36/4 heads, 1.07 of the
+//           dK/dV time uncut, 8192 and 12000 tokens 1.01.)
 //   device: how many it gets follows from its own trips and the batch's total.
 struct DkdvSplit {
   float *partial;   // [pairs * max_chunks] slots of 2 * kKeys * kDh floats
   int max_chunks;   // per (tile, KV head) pair; 1: no tile is cut
   int per_slot;     // chunks of average size per resident workgroup that the batch is cut into
 };
-constexpr int kMaxChunks = 32;
+// Most chunks of a tile; the workgroups of chunks that it does not get are launched for nothing.  With many tiles 3
+// are too few (three rows of 3735 tokens, 36/4 heads: 383 instead of 347 us), more than 4 no faster in 13 batches.
+constexpr int kMaxChunks = 32, kMaxChunksMany = 4;
 // Trips of a chunk: at least kMinTrips (writing and adding a chunk's 64 KB costs about 5 trips), and so many
 // that the batch makes `per_slot` chunks per resident workgroup, for balance.  Measured on six shapes
 // with 1..16 heads per KV head and few tiles: 8 per slot 0...25 % faster than 4, 4 twice as fast as 1; at least 6, 8
@@ -484,21 +489,36 @@ constexpr int kMaxChunks = 32;
 // longer than half of a slot's share of the work are worth a cut: 2 per slot.
 constexpr int kMinTrips = 8;
 constexpr int kChunksPerSlot = 8, kChunksPerSlotMany = 2;
-// Chunks of a tile of n_it trips, and the trips of all but the last.  total_blocks: 64-query blocks over all
-// schedule tiles (meta[2], left by the boundary scan); tiles_x_heads: workgroup tiles per schedule tile x query
-// heads; slots: workgroups the chip holds.  With many tiles the chunks are of one length, whole blocks of G heads:
-// the same chunk of neighbouring tiles of an example then streams the same blocks at about the same time, as uncut
-// tiles do.  With few they share a tile's trips evenly.
+// What the batch allows, the same in every workgroup.  A batch whose longest chain is no longer than a slot's share of the
+// work is not cut: the chunks' sums are 64 KB each, written and read (8192 tokens in examples of 8 to 128, 36/4
+// heads: dK/dV cut 94 us, not cut 78; 2048 tokens, 36/4, the share below the chain: 42, not cut 58).
+struct DkdvPlan {
+  int piece;  // least trips of a chunk
+  int most;   // no tile gets more chunks
+};
+__device__ __forceinline__ DkdvPlan dkdv_plan(const int32_t *__restrict__ meta, int keys, int slots, int N, int T, int hq, int G,
+                                              const DkdvSplit &split) {
+  // 64-query blocks over all schedule tiles (meta[2]) x workgroup tiles in one x heads, over the workgroups the chip holds
+  const float share = (float)meta[2] * (float)(VA_TILE / keys * hq) * (1.f / slots);
+  const int piece = max(kMinTrips, (int)(share * (split.per_slot == kChunksPerSlot ? 1.f / kChunksPerSlot : 1.f / kChunksPerSlotMany)) + 1);
+  // The longest chain that the longest example (meta[1]) allows: a tile's blocks reach from at most keys - 1 tokens before
+  // an example to the end of it, and begin up to `off` tokens behind a multiple of the block.
+  const int off = N == T ? 0 : kBS - min(kBS, T & -T);
+  const int chain = ((meta[1] + keys - 2 + off) / kBS + 1) * G;
+  return {piece, (float)chain < share + (float)kMinTrips ? 1 : max(1, min(split.max_chunks, chain / piece))};
+}
+// Chunks of a tile of n_it trips, and the trips of all but the last.  With many tiles the chunks are of one length, whole
+// blocks of G heads: the same chunk of neighbouring tiles of an example then streams the same blocks at about the
+// same time, as uncut tiles do.  With few they share a tile's trips evenly (even = 0).
 struct DkdvChunks {
   int n, even;
   __device__ __forceinline__ int first(int c, int n_it) const { return even ? c * even : (int)((long long)n_it * c / n); }
   __device__ __forceinline__ int end(int c, int n_it) const { return c + 1 == n ? n_it : first(c + 1, n_it); }
 };
-__device__ __forceinline__ DkdvChunks dkdv_chunks(int n_it, int total_blocks, int tiles_x_heads, int G, int slots, const DkdvSplit &split) {
-  const float total = (float)total_blocks * (float)tiles_x_heads;
-  int trips = max(kMinTrips, (int)(total / (float)(slots * split.per_slot)) + 1);
-  if (split.per_slot == kChunksPerSlot) return {max(1, min(split.max_chunks, n_it / trips)), 0};
-  trips = max(trips, (n_it + split.max_chunks - 1) / split.max_chunks);
+__device__ __forceinline__ DkdvChunks dkdv_chunks(int n_it, const DkdvPlan &plan, int G, const DkdvSplit &split) {
+  if (plan.most == 1) return {1, 0};
+  if (split.per_slot == kChunksPerSlot) return {max(1, min(split.max_chunks, n_it / plan.piece)), 0};
+  int trips = max(plan.piece, (n_it + split.max_chunks - 1) / split.max_chunks);
   trips = (trips + G - 1) / G * G;
   return {max(1, n_it / trips), trips};
 }
@@ -555,18 +575,32 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   const int kg = wave % kKg;
   const bool k_side = wave >= kKg;
   const int l32 = lane & 31, half = lane >> 5;
-  // workgroup -> (tile, KV head) pair `pair` in launch order, chunk `chunk` of its trips
+  // workgroup -> (tile, KV head) pair `pair` in launch order, chunk `chunk` of its trips.  max_chunks workgroups are
+  // launched to a pair; those beyond what the batch allows are numbered last and leave at once.  Numbered among the
+  // others they are expensive: workgroups go to the 8 XCDs and the 4 shader engines of each in turn, so that the working
+  // ones can all fall to one engine, and are started in order, so that an idle one waits for a place in front of
+  // working ones (dK/dV of 2048 tokens in examples of 8 to 60, 32/8 heads: 52 us; numbered last 27; never cut 25).
   int pair = blockIdx.x, chunk = 0;
+  DkdvPlan plan = {0, 1};
   if constexpr (kCut) {
-    if (split.per_slot == kChunksPerSlot) {  // most chunks exist: the longest tiles' first (16 heads on one KV head: 4 % faster)
-      chunk = (pair / hkv) % split.max_chunks;
-      pair = pair / (hkv * split.max_chunks) * hkv + pair % hkv;
-    } else {
-      // Few do.  Last chunks first, so that the workgroups without a chunk come in one run: interleaved with the
-      // others they took turns on the shader engines, and with two or four chunks to a tile half of the engines
-      // got the work (12102 tokens, 36/4 heads: step 1860 us, 1310 this way).
-      const int n_pairs = gridDim.x / split.max_chunks;
-      chunk = split.max_chunks - 1 - pair / n_pairs;
+    plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, hq, hq / hkv, split);
+    const int most = plan.most, n_pairs = gridDim.x / split.max_chunks;
+    if (pair >= n_pairs * most) return;
+    if (most > 1 && split.per_slot == kChunksPerSlot) {
+      // The tiles in order of their length, a tile's chunks together (16 heads on one KV head, 6141 tokens: 79 us; the
+      // first chunks of all tiles, then the second ones, ...: 107 us).  Where `most` is even, the first chunks, which every
+      // tile has, would keep to every other engine or XCD: they move on by the digit sum of the tile's number (4096 tokens
+      // in examples of 8 to 128, 40/8 heads: 85 -> 57 us; moved on where it is odd, the 1500 tokens of four examples: 48 -> 58).
+      const int q = pair / hkv, u = q / most;
+      int turn = q - u * most;
+      if (most % 2 == 0)
+        for (int x = u; x > 0; x /= most) turn += x;
+      chunk = turn % most;
+      pair += (u - q) * hkv;
+    } else if (most > 1) {
+      // Most tiles have one chunk: last chunks first, so that the longest tiles start early (three rows of 3735 tokens,
+      // 36/4 heads: 347 us, numbered by tile 440).
+      chunk = most - 1 - pair / n_pairs;
       pair = pair % n_pairs;
     }
   }
@@ -582,7 +616,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   const int t_last = min(t0 + kKeys, row_end) - 1;
   const int ib_lo = t0 / kBS;
   auto chunks_of = [&](int n_trips) {
-    return dkdv_chunks(n_trips, meta[2], kSubTiles * hq, G, 256 * Shape::kWgPerCu, split);
+    return dkdv_chunks(n_trips, plan, G, split);
   };
   if (kCut && chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G).n) return;  // workgroup-uniform
 
@@ -884,8 +918,10 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
   const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && dkdv_small(meta, N, T, tiles_per_row, small.per_slot == kChunksPerSlot)));
   const DkdvSplit split = is_small ? small : large;
   const int key_groups = is_small || kDh > 128 ? 2 : 4;
-  const int wg_per_cu = is_small ? 2 : 1;
   const int sub_tiles = VA_TILE / 32 / key_groups;
+  if (split.max_chunks == 1) return;
+  const DkdvPlan plan = dkdv_plan(meta, 32 * key_groups, is_small ? 512 : 256, N, T, hq, hq / hkv, split);
+  if (plan.most == 1) return;  // before any tile is looked up
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
   const int kgi = blockIdx.x % (VA_TILE / 32), head_slot = blockIdx.x / (VA_TILE / 32) % hkv;
   const int rank = blockIdx.x / (VA_TILE / 32 * hkv);
@@ -899,7 +935,7 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
   if (t0 + kg * 32 >= row_end) return;
   const int t_last = min(t0 + keys, row_end) - 1;
   const int n_it = ((uniform(seg_end[t_last]) - 1) / kBS - t0 / kBS + 1) * (hq / hkv);
-  const int n_chunks = dkdv_chunks(n_it, meta[2], sub_tiles * hq, hq / hkv, 256 * wg_per_cu, split).n;
+  const int n_chunks = dkdv_chunks(n_it, plan, hq / hkv, split).n;
   if (n_chunks == 1) return;  // stored by its only workgroup
   const int side = wave >> 1;
   const int nrows = min(32, row_end - (t0 + kg * 32));
@@ -941,15 +977,17 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
 
 // How the (tile, KV head) pairs of one workgroup shape may be cut (see DkdvSplit): finely if kDkdvSplitBytes hold
 // at least two chunks of every pair; else only the longest chains, if the workspace holds two; and not where no row
-// is long enough for three chunks (the merge launch, about 4 us, would buy nothing).
-static DkdvSplit plan_split(const Partials &partial, size_t slot_floats, long long n_pairs, long long max_trips) {
+// is long enough (longest_chain: trips of one that a single example fills).  Cut over uncut there, one such row: 32 trips, 128,
+// 256 and 512 pairs 0.68, 0.91 and 1.07 (head_dim 64: 1.25); 24 trips, 384 pairs 0.96; 48, 384 0.81; 64, 512 0.88.
+// Where a row could hold a long example, but none is, the idle workgroups and the merge launch cost 1 to 5 us.
+static DkdvSplit plan_split(const Partials &partial, size_t slot_floats, long long n_pairs, long long longest_chain, int slots) {
   const auto chunks = [&](size_t bytes) {
-    const long long c = (long long)(bytes / 4 / slot_floats) / n_pairs;
-    return (int)(c < kMaxChunks ? c : kMaxChunks);
+    const long long c = (long long)(bytes / 4 / slot_floats) / n_pairs, trips = longest_chain / kMinTrips;
+    return (int)std::min({c, trips, (long long)kMaxChunks});
   };
   const int few = chunks(partial.bytes < kDkdvSplitBytes ? partial.bytes : kDkdvSplitBytes), many = chunks(partial.bytes);
-  if (max_trips < 3 * kMinTrips || many < 2) return {partial.p, 1, 0};
-  return few >= 2 ? DkdvSplit{partial.p, few, kChunksPerSlot} : DkdvSplit{partial.p, many, kChunksPerSlotMany};
+  if (longest_chain < 3 * kMinTrips || longest_chain * slots < 6 * kMinTrips * std::min(n_pairs, (long long)slots) || many < 2) return {partial.p, 1, 0};
+  return few >= 2 ? DkdvSplit{partial.p, few, kChunksPerSlot} : DkdvSplit{partial.p, std::min(many, kMaxChunksMany), kChunksPerSlotMany};
 }
 
 template <class E, class EOut, int kDh>
@@ -973,9 +1011,9 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     bool run_small = kDh <= 128 && !(stages & VA_HINT_LONG_EXAMPLES);
     if (run_small && T < kDkdvLongMean) run_large = false;
     const int select_large = run_small ? 1 : 0, select_small = run_large ? 2 : 0;
-    const long long max_trips = (long long)(T / kBS + 1) * (hq / hkv);
-    const DkdvSplit sl = plan_split(partial, (size_t)2 * Large::kKeys * kDh, n_large, max_trips);
-    const DkdvSplit ss = plan_split(partial, (size_t)2 * Small::kKeys * kDh, n_small, max_trips);
+    const long long longest_chain = (long long)((T - 1 + (N == T || T % kBS == 0 ? 0 : kBS - 1)) / kBS + 1) * (hq / hkv);
+    const DkdvSplit sl = plan_split(partial, (size_t)2 * Large::kKeys * kDh, n_large, longest_chain, 256 * Large::kWgPerCu);
+    const DkdvSplit ss = plan_split(partial, (size_t)2 * Small::kKeys * kDh, n_small, longest_chain, 256 * Small::kWgPerCu);
     auto launch = [&](auto *kernel, long long pairs, int threads, int select, const DkdvSplit &split) {
       kernel<<<(unsigned)(pairs * split.max_chunks), threads, 0, stream>>>(g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta,
                                                                            select, ss.per_slot == kChunksPerSlot, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);

@@ -21,6 +21,10 @@ pytestmark = pytest.mark.gpu
     ([[700, 31]], 6, 1, 256, "f16", 0),                    # two 128-column halves
     ([[1700]], 1, 1, 80, "bf16", 0),                       # no grouped heads: blocks in ascending order
     ([[30] * 40], 16, 1, 64, "bf16", 0),                   # cut or not by a short tile's trips
+    ([[500]], 4, 1, 128, "bf16", 0),                       # four chunks at most: first chunks move on from tile to tile
+    ([[100] * 20], 6, 1, 64, "f16", 0),                    # two chunks at most
+    ([[55] * 40], 8, 2, 64, "bf16", 0),                    # a row that could be cut, examples that are not
+    ([[900, 50], [475, 475]], 16, 2, 96, "bf16", 0),       # rows off the 64-token grid, off the schedule tile
 ])
 def test_cut_tiles(lengths, hq, hkv, d, dtype, hint):
     w = wl.make_custom(lengths, hq, hkv, d, dtype, seed=71)
