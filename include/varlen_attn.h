@@ -171,10 +171,11 @@ va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *
  * large entries of P and dS through the matrix units in two 16-bit parts.
  *   grad_dt   : element type of dQ, dK, dV: VA_F32, or the 16-bit type of the inputs (VA_BF16 also
  *               with fp32 inputs); other pairs: VA_ERR_UNSUPPORTED.
- *   workspace : va_attn_workspace_bytes(..., 1) bytes: D, [Hq, N] float, and 64 or (Hq > Hkv and
- *               24576 < N * Hkv <= 98304) 192 MiB for the partial sums of key tiles whose work is shared by
- *               several workgroups.  At least D has to fit (its size
- *               rounded up to 256 bytes); with less room behind it fewer tiles, or none, are shared.
+ *   workspace : va_attn_workspace_bytes(..., 1) bytes: D, [Hq, N] float, and up to 64 MiB for the partial
+ *               sums of key tiles whose work is shared by several workgroups (none where no tile can be).
+ *               At least D has to fit (its size rounded up to 256 bytes); with less room behind it fewer
+ *               tiles, or none, are shared, and dK and dV may differ in the last bits.  More than asked for
+ *               is not used.
  */
 va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const void *V,
                              const void *O, const float *LSE, void *dQ, void *dK, void *dV,
@@ -187,10 +188,8 @@ va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const
  * The backward above for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and errors as va_varlen_attn_bwd, without `workspace`: it lives in a device array inside the library
- * (VA_NOALLOC_SCRATCH_BYTES for D and 64 MiB for partial sums per GPU, held until the process ends).  Where
- * va_attn_workspace_bytes asks for 192 MiB of partial sums the two may differ in the last bits of dK and dV (fewer
- * key tiles are shared here).  Calls no hipMalloc / hipFree and no
- * allocating routine; the first call on a device looks the array's address up once (make that call
+ * (VA_NOALLOC_SCRATCH_BYTES for D and 64 MiB for partial sums per GPU, held until the process ends).
+ * Calls no hipMalloc / hipFree and no allocating routine; the first call on a device looks the array's address up once (make that call
  * outside stream capture).
  *   Limit: rows * tokens_per_row * hq * 4 <= VA_NOALLOC_SCRATCH_BYTES, else VA_ERR_WORKSPACE and
  *   nothing is enqueued.

@@ -323,7 +323,7 @@ NOALLOC_SCRATCH_BYTES = 32 << 20
 
 def varlen_attn_bwd_noalloc(do, q, k, v, o, lse, seg: Segments, dq, dk, dv, softmax_scale: float = 0.0):
     """The backward through the entry point that allocates nothing: the caller passes every output,
-    D lives in the library's own device array (N * Hq * 4 <= NOALLOC_SCRATCH_BYTES).  No tensor is
+    the workspace is the library's own device array (for D, N * Hq * 4 <= NOALLOC_SCRATCH_BYTES).  No tensor is
     created here either."""
     _need_cuda(do, q, k, v, o, lse, dq, dk, dv)
     N, hq, hkv, d = _shapes(q, k, v, seg)

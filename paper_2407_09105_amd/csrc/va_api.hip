@@ -1,4 +1,5 @@
 // C ABI of the library: argument validation and dispatch.  See include/varlen_attn.h.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -11,6 +12,10 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // D = rowsum(dO * O), [Hq, N] float: the first part of the backward's workspace
 inline size_t d_bytes(int32_t n_tokens, int32_t hq) { return align_up((size_t)n_tokens * (size_t)hq * sizeof(float)); }
+// the second: sums of shared dK/dV tiles, of whichever kernels the element type selects
+inline size_t partial_bytes(int32_t n_tokens, int32_t hq, int32_t hkv, int32_t d) {
+  return std::max(va::mfma_partial_bytes(n_tokens, hq, hkv, d), va::f32_partial_bytes(n_tokens, hq, hkv, d));
+}
 
 struct PlanLayout {
   size_t cu, seg_id, seg_start, seg_end, meta, q_order, kv_order, scratch, total;
@@ -137,9 +142,7 @@ va_status va_rope_apply(const void *x, void *y, va_dtype dt, const void *positio
 size_t va_attn_workspace_bytes(int32_t n_tokens, int32_t hq, int32_t hkv, int32_t d, int is_bwd) {
   if (n_tokens <= 0 || hq <= 0 || hkv <= 0 || d <= 0) return 0;
   if (!is_bwd) return 0;
-  const long long rows = (long long)n_tokens * hkv;
-  const bool more = hkv < hq && d <= 256 && rows > va::kMoreSplitRows / 4 && rows <= va::kMoreSplitRows;
-  return d_bytes(n_tokens, hq) + (more ? va::kMoreSplitBytes : va::kDkdvSplitBytes);
+  return d_bytes(n_tokens, hq) + partial_bytes(n_tokens, hq, hkv, d);
 }
 
 va_status va_varlen_attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
@@ -193,8 +196,8 @@ va_status va_varlen_attn_bwd_stages(const void *dO, const void *Q, const void *K
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d);
   float *delta = (float *)workspace;
   const uintptr_t behind = align_up((uintptr_t)workspace + d_bytes(N, hq)), end = (uintptr_t)workspace + workspace_bytes;
-  va::Partials partial = {(float *)behind, end > behind ? end - behind : 0};
-  if (partial.bytes > va::kMoreSplitBytes) partial.bytes = va::kMoreSplitBytes;
+  const size_t room = end > behind ? end - behind : 0;
+  auto partials = [&](size_t use) { return va::Partials{(float *)behind, std::min(room, use)}; };
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   const unsigned hints = stages & (VA_HINT_LONG_EXAMPLES | VA_HINT_SHORT_EXAMPLES);
@@ -206,11 +209,11 @@ va_status va_varlen_attn_bwd_stages(const void *dO, const void *Q, const void *K
   if (e != hipSuccess) return VA_ERR_HIP;
   if (mfma_stages)
     e = va::launch_mfma_bwd(dO, Q, K, V, O, LSE, delta, dQ, dK, dV, grad_dt, *seg, rows, tokens_per_row, hq, hkv,
-                            d, dt, scale, partial, st, mfma_stages | hints);
+                            d, dt, scale, partials(va::mfma_partial_bytes(N, hq, hkv, d)), st, mfma_stages | hints);
   if (e != hipSuccess) return VA_ERR_HIP;
   if (plain_stages)
     e = va::launch_f32_bwd(dO, Q, K, V, O, LSE, delta, dQ, dK, dV, grad_dt, *seg, rows, tokens_per_row, hq, hkv, d, dt,
-                           scale, partial, st, plain_stages);
+                           scale, partials(va::f32_partial_bytes(N, hq, hkv, d)), st, plain_stages);
   return e == hipSuccess ? VA_OK : VA_ERR_HIP;
 }
 
@@ -265,7 +268,7 @@ va_status va_varlen_attn_bwd_noalloc(const void *dO, const void *Q, const void *
   // every byte of D that the dK/dV kernel reads is written by the dQ (or D) kernel of the same call,
   // so nothing of the previous call's contents has to be cleared
   return va_varlen_attn_bwd(dO, Q, K, V, O, LSE, dQ, dK, dV, grad_dt, seg, rows, tokens_per_row, hq, hkv, d, dt,
-                            softmax_scale, ws, sizeof(scratch), stream);
+                            softmax_scale, ws, va_attn_workspace_bytes(rows * tokens_per_row, hq, hkv, d, 1), stream);
 }
 
 const char *va_status_string(va_status s) {

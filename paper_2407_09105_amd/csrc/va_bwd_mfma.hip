@@ -475,18 +475,19 @@ template <int kDh, bool kSmall> struct DkdvShape {
 //           dK/dV time uncut, 8192 and 12000 tokens 1.01.)
 //   device: how many it gets follows from its own trips and the batch's total.
 struct DkdvSplit {
-  float *partial;   // [pairs * max_chunks] slots of 2 * kKeys * kDh floats
+  float *partial;   // slots of 2 * kKeys * kDh floats
   int max_chunks;   // per (tile, KV head) pair; 1: no tile is cut
-  int per_slot;     // chunks of average size per resident workgroup that the batch is cut into
+  bool fine;        // few tiles: every pair has max_chunks slots; otherwise only chunks of cut tiles have one
+  int room;         // the slots there are for one KV head (read where only cut tiles have them)
 };
 // Most chunks of a tile; the workgroups of chunks that it does not get are launched for nothing.  With many tiles 3
 // are too few (three rows of 3735 tokens, 36/4 heads: 383 instead of 347 us), more than 4 no faster in 13 batches.
 constexpr int kMaxChunks = 32, kMaxChunksMany = 4;
 // Trips of a chunk: at least kMinTrips (writing and adding a chunk's 64 KB costs about 5 trips), and so many
-// that the batch makes `per_slot` chunks per resident workgroup, for balance.  Measured on six shapes
+// that the batch makes kChunksPerSlot chunks per resident workgroup, for balance.  Measured on six shapes
 // with 1..16 heads per KV head and few tiles: 8 per slot 0...25 % faster than 4, 4 twice as fast as 1; at least 6, 8
-// or 12 trips within 5 % of each other where total work is small.  With more tiles (kMoreSplitBytes) only chains
-// longer than half of a slot's share of the work are worth a cut: 2 per slot.
+// or 12 trips within 5 % of each other where total work is small.  With more tiles only chains longer than a slot's
+// share of the work are worth a cut: 2 per slot.
 constexpr int kMinTrips = 8;
 constexpr int kChunksPerSlot = 8, kChunksPerSlotMany = 2;
 // What the batch allows, the same in every workgroup.  A batch whose longest chain is no longer than a slot's share of the
@@ -500,7 +501,7 @@ __device__ __forceinline__ DkdvPlan dkdv_plan(const int32_t *__restrict__ meta, 
                                               const DkdvSplit &split) {
   // 64-query blocks over all schedule tiles (meta[2]) x workgroup tiles in one x heads, over the workgroups the chip holds
   const float share = (float)meta[2] * (float)(VA_TILE / keys * hq) * (1.f / slots);
-  const int piece = max(kMinTrips, (int)(share * (split.per_slot == kChunksPerSlot ? 1.f / kChunksPerSlot : 1.f / kChunksPerSlotMany)) + 1);
+  const int piece = max(kMinTrips, (int)(share * (split.fine ? 1.f / kChunksPerSlot : 1.f / kChunksPerSlotMany)) + 1);
   // The longest chain that the longest example (meta[1]) allows: a tile's blocks reach from at most keys - 1 tokens before
   // an example to the end of it, and begin up to `off` tokens behind a multiple of the block.
   const int off = N == T ? 0 : kBS - min(kBS, T & -T);
@@ -517,10 +518,37 @@ struct DkdvChunks {
 };
 __device__ __forceinline__ DkdvChunks dkdv_chunks(int n_it, const DkdvPlan &plan, int G, const DkdvSplit &split) {
   if (plan.most == 1) return {1, 0};
-  if (split.per_slot == kChunksPerSlot) return {max(1, min(split.max_chunks, n_it / plan.piece)), 0};
+  if (split.fine) return {max(1, min(split.max_chunks, n_it / plan.piece)), 0};
   int trips = max(plan.piece, (n_it + split.max_chunks - 1) / split.max_chunks);
   trips = (trips + G - 1) / G * G;
   return {max(1, n_it / trips), trips};
+}
+
+// With many tiles: the first slot of tile `u` (in launch order, workgroup tiles) in every KV head's run of slots, from the
+// chunks of the cut tiles before it.  The pieces are at least half of a slot's share of the work, so that all chunks
+// of cut tiles are at most kChunksPerSlotMany per resident workgroup: 64 MiB whatever the number of tiles.  All threads of
+// the workgroup call it; `lds`: an int per wave.  About 3 us, in workgroups of cut tiles only.
+template <int kThreads>
+__device__ __forceinline__ int dkdv_first_slot(int u, int keys, const int32_t *__restrict__ seg_end, const int32_t *__restrict__ kv_tile_order,
+                                               int T, int tiles_per_row, int G, const DkdvPlan &plan, const DkdvSplit &split, int *lds) {
+  const int sub_tiles = VA_TILE / keys;
+  int sum = 0;
+  for (int x = threadIdx.x; x < u; x += kThreads) {
+    const int tile = order_tile(kv_tile_order[x / sub_tiles]), r = tile / tiles_per_row, row_end = (r + 1) * T;
+    const int t0 = r * T + tile % tiles_per_row * VA_TILE + x % sub_tiles * keys;
+    if (t0 >= row_end) continue;
+    const int n = dkdv_chunks(((seg_end[min(t0 + keys, row_end) - 1] - 1) / kBS - t0 / kBS + 1) * G, plan, G, split).n;
+    if (n > 1) sum += n;
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  sum = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) sum += lds[w];
+  __syncthreads();
+  return uniform(sum);
 }
 
 __device__ __forceinline__ void lds_barrier() {  // LDS traffic of this wave done, then workgroup barrier
@@ -586,7 +614,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
     plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, hq, hq / hkv, split);
     const int most = plan.most, n_pairs = gridDim.x / split.max_chunks;
     if (pair >= n_pairs * most) return;
-    if (most > 1 && split.per_slot == kChunksPerSlot) {
+    if (most > 1 && split.fine) {
       // The tiles in order of their length, a tile's chunks together (16 heads on one KV head, 6141 tokens: 79 us; the
       // first chunks of all tiles, then the second ones, ...: 107 us).  Where `most` is even, the first chunks, which every
       // tile has, would keep to every other engine or XCD: they move on by the digit sum of the tile's number (4096 tokens
@@ -615,10 +643,23 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   if (t0 >= row_end) return;  // workgroup-uniform: the schedule tile is ragged
   const int t_last = min(t0 + kKeys, row_end) - 1;
   const int ib_lo = t0 / kBS;
+  // The tile's chunks; with many tiles also its slots, and one chunk where there are too few left.
+  int slot0 = pair * split.max_chunks, slot_step = 1;
   auto chunks_of = [&](int n_trips) {
-    return dkdv_chunks(n_trips, plan, G, split);
+    DkdvChunks c = dkdv_chunks(n_trips, plan, G, split);
+    if (c.n > 1 && c.n > chunk && !split.fine) {
+      const int before = dkdv_first_slot<Shape::kThreads>(pair / hkv, kKeys, seg_end, kv_tile_order, T, tiles_per_row, G, plan, split, (int *)exch);
+      slot0 = before * hkv + pair % hkv;
+      slot_step = hkv;
+      if (before + c.n > split.room) c = {1, 0};
+    }
+    return c;
   };
-  if (kCut && chunk > 0 && chunk >= chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G).n) return;  // workgroup-uniform
+  DkdvChunks c = {1, 0};
+  if (kCut && chunk > 0) {
+    c = chunks_of((((uniform(seg_end[t_last]) - 1) / kBS) - ib_lo + 1) * G);
+    if (chunk >= c.n) return;  // workgroup-uniform
+  }
 
   const size_t row_bytes = (size_t)hq * d * 2;
   const size_t base_off = (size_t)ib_lo * kBS * row_bytes;
@@ -697,7 +738,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   int n_it = (ib_hi - ib_lo + 1) * G;
   int n_chunks = 1, it0 = 0;
   if constexpr (kCut) {
-    const DkdvChunks c = chunks_of(n_it);
+    if (chunk == 0) c = chunks_of(n_it);
     n_chunks = c.n;
     it0 = c.first(chunk, n_it);
     n_it = c.end(chunk, n_it) - it0;
@@ -882,7 +923,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
     if (act_b) k_finish(xb, tyb, 1);  // the last sub-block's dK
   }
   if (kCut && n_chunks > 1) {  // leave the accumulators to the merge kernel: [wave][4-register group][lane] x 16 B
-    float *out = split.partial + ((size_t)pair * split.max_chunks + chunk) * (2 * kKeys * kDh) +
+    float *out = split.partial + (size_t)(slot0 + chunk * slot_step) * (2 * kKeys * kDh) +
                  ((kg * 2 + (k_side ? 1 : 0)) * kCb * 4 * 64 + lane) * 4;
 #pragma unroll
     for (int cb = 0; cb < kCb; ++cb)
@@ -915,7 +956,7 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
                   DkdvSplit small, DkdvSplit large, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale) {
   constexpr int kCb = kDh / 32;
   __shared__ __attribute__((aligned(16))) float lds[4 * kStageFloatsPerWave];
-  const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && dkdv_small(meta, N, T, tiles_per_row, small.per_slot == kChunksPerSlot)));
+  const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && dkdv_small(meta, N, T, tiles_per_row, small.max_chunks > 1 && small.fine)));
   const DkdvSplit split = is_small ? small : large;
   const int key_groups = is_small || kDh > 128 ? 2 : 4;
   const int sub_tiles = VA_TILE / 32 / key_groups;
@@ -937,10 +978,17 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
   const int n_it = ((uniform(seg_end[t_last]) - 1) / kBS - t0 / kBS + 1) * (hq / hkv);
   const int n_chunks = dkdv_chunks(n_it, plan, hq / hkv, split).n;
   if (n_chunks == 1) return;  // stored by its only workgroup
+  int slot0 = pair * split.max_chunks, slot_step = 1;
+  if (!split.fine) {
+    const int before = dkdv_first_slot<256>(pair / hkv, keys, seg_end, kv_tile_order, T, tiles_per_row, hq / hkv, plan, split, (int *)lds);
+    if (before + n_chunks > split.room) return;  // likewise
+    slot0 = before * hkv + head_slot;
+    slot_step = hkv;
+  }
   const int side = wave >> 1;
   const int nrows = min(32, row_end - (t0 + kg * 32));
-  const size_t slot = (size_t)2 * keys * kDh;
-  const float *src = split.partial + (size_t)pair * split.max_chunks * slot + ((kg * 2 + side) * kCb * 1024 + lane * 4);
+  const size_t slot = (size_t)2 * keys * kDh * slot_step;
+  const float *src = split.partial + (size_t)slot0 * (2 * keys * kDh) + ((kg * 2 + side) * kCb * 1024 + lane * 4);
 #pragma unroll 1
   for (int p = wave & 1; p < (kCb + 1) / 2; p += 2) {
     f32x16 acc[2];
@@ -976,18 +1024,56 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
 }  // namespace
 
 // How the (tile, KV head) pairs of one workgroup shape may be cut (see DkdvSplit): finely if kDkdvSplitBytes hold
-// at least two chunks of every pair; else only the longest chains, if the workspace holds two; and not where no row
-// is long enough (longest_chain: trips of one that a single example fills).  Cut over uncut there, one such row: 32 trips, 128,
-// 256 and 512 pairs 0.68, 0.91 and 1.07 (head_dim 64: 1.25); 24 trips, 384 pairs 0.96; 48, 384 0.81; 64, 512 0.88.
+// at least two chunks of every pair; else, with grouped heads and up to kMorePairs pairs per resident workgroup, only the
+// longest chains (that is as far as cuts were measured); and not where no row is long enough (longest_chain: trips of one
+// that a single example fills).  Cut over uncut there, one such row: 32 trips, 128, 256 and 512 pairs 0.68, 0.91
+// and 1.07 (head_dim 64: 1.25); 24 trips, 384 pairs 0.96; 48, 384 0.81; 64, 512 0.88.
 // Where a row could hold a long example, but none is, the idle workgroups and the merge launch cost 1 to 5 us.
-static DkdvSplit plan_split(const Partials &partial, size_t slot_floats, long long n_pairs, long long longest_chain, int slots) {
-  const auto chunks = [&](size_t bytes) {
-    const long long c = (long long)(bytes / 4 / slot_floats) / n_pairs, trips = longest_chain / kMinTrips;
-    return (int)std::min({c, trips, (long long)kMaxChunks});
-  };
-  const int few = chunks(partial.bytes < kDkdvSplitBytes ? partial.bytes : kDkdvSplitBytes), many = chunks(partial.bytes);
-  if (longest_chain < 3 * kMinTrips || longest_chain * slots < 6 * kMinTrips * std::min(n_pairs, (long long)slots) || many < 2) return {partial.p, 1, 0};
-  return few >= 2 ? DkdvSplit{partial.p, few, kChunksPerSlot} : DkdvSplit{partial.p, std::min(many, kMaxChunksMany), kChunksPerSlotMany};
+// slots: workgroups of the shape that the chip holds.
+constexpr int kMorePairs = 3;
+static DkdvSplit plan_split(const Partials &partial, size_t slot_bytes, long long n_pairs, int hq, int hkv, long long longest_chain, int slots) {
+  const DkdvSplit none = {partial.p, 1, true, 0};
+  if (longest_chain < 3 * kMinTrips || longest_chain * slots < 6 * kMinTrips * std::min(n_pairs, (long long)slots)) return none;
+  const long long trips = longest_chain / kMinTrips;
+  if (n_pairs * 2 <= (long long)(kDkdvSplitBytes / slot_bytes)) {
+    const int n = (int)std::min({(long long)(partial.bytes / slot_bytes) / n_pairs, trips, (long long)kMaxChunks});
+    return n >= 2 ? DkdvSplit{partial.p, n, true, 0} : none;
+  }
+  const int room = (int)(partial.bytes / slot_bytes) / hkv;
+  if (hq == hkv || n_pairs > kMorePairs * slots || room < 2) return none;
+  return {partial.p, (int)std::min({2 * kMorePairs * slots / n_pairs, trips, (long long)kMaxChunksMany}), false, room};
+}
+
+// The plans of both shapes for rows of T tokens.
+template <int kDh> struct DkdvLaunch {
+  typedef DkdvShape<kDh, false> Large;
+  typedef DkdvShape<kDh, (kDh <= 128)> Small;  // head_dim above 128 has one shape
+  long long n_large, n_small;                  // (workgroup tile, KV head) pairs
+  DkdvSplit large, small;
+  DkdvLaunch(const Partials &partial, int N, int T, int hq, int hkv) {
+    const long long tiles = (T + VA_TILE - 1ll) / VA_TILE * (N / T) * hkv;
+    n_large = tiles * Large::kSubTiles;
+    n_small = tiles * Small::kSubTiles;
+    const int off = N == T || T % kBS == 0 ? 0 : kBS - 1;  // a row may begin that far behind a multiple of the block
+    const long long longest_chain = ((T - 1ll + off) / kBS + 1) * (hq / hkv);
+    large = plan_split(partial, (size_t)2 * Large::kKeys * kDh * 4, n_large, hq, hkv, longest_chain, 256 * Large::kWgPerCu);
+    small = plan_split(partial, (size_t)2 * Small::kKeys * kDh * 4, n_small, hq, hkv, longest_chain, 256 * Small::kWgPerCu);
+  }
+};
+
+template <class F> static auto by_head_dim(int d, F f) {
+  if (d <= 64) return f(std::integral_constant<int, 64>());
+  if (d <= 96) return f(std::integral_constant<int, 96>());
+  if (d <= 128) return f(std::integral_constant<int, 128>());
+  return f(std::integral_constant<int, 256>());
+}
+
+size_t mfma_partial_bytes(int N, int hq, int hkv, int d) {
+  if (d % 8 != 0 || d > 256 || hq % hkv != 0) return 0;
+  return by_head_dim(d, [&](auto dh) {  // in one row tiles are fewest and chains longest
+    const DkdvLaunch<decltype(dh)::value> l({nullptr, kDkdvSplitBytes}, N, N, hq, hkv);
+    return l.large.max_chunks > 1 || l.small.max_chunks > 1 ? kDkdvSplitBytes : (size_t)0;
+  });
 }
 
 template <class E, class EOut, int kDh>
@@ -1001,9 +1087,10 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
                                                          seg.q_tile_order, N, T, tiles_per_row, hq, hkv, d,
                                                          scale_log2, scale);
   if (stages & VA_STAGE_DKDV) {
-    typedef DkdvShape<kDh, false> Large;
-    typedef DkdvShape<kDh, (kDh <= 128)> Small;  // head_dim above 128 has one shape
-    const long long n_large = (long long)gkv * (Large::kSubTiles / kSub), n_small = (long long)gkv * (Small::kSubTiles / kSub);
+    typedef typename DkdvLaunch<kDh>::Large Large;
+    typedef typename DkdvLaunch<kDh>::Small Small;
+    const DkdvLaunch<kDh> l(partial, N, T, hq, hkv);
+    const DkdvSplit &sl = l.large, &ss = l.small;
     // Nothing about the lengths is known on the host: both shapes are launched and the device picks, unless
     // the caller's hint names the shape or no example can be as long as calls for the large one (a row of fewer than
     // kDkdvLongMean tokens has at most 10 blocks a tile).
@@ -1011,19 +1098,16 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     bool run_small = kDh <= 128 && !(stages & VA_HINT_LONG_EXAMPLES);
     if (run_small && T < kDkdvLongMean) run_large = false;
     const int select_large = run_small ? 1 : 0, select_small = run_large ? 2 : 0;
-    const long long longest_chain = (long long)((T - 1 + (N == T || T % kBS == 0 ? 0 : kBS - 1)) / kBS + 1) * (hq / hkv);
-    const DkdvSplit sl = plan_split(partial, (size_t)2 * Large::kKeys * kDh, n_large, longest_chain, 256 * Large::kWgPerCu);
-    const DkdvSplit ss = plan_split(partial, (size_t)2 * Small::kKeys * kDh, n_small, longest_chain, 256 * Small::kWgPerCu);
     auto launch = [&](auto *kernel, long long pairs, int threads, int select, const DkdvSplit &split) {
       kernel<<<(unsigned)(pairs * split.max_chunks), threads, 0, stream>>>(g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta,
-                                                                           select, ss.per_slot == kChunksPerSlot, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
+                                                                           select, ss.max_chunks > 1 && ss.fine, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
     };
     if (run_large)
-      launch(sl.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, false, true> : dkdv_mfma_kernel<E, EOut, kDh, false, false>, n_large,
+      launch(sl.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, false, true> : dkdv_mfma_kernel<E, EOut, kDh, false, false>, l.n_large,
              Large::kThreads, select_large, sl);
     if constexpr (kDh <= 128) {
       if (run_small)
-        launch(ss.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, true, true> : dkdv_mfma_kernel<E, EOut, kDh, true, false>, n_small,
+        launch(ss.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, true, true> : dkdv_mfma_kernel<E, EOut, kDh, true, false>, l.n_small,
                Small::kThreads, select_small, ss);
     }
     if ((run_large && sl.max_chunks > 1) || (run_small && ss.max_chunks > 1))

@@ -588,6 +588,12 @@ template <typename T, bool kVec, int kDh> hipError_t run_fwd(const Args &a) {
       a.scale * 1.4426950408889634f, a.scale);
   return hipGetLastError();
 }
+// Parts that the work of a dK/dV tile is shared out to: enough workgroups for two per CU, but at least two rounds of the
+// waves in the longest chain that a row of T tokens allows.
+long long dkdv_parts(int N, int T, int hq, int hkv) {
+  const long long tiles = (N + kRows - 1ll) / kRows, rounds = (T + kStep - 1ll) / kStep * (hq / hkv) / kWaves;
+  return std::max(1ll, std::min(512 / (tiles * hkv), rounds / 2));
+}
 template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
   const long long gq = (long long)ceil_div(a.N, kRows) * a.hq, gkv = (long long)ceil_div(a.N, kRows) * a.hkv;
   if (gq > 0x7fffffffll) return hipErrorInvalidValue;
@@ -597,11 +603,8 @@ template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, (const T *)a.O, a.LSE, a.delta, a.out,
         a.seg->seg_start, a.N, a.hq, a.hkv, a.d, a.out_dt, scale_log2, a.scale);
   if (a.stages & VA_STAGE_DKDV) {
-    // Parts per tile: enough workgroups for two per CU, but at least two rounds of the waves in the longest chain
-    // a row allows, and as far as the workspace reaches.
     const size_t n = (size_t)a.N * a.hkv * a.d;
-    const long long rounds = (long long)ceil_div(a.T, kStep) * (a.hq / a.hkv) / kWaves;
-    const long long parts = std::max(1ll, std::min({512 / gkv, rounds / 2, (long long)(a.partial.bytes / 8 / n)}));
+    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv), (long long)(a.partial.bytes / 8 / n)));
     f32_dkdv_kernel<T, kVec, kDh><<<dim3((unsigned)gkv, (unsigned)parts), 64 * kWaves, 0, a.stream>>>(
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
         a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, scale_log2, a.scale);
@@ -631,6 +634,11 @@ template <bool kFwd> hipError_t by_type(va_dtype dt, const Args &a) {
 }
 
 }  // namespace
+
+size_t f32_partial_bytes(int N, int hq, int hkv, int d) {
+  const long long parts = dkdv_parts(N, N, hq, hkv);  // one row: the longest chains
+  return parts > 1 ? (size_t)parts * 8 * N * hkv * d : 0;
+}
 
 hipError_t launch_f32_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
                           const va_segments &seg, int N, int hq, int hkv, int d, va_dtype dt,

@@ -10,16 +10,15 @@ constexpr int kTile = VA_TILE;       // tokens per schedule tile
 constexpr int kScanChunk = 2048;     // tokens per workgroup in the boundary scan
 constexpr int kScanThreads = 256;
 
-// Workspace of the backward beside D: fp32 sums of dK/dV tiles whose work is shared by several
+// Most workspace of the backward beside D: fp32 sums of dK/dV tiles whose work is shared by several
 // workgroups; 1024 chunks of 64 keys at head_dim 128.
 constexpr size_t kDkdvSplitBytes = (size_t)64 << 20;
-// With up to kMoreSplitRows (token, KV head) rows that does not hold two chunks of every tile, but a few examples
-// of thousands of tokens, times the query heads of a KV head, can still be longer chains than a compute unit's share of
-// all work: there the workspace is larger.  Beyond, the share is larger than any chain that matters.
-constexpr size_t kMoreSplitBytes = (size_t)192 << 20;
-constexpr long long kMoreSplitRows = 98304;
+// How much of it a backward of this shape can use, however its tokens are cut into rows: 0 where no tile can be shared.
+// A caller's room beyond that stays unused, so that the bits of dK and dV do not depend on it.
+size_t mfma_partial_bytes(int N, int hq, int hkv, int d);  // 16-bit kernels
+size_t f32_partial_bytes(int N, int hq, int hkv, int d);   // fp32-arithmetic kernels
 
-// The part of a caller's workspace behind D, at most kMoreSplitBytes; may be empty (then no tile is shared).
+// The part of a caller's workspace behind D that the call may use; may be empty (then no tile is shared).
 struct Partials {
   float *p;
   size_t bytes;

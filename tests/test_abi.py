@@ -154,7 +154,12 @@ def test_attn_validation(L):
     assert fwd(*big) == 1                                  # (rejected later, for the missing segments)
     assert bwd(*withb(18, None)) == 1                      # workspace required
     assert bwd(*withb(19, 16)) == 4                        # workspace too small
-    assert L.va_attn_workspace_bytes(16, 2, 2, 16, 1) >= 16 * 2 * 4
+    assert L.va_attn_workspace_bytes(16, 2, 2, 16, 1) == 256   # D alone, in units of 256 bytes: no key tile can be shared
+    behind = lambda n, hq, hkv, d: L.va_attn_workspace_bytes(n, hq, hkv, d, 1) - n * hq * 4
+    assert behind(8192, 32, 32, 128) == behind(16384, 32, 8, 128) == behind(16384, 16, 4, 256) == 0   # nor here
+    assert behind(8192, 32, 8, 128) == behind(6144, 16, 1, 64) == 64 << 20
+    assert 0 < behind(1024, 8, 2, 63) < 16 << 20               # fp32 arithmetic
+    assert L.va_attn_workspace_bytes(2 ** 31 - 2, 1, 1, 8, 1) == (2 ** 31 - 2) * 4 + 8
     assert L.va_attn_workspace_bytes(16, 2, 2, 16, 0) == 0
     assert L.va_attn_workspace_bytes(0, 2, 2, 16, 1) == 0
 

@@ -36,11 +36,15 @@ def test_cut_tiles(lengths, hq, hkv, d, dtype, hint):
         assert np.array_equal(got[key], again[key]), key   # the chunks are added in a fixed order
 
 
-@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "f32")])
+@pytest.mark.parametrize("lengths,hq,hkv,d,dtype", [
+    ([[640]], 4, 1, 128, "bf16"),
+    ([[640]], 4, 1, 64, "f32"),
+    ([[33] * 70 + [1500] + [33] * 80], 21, 7, 96, "bf16"),   # only chunks of long key tiles have a place
+])
 @pytest.mark.parametrize("room", [0, 1, 3 << 20])   # bytes behind D: none, too little for a chunk, for some chunks only
-def test_workspace_of_any_size(d, dtype, room):
-    w = wl.make_custom([[640]], 4, 1, d, dtype, seed=72)
-    N, hq, hkv = 640, 4, 1
+def test_workspace_of_any_size(lengths, hq, hkv, d, dtype, room):
+    w = wl.make_custom(lengths, hq, hkv, d, dtype, seed=72)
+    N = w.q.shape[0]
     q, k, v, do = (to_dev(a, dtype) for a in (w.q, w.k, w.v, w.do))
     seg = binding.pack_to_cu_seqlens(torch.from_numpy(w.position_ids).to(DEV))
     o, lse = binding.varlen_attn_fwd(q, k, v, seg)

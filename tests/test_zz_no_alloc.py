@@ -1,4 +1,4 @@
-"""The backward entry point that allocates nothing (its D workspace is a device array inside the
+"""The backward entry point that allocates nothing (its workspace is a device array inside the
 library) against the ordinary backward, through the C ABI: two calls in a row, the second on a
 smaller input, so that what the first call left in the shared array is still there."""
 import pytest
@@ -39,6 +39,22 @@ def test_noalloc_backward_matches_backward_twice_in_a_row():
     _both([[100, 219]], 2, 2, 64, "bf16", 62, torch.bfloat16)
     # plain kernels (fp32 inputs): D comes from the stand-alone D kernel
     _both([[40, 7, 81]], 4, 2, 40, "f32", 63, torch.float32)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,dtype", [
+    ([[3072]], 12, 12, 128, "bf16"),                    # more room would hold two chunks of every key tile
+    ([[1800] + [20] * 125] * 2, 20, 4, 128, "bf16"),    # only long key tiles are shared by several workgroups
+    ([[700, 31]], 6, 1, 256, "f16"),                    # all are
+    ([[700, 41]], 8, 1, 64, "f32"),
+])
+def test_results_do_not_depend_on_where_the_workspace_lies(lengths, hq, hkv, d, dtype):
+    _both(lengths, hq, hkv, d, dtype, 64, torch.float32)
+    q, k, v, do, o, lse, seg = _inputs(lengths, hq, hkv, d, dtype, 64)
+    asked = binding.bwd_workspace(q, k)
+    more = torch.empty(asked.numel() + (192 << 18), device=DEV)   # nor on room that was not asked for
+    ref = binding.varlen_attn_bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float32, workspace=asked)
+    for a, b in zip(binding.varlen_attn_bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float32, workspace=more), ref):
+        assert torch.equal(a, b)
 
 
 def test_noalloc_backward_rejects_sizes_beyond_its_array():
