@@ -492,7 +492,11 @@ constexpr int kMinTrips = 8;
 constexpr int kChunksPerSlot = 8, kChunksPerSlotMany = 2;
 // What the batch allows, the same in every workgroup.  A batch whose longest chain is no longer than a slot's share of the
 // work is not cut: the chunks' sums are 64 KB each, written and read (8192 tokens in examples of 8 to 128, 36/4
-// heads: dK/dV cut 94 us, not cut 78; 2048 tokens, 36/4, the share below the chain: 42, not cut 58).
+// heads: dK/dV cut 94 us, not cut 78; 2048 tokens, 36/4, the share below the chain: 42, not cut 58).  With many tiles
+// and long examples alone the bar is 1.5 shares: the tiles' chains then take all lengths up to the longest, and those just
+// too short for two chunks, which stay whole, begin after the chunks of the others.  Cut over uncut, examples that fill
+// their rows, by the longest chain in shares: 1.9 0.87, 1.8 0.93, 1.6 0.98, 1.45 0.98 and 1.12 (one row and three),
+// 1.35 0.98 and 1.08, 1.15 1.02; examples of about 1500 tokens, 6000 in all, 1.09.
 struct DkdvPlan {
   int piece;  // least trips of a chunk
   int most;   // no tile gets more chunks
@@ -506,7 +510,9 @@ __device__ __forceinline__ DkdvPlan dkdv_plan(const int32_t *__restrict__ meta, 
   // an example to the end of it, and begin up to `off` tokens behind a multiple of the block.
   const int off = N == T ? 0 : kBS - min(kBS, T & -T);
   const int chain = ((meta[1] + keys - 2 + off) / kBS + 1) * G;
-  return {piece, (float)chain < share + (float)kMinTrips ? 1 : max(1, min(split.max_chunks, chain / piece))};
+  const bool all_long = !split.fine && (long long)N >= (long long)kDkdvLongMean * meta[0];
+  const float bar = all_long ? 1.5f * share : share + (float)kMinTrips;
+  return {piece, (float)chain < bar ? 1 : max(1, min(split.max_chunks, chain / piece))};
 }
 // Chunks of a tile of n_it trips, and the trips of all but the last.  With many tiles the chunks are of one length, whole
 // blocks of G heads: the same chunk of neighbouring tiles of an example then streams the same blocks at about the
