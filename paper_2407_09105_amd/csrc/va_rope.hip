@@ -4,6 +4,8 @@
 // turns by the angle pos * base^(-2c/d); `inverse` turns by the negative angle (the transpose,
 // used for gradients).  HBM-bound: every element is read and written once; the sines and
 // cosines of a (token, pair) are computed once and shared by all heads.
+#include <algorithm>
+
 #include "va_internal.h"
 #include "va_mfma_common.h"
 
@@ -34,53 +36,69 @@ template <typename T> struct Chunk<T, 1> {
 constexpr int kThreads = 256;
 constexpr int kItems = 4;
 constexpr int kMaxPairs = 2048;  // (token, pair) entries of the table: 16 KB
-constexpr int kMinGroups = 512;  // fewer tokens per workgroup rather than fewer than two workgroups per CU
+constexpr long long kMinGroups = 512;  // fewer tokens per workgroup rather than fewer than two workgroups per CU,
+constexpr int kLeastItems = 64;        // but a wave's worth of items (1000 tokens, one head of 64: 3.1 us, down to one token 4.6)
 
-template <typename T, int kVec, typename IdT>
+__device__ __forceinline__ void cos_sin(double pos, int c, double neg2_log2base_over_d, int inverse, float &cs, float &sn) {
+  // angle in fp64, reduced to [-pi, pi] before the fp32 sine / cosine: exact to ~1e-7 at any position
+  double w = pos * exp2((double)c * neg2_log2base_over_d);
+  w -= 6.283185307179586476925 * rint(w * 0.15915494309189533577);
+  sincosf((float)w, &sn, &cs);
+  if (inverse) sn = -sn;
+}
+
+// kDirect: one head, whose table would share nothing; every thread forms the cosines and sines of its only item itself.
+template <typename T, int kVec, typename IdT, bool kDirect>
 __global__ void __launch_bounds__(kThreads)
 rope_kernel(const T *x, T *y, const IdT *__restrict__ pos, long long N, int tokens,  // y may be x (in place)
-            size_t token_elems, int H, int d, double neg2_log2base_over_d, int inverse) {
+            int H, int heads, int d, double neg2_log2base_over_d, int inverse) {
   typedef Chunk<T, kVec> C;
   typedef typename C::type chunk_t;
-  __shared__ __attribute__((aligned(16))) float cs[kMaxPairs], sn[kMaxPairs];
+  constexpr int kFly = kDirect ? 1 : kItems, kTable = kDirect ? 1 : kMaxPairs;
+  __shared__ __attribute__((aligned(16))) float cs[kTable], sn[kTable];
   const int hd = d / 2, cpt = hd / kVec;
   const long long t0 = (long long)blockIdx.x * tokens;
   const int nt = (int)min((long long)tokens, N - t0);
-  const int n_items = nt * H * cpt;
-  for (int e = threadIdx.x; e < nt * hd; e += kThreads) {
-    const int t = e / hd, c = e - t * hd;
-    // angle in fp64, reduced to [-pi, pi] before the fp32 sine / cosine: exact to ~1e-7 at any position
-    double w = (double)pos[t0 + t] * exp2((double)c * neg2_log2base_over_d);
-    w -= 6.283185307179586476925 * rint(w * 0.15915494309189533577);
-    float s1, c1;
-    sincosf((float)w, &s1, &c1);
-    cs[e] = c1;
-    sn[e] = inverse ? -s1 : s1;
+  const int h0 = blockIdx.y * heads, nh = min(heads, H - h0);
+  const size_t token_elems = (size_t)H * d;
+  const int n_items = nt * nh * cpt;
+  if constexpr (!kDirect) {
+    for (int e = threadIdx.x; e < nt * hd; e += kThreads) {
+      const int t = e / hd;
+      cos_sin((double)pos[t0 + t], e - t * hd, neg2_log2base_over_d, inverse, cs[e], sn[e]);
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  const T *const xb = x + (size_t)t0 * token_elems;
-  T *const yb = y + (size_t)t0 * token_elems;
-  for (int i0 = threadIdx.x; i0 < n_items; i0 += kItems * kThreads) {
-    chunk_t a[kItems], b[kItems];
-    size_t off[kItems];
-    int e0[kItems];
+  const T *const xb = x + (size_t)t0 * token_elems + (size_t)h0 * d;
+  T *const yb = y + (size_t)t0 * token_elems + (size_t)h0 * d;
+  for (int i0 = threadIdx.x; i0 < n_items; i0 += kFly * kThreads) {
+    chunk_t a[kFly], b[kFly];
+    size_t off[kFly];
+    int e0[kFly];
 #pragma unroll
-    for (int u = 0; u < kItems; ++u) {  // the last items of a workgroup are loaded more than once, stored once
+    for (int u = 0; u < kFly; ++u) {  // the last items of a workgroup are loaded more than once, stored once
       const int i = min(i0 + u * kThreads, n_items - 1);
       const int row = i / cpt, c0 = (i - row * cpt) * kVec;
-      const int t = row / H;
-      off[u] = (size_t)t * token_elems + (size_t)(row - t * H) * d + c0;
+      const int t = kDirect ? row : row / nh;
+      off[u] = (size_t)t * token_elems + (size_t)(row - t * nh) * d + c0;
       e0[u] = t * hd + c0;
       a[u] = *(const chunk_t *)(xb + off[u]);
       b[u] = *(const chunk_t *)(xb + off[u] + hd);
     }
 #pragma unroll
-    for (int u = 0; u < kItems; ++u) {
+    for (int u = 0; u < kFly; ++u) {
       if (i0 + u * kThreads >= n_items) break;
       chunk_t ra, rb;
 #pragma unroll
       for (int e = 0; e < kVec; ++e) {
-        const float x1 = C::get(a[u], e), x2 = C::get(b[u], e), c1 = cs[e0[u] + e], s1 = sn[e0[u] + e];
+        const float x1 = C::get(a[u], e), x2 = C::get(b[u], e);
+        float c1, s1;
+        if constexpr (kDirect) {
+          cos_sin((double)pos[t0 + i0 / cpt], i0 % cpt * kVec + e, neg2_log2base_over_d, inverse, c1, s1);
+        } else {
+          c1 = cs[e0[u] + e];
+          s1 = sn[e0[u] + e];
+        }
         C::set(ra, e, x1 * c1 - x2 * s1);
         C::set(rb, e, x2 * c1 + x1 * s1);
       }
@@ -95,19 +113,21 @@ hipError_t launch(const void *x, void *y, const void *pos, long long N, int H, i
                   int inverse, hipStream_t stream) {
   if (N == 0) return hipSuccess;
   const int hd = d / 2, cpt = hd / kVec;
-  const int h_most = (1 << 24) / cpt;  // heads of one launch: a workgroup counts its items in 32 bits
-  for (int h0 = 0; h0 < H; h0 += h_most) {
-    const int h = H - h0 < h_most ? H - h0 : h_most;
-    long long tokens = kItems * kThreads / ((long long)h * cpt);
-    if (tokens > kMaxPairs / hd) tokens = kMaxPairs / hd;
-    while (tokens > 1 && N / tokens < kMinGroups) tokens /= 2;
-    if (tokens < 1) tokens = 1;
-    const long long grid = (N + tokens - 1) / tokens;
-    if (grid > 0x7fffffffll) return hipErrorInvalidValue;
-    rope_kernel<T, kVec, IdT><<<(unsigned)grid, kThreads, 0, stream>>>(
-        (const T *)x + (size_t)h0 * d, (T *)y + (size_t)h0 * d, (const IdT *)pos, N, (int)tokens, (size_t)H * d, h, d,
-        -2.0 * log2(base) / (double)d, inverse);
-  }
+  const long long per_token = (long long)H * cpt;  // items
+  // One head and a workgroup of single items per CU: 65536 tokens of 128 12.2 us (with a table 17), 20000 of 64
+  // 4.7 (5.7), but 12000 of 64 4.1 (3.9): fewer leave the chip waiting for eight sines in a row.
+  const bool direct = H == 1 && N * cpt >= 256 * kThreads;
+  long long tokens = direct ? kThreads / cpt : std::max(1ll, std::min(kItems * kThreads / per_token, (long long)kMaxPairs / hd));
+  while (!direct && tokens > 1 && N / tokens < kMinGroups && tokens * per_token >= 2 * kLeastItems) tokens /= 2;
+  const long long groups = (N + tokens - 1) / tokens;
+  if (groups > 0x7fffffffll) return hipErrorInvalidValue;
+  // Tokens alone are too few to fill the chip, but have more items than a workgroup keeps in flight: heads are split too
+  // (16 tokens, 2048 heads of 256: 47 -> 6.6 us).  A workgroup counts its items in 32 bits.
+  const long long parts = std::max({std::min((kMinGroups + groups - 1) / groups, per_token / (kItems * kThreads)), per_token >> 24, 1ll});
+  const int heads = (int)((H + parts - 1) / parts);
+  auto *kernel = direct ? rope_kernel<T, kVec, IdT, true> : rope_kernel<T, kVec, IdT, false>;
+  kernel<<<dim3((unsigned)groups, (unsigned)((H + heads - 1) / heads)), kThreads, 0, stream>>>(
+      (const T *)x, (T *)y, (const IdT *)pos, N, (int)tokens, H, heads, d, -2.0 * log2(base) / (double)d, inverse);
   return hipGetLastError();
 }
 

@@ -43,7 +43,8 @@ def test_collate(n, cut):
     _compare(ids, lengths, 0 if cut == 5 else total - cut, pad_id=3)
 
 
-@pytest.mark.parametrize("shape", [(4099, 1, 16), (1027, 7, 128), (3, 200, 128), (700, 5, 80), (259, 3, 6), (2, 130, 256)])
+@pytest.mark.parametrize("shape", [(4099, 1, 16), (1027, 7, 128), (3, 200, 128), (700, 5, 80), (259, 3, 6), (2, 130, 256), (5, 700, 96), (1, 2100, 10),
+                                   (11000, 1, 96), (66000, 1, 2), (21845, 1, 48)])   # one head, an item a thread
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("inplace", [False, True])
 def test_rope(shape, dtype, inplace):
