@@ -80,8 +80,12 @@ collate_tokens_kernel(const IdT *__restrict__ ids, const IdT *__restrict__ label
 // Minibatches of 1 .. kOneMax examples, in one launch: every workgroup sums the lengths into offsets of its own
 // in LDS (at most kOneMax ints, read from L2), where the bisection then runs; the first one stores them.
 // Bound: launch latency.  1024 examples, 70 thousand tokens: 5.6 us; 4 examples: 4.1 us (offsets and
-// tokens in two launches: 10.4 and 5.3 us).
-constexpr int kOneMax = 2048;
+// tokens in two launches: 10.4 and 5.3 us).  With many examples and many workgroups (of 256 tokens) the sums that
+// each repeats cost more than the launch.  One launch / two, us: 2048 examples, 540, 915, 1416, 2120, 8222 workgroups
+// 6.3 / 8.6, 7.4 / 8.9, 9.8 / 9.8, 13.5 / 11.5, 37 / 26; 1500, 667, 2079, 4440 5.8 / 8.7, 11.3 / 11.5, 19.2 / 17.3;
+// 1024, 3027, 14164 11.9 / 11.9, 37 / 35; 768, 4608 14.7 / 15.6; 512, 14204 28 / 33.
+constexpr int kOneMax = 2048, kOneAlways = 512;
+constexpr long long kOneWork = 3 << 19;  // examples beyond kOneAlways x workgroups
 template <typename IdT>
 __global__ void __launch_bounds__(256)
 collate_one_kernel(const IdT *__restrict__ ids, const IdT *__restrict__ labels_in, const int32_t *__restrict__ lengths,
@@ -126,8 +130,8 @@ collate_one_kernel(const IdT *__restrict__ ids, const IdT *__restrict__ labels_i
 hipError_t launch_collate(const void *ids, const void *labels_in, va_itype it, const int32_t *lengths,
                           int n, int Lp, int n_out, long long pad_id, void *input_ids, void *labels,
                           void *position_ids, int32_t *offsets, hipStream_t stream) {
-  const bool one = n >= 1 && n <= kOneMax;
   const unsigned grid = (unsigned)(n_out > 0 ? ceil_div(n_out, 256) : 1);
+  const bool one = n >= 1 && n <= kOneMax && (n - kOneAlways) * (long long)grid <= kOneWork;
   if (!one) {
     collate_offsets_kernel<<<1, kOffThreads, 0, stream>>>(lengths, n, Lp, offsets);
     hipError_t e = hipGetLastError();

@@ -43,6 +43,15 @@ def test_collate(n, cut):
     _compare(ids, lengths, 0 if cut == 5 else total - cut, pad_id=3)
 
 
+@pytest.mark.parametrize("n_out", [1024 * 256, 1024 * 256 + 1])  # the last of 2048 examples in one launch, the first in two
+def test_collate_many_tokens(n_out):
+    rng = np.random.default_rng(n_out)
+    lengths = rng.integers(100, 160, size=2048).astype(np.int32)
+    ids = rng.integers(0, 1000, size=(2048, 160))
+    assert int(lengths.sum()) > n_out
+    _compare(ids, lengths, n_out, pad_id=3)
+
+
 @pytest.mark.parametrize("shape", [(4099, 1, 16), (1027, 7, 128), (3, 200, 128), (700, 5, 80), (259, 3, 6), (2, 130, 256), (5, 700, 96), (1, 2100, 10),
                                    (11000, 1, 96), (66000, 1, 2), (21845, 1, 48)])   # one head, an item a thread
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
