@@ -53,30 +53,15 @@ def flops(cfg, pairs):
     return f, b
 
 
-def mean_blocks(pos_np):
-    """64-query blocks that a 256-key tile streams, on average over the batch."""
-    rows, T = pos_np.shape
-    start = pos_np.reshape(-1) == 0
-    start[::T] = True
-    starts = np.flatnonzero(start)
-    end = np.repeat(np.append(starts[1:], rows * T), np.diff(np.append(starts, rows * T)))
-    t0 = (np.arange(rows)[:, None] * T + np.arange(0, T, 256)[None, :])
-    t1 = np.minimum(t0 + 256, (np.arange(rows)[:, None] + 1) * T) - 1
-    return float(np.mean((end[t1] - 1) // 64 - t0 // 64 + 1))
-
-
 class GpuRun:
     """Device buffers + one `step()` of the path; stage events for per-kernel timing."""
 
-    def __init__(self, torch, binding, pos_np, q, k, v, do, n_examples=None):
+    def __init__(self, torch, binding, pos_np, q, k, v, do):
         self.torch, self.b = torch, binding
         # the host made these lengths, so it can name the dK/dV kernel's shape instead of having the
-        # device pick between two launches (the device's own rule: mean example length >= 1024 tokens, or
-        # an average of 12 or more 64-query blocks per 256-key tile)
-        self.hint = 0
-        if n_examples:
-            long_ = pos_np.size >= 1024 * n_examples or mean_blocks(pos_np) >= 12
-            self.hint = binding.HINT_LONG_EXAMPLES if long_ else binding.HINT_SHORT_EXAMPLES
+        # device pick between two launches
+        from paper_2407_09105_amd.workloads import example_length_hint
+        self.hint = example_length_hint(pos_np, q.shape[1], k.shape[1], q.shape[2])
         self.pos = torch.from_numpy(pos_np).cuda()
         self.q, self.k, self.v, self.do = q, k, v, do
         self.seg = binding.Segments(pos_np.shape[0], pos_np.shape[1], "cuda")
@@ -146,7 +131,7 @@ def padded_run(torch, binding, wl, w, q, k, v, do, mode="group_max"):
         out[ip] = t[ir]
         return out
 
-    run = GpuRun(torch, binding, pos, pad(q), pad(k), pad(v), pad(do), n_examples=len(lay))
+    run = GpuRun(torch, binding, pos, pad(q), pad(k), pad(v), pad(do))
     return run, n_pad, ir, ip
 
 
@@ -156,7 +141,7 @@ def no_posid_run(torch, binding, w, q, k, v, do):
     row, so no key tile is skipped; useful FLOPs counted are still those of the real examples."""
     cfg = w.cfg
     pos = np.tile(np.arange(cfg.tokens_per_row, dtype=np.int64), (cfg.rows, 1))
-    return GpuRun(torch, binding, pos, q, k, v, do, n_examples=cfg.rows)
+    return GpuRun(torch, binding, pos, q, k, v, do)
 
 
 def collate_timing(torch, binding, w, steps):
@@ -181,7 +166,7 @@ def collate_timing(torch, binding, w, steps):
     ok = bool((out["position_ids"].cpu().numpy() == w.position_ids[:1]).all())
     return {"ms": ms, "examples": n, "padded_len": Lp, "tokens": T, "algorithmic_bytes": algo_bytes,
             "achieved_GBs": algo_bytes / (ms * 1e-3) / 1e9, "frac_hbm_peak": algo_bytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-            "bound": "launch latency (two tiny kernels)", "position_ids_match_workload": ok}
+            "bound": "launch latency (one or two tiny kernels)", "position_ids_match_workload": ok}
 
 
 def rope_timing(torch, binding, w, q, steps):
@@ -255,8 +240,7 @@ def measured_peaks(torch):
 def cold_cache_ms(torch, binding, w, q, k, v, do, steps, copies=3):
     """The same step cycling through `copies` independent sets of inputs and outputs (each ~0.5 GB on
     config 2), so that no step finds its tensors in the 256 MB last-level cache."""
-    runs = [GpuRun(torch, binding, w.position_ids, q.clone(), k.clone(), v.clone(), do.clone(),
-                   n_examples=w.stats["n_segments"]) for _ in range(copies)]
+    runs = [GpuRun(torch, binding, w.position_ids, q.clone(), k.clone(), v.clone(), do.clone()) for _ in range(copies)]
     for r in runs:
         r.step()
     torch.cuda.synchronize()
@@ -287,8 +271,7 @@ def packer_runs(torch, binding, wl, cfg, seed, steps):
         pos = pk.position_ids(rows, T)
         N = pos.size
         mk = lambda h: torch.randn((N, h, cfg.d), device="cuda", generator=g, dtype=torch.float32).to(torch.bfloat16)
-        run = GpuRun(torch, binding, pos, mk(cfg.hq), mk(cfg.hkv), mk(cfg.hkv), mk(cfg.hq),
-                     n_examples=sum(len(r) for r in rows))
+        run = GpuRun(torch, binding, pos, mk(cfg.hq), mk(cfg.hkv), mk(cfg.hkv), mk(cfg.hq))
         ms, _ = timed(torch, run, steps, 3, with_events=False)
         pairs = sum(L * (L + 1) // 2 for r in rows for _, L in r)
         fl = sum(flops(cfg, pairs))
@@ -417,7 +400,7 @@ def bench_config(torch, binding, wl, cfg_id, args, headline):
     assert cfg.dtype == "bf16"
     to_dev = lambda a: torch.from_numpy(a).cuda().to(torch.bfloat16)
     q, k, v, do = to_dev(w.q), to_dev(w.k), to_dev(w.v), to_dev(w.do)
-    run = GpuRun(torch, binding, w.position_ids, q, k, v, do, n_examples=w.stats["n_segments"])
+    run = GpuRun(torch, binding, w.position_ids, q, k, v, do)
     ms, stages = timed(torch, run, args.steps, args.warmup)
     # the same K steps without stage events (the figure reported as `value`)
     ms_plain, _ = timed(torch, run, args.steps, 2, with_events=False)

@@ -210,3 +210,23 @@ def padded_layout(lengths_per_row: List[List[int]], group: int = 4, mode: str = 
         m = max(g)
         out.extend((L, m) for L in g)
     return out
+
+
+def example_length_hint(position_ids: np.ndarray, hq: int, hkv: int, d: int) -> int:
+    """The hint of the backward (binding.HINT_*) with which the dK/dV shape runs that the device would pick for these
+    position ids ([rows, tokens] on the host): long where the mean example has 1024 tokens or where a 256-key tile streams
+    12 blocks of 64 queries on average.  0, the choice left to the device, where key tiles may be shared by several
+    workgroups: what it asks there depends on how finely they can be cut."""
+    from . import binding
+    rows, T = position_ids.shape
+    if binding.lib().va_attn_workspace_bytes(rows * T, hq, hkv, d, 1) > (rows * T * hq * 4 + 255) // 256 * 256:
+        return 0
+    start = position_ids.reshape(-1) == 0
+    start[::T] = True
+    starts = np.flatnonzero(start)
+    end = np.repeat(np.append(starts[1:], rows * T), np.diff(np.append(starts, rows * T)))
+    row0 = np.arange(rows)[:, None] * T
+    t0 = row0 + np.arange(0, T, 256)[None, :]
+    blocks = (end[np.minimum(t0 + 256, row0 + T) - 1] - 1) // 64 - t0 // 64 + 1
+    long_ = rows * T >= 1024 * starts.size or blocks.sum() >= 12 * blocks.size
+    return binding.HINT_LONG_EXAMPLES if long_ else binding.HINT_SHORT_EXAMPLES

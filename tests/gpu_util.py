@@ -6,7 +6,7 @@ import numpy as np
 import torch
 
 from oracle import oracle
-from paper_2407_09105_amd import binding
+from paper_2407_09105_amd import binding, workloads as wl
 from tests.conftest import progress
 
 DEV = "cuda:0"
@@ -34,9 +34,8 @@ def max_abs(x, ref) -> float:
 
 
 def bench_hint(w):
-    """The example-length hint bench.py passes for this workload (same rule: mean length against 1024)."""
-    n = int(oracle.pack(w.position_ids)["cu_seqlens"].size) - 1
-    return binding.HINT_LONG_EXAMPLES if w.position_ids.size >= 1024 * n else binding.HINT_SHORT_EXAMPLES
+    """The example-length hint bench.py passes for this workload."""
+    return wl.example_length_hint(w.position_ids, w.cfg.hq, w.cfg.hkv, w.cfg.d)
 
 
 def run_gpu(w, grad_dtype=None, scale=0.0, pos_dtype=torch.int64, nan_fill=False, hint=0):

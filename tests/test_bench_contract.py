@@ -6,11 +6,14 @@ import subprocess
 import sys
 
 import numpy as np
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import bench  # noqa: E402
-from paper_2407_09105_amd import workloads as wl  # noqa: E402
+from oracle import oracle  # noqa: E402
+from paper_2407_09105_amd import binding, workloads as wl  # noqa: E402
+from tests.gpu_util import bench_hint  # noqa: E402
 
 
 def test_more_than_one_gpu_is_refused_with_a_message():
@@ -89,6 +92,40 @@ def test_product_path_never_imports_the_oracle():
     for name in os.listdir(os.path.join(ROOT, "oracle")):
         if name.endswith((".py", ".c")):
             assert "paper_2407_09105_amd" not in open(os.path.join(ROOT, "oracle", name)).read(), name
+
+
+def _device_rule(w):
+    """The dK/dV shape rule of the device where no tile is cut, from the oracle's boundaries."""
+    seg = oracle.pack(w.position_ids)
+    rows, T = w.position_ids.shape
+    blocks = []
+    for t0 in (r * T + m for r in range(rows) for m in range(0, T, 256)):
+        last = min(t0 + 256, (t0 // T + 1) * T) - 1
+        blocks.append((int(seg["seg_end"][last]) - 1) // 64 - t0 // 64 + 1)
+    long_ = rows * T >= 1024 * seg["n"] or sum(blocks) >= 12 * len(blocks)
+    return binding.HINT_LONG_EXAMPLES if long_ else binding.HINT_SHORT_EXAMPLES
+
+
+@pytest.mark.parametrize("cfg_id", [2, 3, 4, 5])
+def test_the_parity_tests_and_the_benchmark_run_the_shape_the_device_would_pick(cfg_id):
+    class Torch:   # GpuRun allocates its buffers here
+        float32 = None
+        empty = empty_like = staticmethod(lambda *a, **k: None)
+        from_numpy = staticmethod(lambda a: type("T", (), {"cuda": lambda self: None})())
+    w = wl.make_workload(cfg_id, tensors=False)
+    cfg = w.cfg
+    fake = type("B", (), {"Segments": lambda *a: None, "bwd_workspace": lambda *a: None})
+    q, k = np.empty((0, cfg.hq, cfg.d)), np.empty((0, cfg.hkv, cfg.d))
+    run = bench.GpuRun(Torch, fake, w.position_ids, q, k, k, q)
+    assert run.hint == bench_hint(w) == _device_rule(w)
+    # config 2: 546 tokens a mean example, but 12.9 blocks a key tile
+    assert run.hint == {2: binding.HINT_LONG_EXAMPLES, 4: binding.HINT_SHORT_EXAMPLES, 5: binding.HINT_LONG_EXAMPLES}.get(cfg_id, run.hint)
+
+
+def test_no_hint_where_key_tiles_may_be_shared():
+    pos = wl.position_ids_from_lengths([[3600] + [31] * 16])   # 241 tokens a mean example, 27 blocks a key tile
+    assert wl.example_length_hint(pos, 16, 2, 128) == 0
+    assert wl.example_length_hint(pos, 32, 32, 128) == binding.HINT_LONG_EXAMPLES
 
 
 def test_padded_layout_groups_of_four():
