@@ -1098,8 +1098,9 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     const DkdvLaunch<kDh> l(partial, N, T, hq, hkv);
     const DkdvSplit &sl = l.large, &ss = l.small;
     // Nothing about the lengths is known on the host: both shapes are launched and the device picks, unless
-    // the caller's hint names the shape or no example can be as long as calls for the large one (a row of fewer than
-    // kDkdvLongMean tokens has at most 10 blocks a tile).
+    // the caller's hint names the shape or no example can be as long as calls for the large one: four tiles of a row of 1023
+    // tokens, begun 63 tokens behind a multiple of the block, stream at most 17 + 13 + 9 + 5 blocks, 11 a tile.
+    static_assert(kDkdvLongMean == 1024 && kBS == 64 && VA_TILE == 256 && kDkdvLongBlocks > 11, "shorter rows may call for the large shape");
     bool run_large = kDh > 128 || !(stages & VA_HINT_SHORT_EXAMPLES);
     bool run_small = kDh <= 128 && !(stages & VA_HINT_LONG_EXAMPLES);
     if (run_small && T < kDkdvLongMean) run_large = false;

@@ -14,7 +14,7 @@ def _gpu_pack(pos_np, dtype=torch.int64):
     pos = torch.from_numpy(pos_np).to(DEV).to(dtype)
     seg = binding.pack_to_cu_seqlens(pos)
     torch.cuda.synchronize()
-    return seg.host()
+    return {**seg.host(), "key_blocks": int(seg.meta[2])}
 
 
 def _check_orders(got, pos_np):
@@ -29,6 +29,8 @@ def _check_orders(got, pos_np):
     ss, se = ref["seg_start"].astype(np.int64), ref["seg_end"].astype(np.int64)
     cost_q = (t1 >> 6) - (ss[t0] >> 6) + 1
     cost_kv = ((se[t1] - 1) >> 6) - (t0 >> 6) + 1
+
+    assert got["key_blocks"] == cost_kv.sum()   # the dK/dV kernels choose their shape and their cuts by it
 
     def key(length, start, cost):
         # examples of at most one schedule tile all rank alike (they stay in stream order), longer ones by length
