@@ -5,11 +5,12 @@ One "step" = one pass of the whole path over one packed batch resident in HBM:
 position_ids -> cu_seqlens / tile schedule, forward (O, LSE), backward (dQ, dK, dV).
 
 Prints ONE JSON line.  Its headline (`value`, `roofline`, `cpu_baseline`) is the largest
-single-GPU workload, configs[4] (2 x 16384 tokens, 40 / 8 heads, long-tail lengths): useful
+single-GPU workload (2 x 16384 tokens, 40 / 8 heads, long-tail lengths): useful
 (mask-respecting, padding-free) attention TFLOP/s of fwd+bwd, tokens/s, the roofline fraction
 of the dominant kernel and the CPU oracle timed on a bounded sample of the same workload.
-`per_config` carries the same figures for every bf16 workload (configs[1..4]), each with the
-same kernels on the equivalent padded batches and without position ids.
+`per_config` carries the main figures of every bf16 workload, with the same kernels on the
+equivalent padded batches and without position ids; all of a workload's figures go to stderr,
+one JSON line each (in one line they are longer than 8 KB, and consoles keep only its end).
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 5] [--only] [--no-cpu-baseline]
 """
@@ -462,6 +463,29 @@ def bench_config(torch, binding, wl, cfg_id, args, headline):
     return out
 
 
+def brief(r):
+    """A workload's entry in the `per_config` list (everything measured on it is printed to stderr)."""
+    pick = lambda d, *keys: {k: d[k] for k in keys if k in d}
+    out = {"workload": r["config"]["workload"], **pick(r, "value", "unit", "ms_per_step", "tokens_per_s", "stage_ms"),
+           "roofline": pick(r["roofline"], "kernel", "bound", "achieved", "unit", "frac")}
+    if "padded" in r:
+        out["padded"] = {mode: pick(p, "ms_per_step", "packing_gain") for mode, p in r["padded"].items()}
+    if "no_position_ids" in r:
+        out["no_position_ids"] = pick(r["no_position_ids"], "ms_per_step", "position_id_gain")
+    if "cpu_baseline" in r:
+        out["cpu_baseline"] = pick(r["cpu_baseline"], "value", "unit", "full_workload_seconds_is")
+    return out
+
+
+def rounded(x):
+    """Floats to six digits: what is printed of them beyond that is noise, and a third of the line."""
+    if isinstance(x, dict):
+        return {k: rounded(v) for k, v in x.items()}
+    if isinstance(x, list):
+        return [rounded(v) for v in x]
+    return float(f"{x:.6g}") if isinstance(x, float) else x
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -496,14 +520,19 @@ def main():
         "ms_per_step": head["ms_per_step"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
     }
-    out.update({k: v for k, v in head.items() if k not in out})
+    aside = {"collate", "rope", "packers"}   # measured with the headline's inputs: with the rest on stderr
+    out.update({k: v for k, v in {**head, **brief(head)}.items() if k not in out and k not in aside | {"workload"}})
+    out.update({k: head[k] for k in ("roofline", "cpu_baseline") if k in head})
     if not args.no_extras:
         out["measured_peaks"] = measured_peaks(torch)
         out["frac_measured_mfma_peak"] = head["value"] / out["measured_peaks"]["mfma_bf16_TFLOPs"]
     if "cpu_baseline" not in out:
         out["cpu_baseline"] = None
-    out["per_config"] = sorted(per_config, key=lambda r: r["config"]["workload"])
-    print(json.dumps(out))
+    per_config.sort(key=lambda r: r["config"]["workload"])
+    for r in per_config:
+        print("bench.py: " + json.dumps(r), file=sys.stderr, flush=True)
+    out["per_config"] = [brief(r) for r in per_config]
+    print(json.dumps(rounded(out)))
 
 
 if __name__ == "__main__":

@@ -1,6 +1,7 @@
 """Host-side parts of the benchmark's contract (no GPU): the one-GPU rule, the FLOP accounting, the
 profile summary it reads, and that nothing of the product path reaches into the oracle."""
 import ast
+import json
 import os
 import subprocess
 import sys
@@ -70,6 +71,18 @@ def test_traffic_summary_is_parsed(tmp_path, monkeypatch):
         for kernel in ("fwd_mfma_kernel", "dq_mfma_kernel", "dkdv_mfma_kernel"):
             t = bench.read_traffic(cfg_id, kernel)
             assert t is not None and t > 0, (cfg_id, kernel)
+
+
+def test_the_line_carries_the_main_figures_of_every_workload():
+    w = wl.make_workload(2)
+    stages = {"fwd": 0.1234567891, "bwd_dQ": 0.2, "bwd_dKdV": 0.3}
+    r = {"config": {"workload": "one row", "n_tokens": 8192}, "value": 512.123456789, "unit": "TFLOP/s", "ms_per_step": 0.5, "tokens_per_s": 1e7,
+         "stage_ms": stages, "roofline": bench.roofline_of(w.cfg, w.stats["pairs"], stages, 2),
+         "padded": {"group_max": {"layout": "x" * 200, "ms_per_step": 1.0, "packing_gain": 2.0}}}
+    b = bench.rounded(bench.brief(r))
+    assert b["workload"] == "one row" and b["value"] == 512.123 and b["stage_ms"]["fwd"] == 0.123457
+    assert b["roofline"]["kernel"] == "dkdv_mfma_kernel" and b["padded"] == {"group_max": {"ms_per_step": 1.0, "packing_gain": 2.0}}
+    assert len(json.dumps(b)) < 1000
 
 
 def test_product_path_never_imports_the_oracle():
