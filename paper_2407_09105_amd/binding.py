@@ -103,15 +103,13 @@ def _dt(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-# torch's own internal call: 0.3 us, where building a torch.cuda.Stream object takes 2.8
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
-def _stream() -> int:
-    """The current device's current stream."""
-    if _raw_stream is None:  # a torch without that call
+# The current device's current stream: torch's internal call takes 0.3 us, building a torch.cuda.Stream object 2.8.
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _stream() -> int:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+else:
+    def _stream() -> int:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
 
 
 def _need_cuda(*ts):

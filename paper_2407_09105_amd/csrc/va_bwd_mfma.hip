@@ -501,17 +501,20 @@ struct DkdvPlan {
   int piece;  // least trips of a chunk
   int most;   // no tile gets more chunks
 };
-__device__ __forceinline__ DkdvPlan dkdv_plan(const int32_t *__restrict__ meta, int keys, int slots, int N, int T, int hq, int G,
-                                              const DkdvSplit &split) {
+__device__ __forceinline__ DkdvPlan dkdv_plan(const int32_t *__restrict__ meta, int keys, int slots, int N, int T, int tiles_per_row,
+                                              int hq, int G, const DkdvSplit &split) {
   // 64-query blocks over all schedule tiles (meta[2]) x workgroup tiles in one x heads, over the workgroups the chip holds
-  const float share = (float)meta[2] * (float)(VA_TILE / keys * hq) * (1.f / slots);
+  const float per_block = (float)(VA_TILE / keys * hq) * (1.f / slots), share = (float)meta[2] * per_block;
   const int piece = max(kMinTrips, (int)(share * (split.fine ? 1.f / kChunksPerSlot : 1.f / kChunksPerSlotMany)) + 1);
   // The longest chain that the longest example (meta[1]) allows: a tile's blocks reach from at most keys - 1 tokens before
   // an example to the end of it, and begin up to `off` tokens behind a multiple of the block.
   const int off = N == T ? 0 : kBS - min(kBS, T & -T);
   const int chain = ((meta[1] + keys - 2 + off) / kBS + 1) * G;
   const bool all_long = !split.fine && (long long)N >= (long long)kDkdvLongMean * meta[0];
-  const float bar = all_long ? 1.5f * share : share + (float)kMinTrips;
+  // Less what the later workgroup tiles of a schedule tile do not stream (16384 tokens in examples of about 100, 36/4 heads,
+  // chains of 126 trips: cut 219 us, not cut 237).  `piece` keeps to the larger number, for which slots suffice.
+  const float least = share - (float)(N / T * tiles_per_row) * ((VA_TILE - keys) / (2.f * kBS)) * per_block;
+  const float bar = all_long ? 1.5f * least : fmaxf(least, 0.f) + (float)kMinTrips;
   return {piece, (float)chain < bar ? 1 : max(1, min(split.max_chunks, chain / piece))};
 }
 // Chunks of a tile of n_it trips, and the trips of all but the last.  With many tiles the chunks are of one length, whole
@@ -617,25 +620,27 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   int pair = blockIdx.x, chunk = 0;
   DkdvPlan plan = {0, 1};
   if constexpr (kCut) {
-    plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, hq, hq / hkv, split);
-    const int most = plan.most, n_pairs = gridDim.x / split.max_chunks;
-    if (pair >= n_pairs * most) return;
+    plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, tiles_per_row, hq, hq / hkv, split);
+    const int most = plan.most;
+    if (blockIdx.x * split.max_chunks >= gridDim.x * most) return;
     if (most > 1 && split.fine) {
       // The tiles in order of their length, a tile's chunks together (16 heads on one KV head, 6141 tokens: 79 us; the
       // first chunks of all tiles, then the second ones, ...: 107 us).  Where `most` is even, the first chunks, which every
       // tile has, would keep to every other engine or XCD: they move on by the digit sum of the tile's number (4096 tokens
       // in examples of 8 to 128, 40/8 heads: 85 -> 57 us; moved on where it is odd, the 1500 tokens of four examples: 48 -> 58).
       const int q = pair / hkv, u = q / most;
-      int turn = q - u * most;
-      if (most % 2 == 0)
-        for (int x = u; x > 0; x /= most) turn += x;
-      chunk = turn % most;
+      chunk = q - u * most;
+      if (most % 2 == 0) {
+        for (int x = u; x > 0; x /= most) chunk += x;
+        chunk %= most;
+      }
       pair += (u - q) * hkv;
     } else if (most > 1) {
       // Most tiles have one chunk: last chunks first, so that the longest tiles start early (three rows of 3735 tokens,
       // 36/4 heads: 347 us, numbered by tile 440).
-      chunk = most - 1 - pair / n_pairs;
-      pair = pair % n_pairs;
+      const int n_pairs = gridDim.x / split.max_chunks, level = pair / n_pairs;
+      chunk = most - 1 - level;
+      pair -= level * n_pairs;
     }
   }
   const int entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
@@ -967,7 +972,7 @@ dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *_
   const int key_groups = is_small || kDh > 128 ? 2 : 4;
   const int sub_tiles = VA_TILE / 32 / key_groups;
   if (split.max_chunks == 1) return;
-  const DkdvPlan plan = dkdv_plan(meta, 32 * key_groups, is_small ? 512 : 256, N, T, hq, hq / hkv, split);
+  const DkdvPlan plan = dkdv_plan(meta, 32 * key_groups, is_small ? 512 : 256, N, T, tiles_per_row, hq, hq / hkv, split);
   if (plan.most == 1) return;  // before any tile is looked up
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
   const int kgi = blockIdx.x % (VA_TILE / 32), head_slot = blockIdx.x / (VA_TILE / 32) % hkv;
