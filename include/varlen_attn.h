@@ -189,8 +189,8 @@ va_status va_varlen_attn_bwd(const void *dO, const void *Q, const void *K, const
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and errors as va_varlen_attn_bwd, without `workspace`: it lives in a device array inside the library
  * (VA_NOALLOC_SCRATCH_BYTES for D and 64 MiB for partial sums per GPU, held until the process ends).
- * Calls no hipMalloc / hipFree and no allocating routine; the first call on a device looks the array's address up once (make that call
- * outside stream capture).
+ * Calls no hipMalloc / hipFree and no allocating routine; the first call on a device looks the
+ * array's address up once (make that call outside stream capture).
  *   Limit: rows * tokens_per_row * hq * 4 <= VA_NOALLOC_SCRATCH_BYTES, else VA_ERR_WORKSPACE and
  *   nothing is enqueued.
  *   All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

@@ -441,7 +441,7 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
 // the work, which the mean does not show.  Time of the large over the small shape, 7 head layouts (1 to 16
 // query heads per KV head, d = 64..128), 8192 to 32768 tokens: 5 blocks a tile 0.85...1.30 (mean 1.14), 6.5 to 8
 // blocks 0.93...1.17 (1.08), 10 to 11.5 blocks 0.91...1.12 (1.00), 13 blocks and more 0.86...1.03 (0.94).  Where
-// the small shape's tiles may be cut (below) no long chain is left for the large one to shorten, and 18 blocks
+// the small shape's tiles may be cut finely (below) no long chain is left for the large one to shorten, and 18 blocks
 // give 0.94...1.09: there the mean alone decides (by_mean).
 constexpr int kDkdvLongMean = 1024;
 constexpr int kDkdvLongBlocks = 12;
@@ -469,11 +469,11 @@ template <int kDh, bool kSmall> struct DkdvShape {
 // 303 us for one example of 4096 tokens with 4 query heads per KV head.
 //   host  : how many chunks a tile may have follows from the number of tiles and the workspace
 //           (plan_split below); with many tiles it is one, and no merge kernel is launched.  In between, where
-//           grouped heads make chains longer than a compute unit's share of the work, only those are cut: 3735 and 4034
-//           tokens in three rows, 36/4 heads: step 1300 -> 1095 and 1602 -> 1310 us; 4248 tokens, 40/8: 415 -> 365.
-//           (Where every example fills its row they gain little or lose: three rows of 4034 tokens, 36/4 heads, 1.07 of the
-//           dK/dV time uncut, 8192 and 12000 tokens 1.01.)
-//   device: how many it gets follows from its own trips and the batch's total.
+//           grouped heads make chains longer than a resident workgroup's share of the work, only those are cut: dK/dV of
+//           three rows of 3735 tokens, 36/4 heads, 510 -> 347 us; 16384 long-tail tokens 640 -> 425; 4248 tokens, 40/8,
+//           one example, 540 -> 480.
+//   device: whether the batch is cut at all follows from its longest example and its total (dkdv_plan), how many chunks a
+//           tile then gets from its own trips.
 struct DkdvSplit {
   float *partial;   // slots of 2 * kKeys * kDh floats
   int max_chunks;   // per (tile, KV head) pair; 1: no tile is cut
