@@ -22,7 +22,7 @@
 // run on whole blocks with a masked factor of 0, and a wave that meets another factor in such a block that is not finite
 // (0 * Inf = NaN) forms its sums again, token by token (`redo`).
 // Measured, 1000 tokens, 8 query / 2 KV heads, d = 64, examples of up to 315 tokens, against one wave per output row
-// on the vector units: forward 257 -> 15 us, dQ (with D) 214 -> 22 us, dK/dV 484 -> 30 us.  Bound there by the
+// on the vector units: forward 257 -> 16 us, dQ (with D) 214 -> 23 us, dK/dV 484 -> 32 us.  Bound there by the
 // matrix instructions of the CUs that hold the longest examples' tiles; one example of 8000 tokens runs the
 // forward at 76 TFLOP/s, half of what a large fp32 library product reaches.
 #include <algorithm>
@@ -77,6 +77,41 @@ __device__ __forceinline__ void load_row(const T *row, int kq, int d, float (&f)
 #pragma unroll
     for (int e = 0; e < 4; ++e) f[4 * i + e] = x[e];
   }
+}
+
+// The products of 16 streamed rows and the tile's 16 rows, over the head_dim, in eight chains of the matrix instruction
+// (head_dim 16: four) that are then added in pairs.  An error of a score is an error of its probability, and a single
+// chain has two to three times that of the pairwise sums of a wave per row, against 64 bits, scores of about 100,
+// head_dim 64: O 1.9e-6 (pairwise 6.7e-7), LSE 1.1e-5 (4.1e-6); two chains 1.1e-6, 6.3e-6; four 7.9e-7, 4.9e-6; eight
+// 6.9e-7, 4.3e-6.
+template <int kDh> __device__ __forceinline__ f32x4 row_product(const float (&a)[kDh / 4], const float (&b)[kDh / 4]) {
+  constexpr int kChains = kDh < 32 ? 4 : 8;
+  f32x4 x[kChains];
+#pragma unroll
+  for (int c = 0; c < kChains; ++c) x[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < kDh / 4; ++i) x[i % kChains] = mfma16(a[i], b[i], x[i % kChains]);
+#pragma unroll
+  for (int n = kChains / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int c = 0; c < n; ++c) x[c] += x[c + n];
+  return x[0];
+}
+// dP likewise; up to head_dim 64 it is dP - D, in one chain from -D: more chains take time (backward of 1000 tokens 43.4 ->
+// 45.2 us, in two 45.7) and give nothing (dQ 3.7e-6; in eight chains 3.6e-6).  Beyond, D is left to the caller
+// (kLessD): eight chains are the faster ones there (backward of 4000 tokens of 128: 1475 us, one from -D 1525).
+template <int kDh> constexpr bool kLessD = kDh <= 64;
+template <int kDh> __device__ __forceinline__ f32x4 grad_product(const float (&a)[kDh / 4], const float (&b)[kDh / 4], const f32x4 &delta) {
+  if constexpr (!kLessD<kDh>) return row_product<kDh>(a, b);
+  f32x4 x = -delta;
+#pragma unroll
+  for (int i = 0; i < kDh / 4; ++i) x = mfma16(a[i], b[i], x);
+  return x;
+}
+// Probability of a scaled score from the row's LSE: the difference is formed before it is scaled for exp2, so that its
+// error is that of the score and the LSE, not theirs times the rounding of scale * log2(e).
+__device__ __forceinline__ float prob(float s, float scale, float lse) {
+  return __builtin_amdgcn_exp2f(fmaf(s, scale, -lse) * 1.4426950408889634f);
 }
 
 // Output columns come in groups of 16 kE; within a group, register block e holds the columns kE * row + e.
@@ -234,9 +269,7 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
     loads_first<kDh>();
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < kDh / 4; ++i) s[b] = mfma16(kf[b][i], qf[i], s[b]);
+      s[b] = row_product<kDh>(kf[b], qf);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int j = j0 + 16 * b + 4 * kq + v;
@@ -249,8 +282,8 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
 #pragma unroll
       for (int v = 0; v < 4; ++v) mx = fmaxf(mx, s[b][v]);
     mx = quad_max(mx);
-    const float base = mx == -INFINITY ? 0.f : mx * scale_log2;  // nothing unmasked yet: exp2(-inf - 0) = 0
-    const float alpha = mx == m ? 1.f : __builtin_amdgcn_exp2f(m * scale_log2 - base);
+    const float base = mx == -INFINITY ? 0.f : mx;  // nothing unmasked yet: exp2(-inf - 0) = 0
+    const float alpha = mx == m ? 1.f : __builtin_amdgcn_exp2f((m - base) * scale_log2);
     m = mx;
     l *= alpha;
 #pragma unroll
@@ -261,7 +294,7 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[b][v], scale_log2, -base));
+        const float p = __builtin_amdgcn_exp2f((s[b][v] - base) * scale_log2);
         l += p;
         if constexpr (!Ahead<kDh>::value) value_cols(b, v);
         if (mixed) probe_finite<kDh>(z, vc[b][v]);
@@ -278,9 +311,9 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
       for (int j = j0; j <= min(j0 + kStep - 1, hi); ++j) {
         const float s = dot_token(Q + ((size_t)i_ld * hq + h) * d, Kh + (size_t)j * kv_row, kq, d);
         if (j < ss_i || j > i_abs) continue;  // the same in the four lanes of a row
-        const float mx = fmaxf(m, s), base = mx == -INFINITY ? 0.f : mx * scale_log2;
-        const float alpha = mx == m ? 1.f : __builtin_amdgcn_exp2f(m * scale_log2 - base);
-        const float p = __builtin_amdgcn_exp2f(fmaf(s, scale_log2, -base));
+        const float mx = fmaxf(m, s), base = mx == -INFINITY ? 0.f : mx;
+        const float alpha = mx == m ? 1.f : __builtin_amdgcn_exp2f((m - base) * scale_log2);
+        const float p = __builtin_amdgcn_exp2f((s - base) * scale_log2);
         m = mx;
         l = l * alpha + (kq == 0 ? p : 0.f);
         add_token<T, kDh>(sums, Vh + (size_t)j * kv_row, kq, d, alpha, p);
@@ -308,13 +341,13 @@ template <typename T, bool kVec, int kDh>
 __global__ void __launch_bounds__(64 * kWaves)
 f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
               const T *__restrict__ O, const float *__restrict__ LSE, float *__restrict__ delta, void *__restrict__ dQ,
-              const int32_t *__restrict__ seg_start, int N, int hq, int hkv, int d, va_dtype gdt, float scale_log2, float scale) {
+              const int32_t *__restrict__ seg_start, int N, int hq, int hkv, int d, va_dtype gdt, float scale) {
   __shared__ float red[kWaves * (kDh / 4) * 64];
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
   const int h = blockIdx.x % hq, g = h / (hq / hkv), t0 = (int)(blockIdx.x / hq) * kRows;
   const int hi = min(t0 + kRows, N) - 1, i_abs = t0 + l16, i_ld = min(i_abs, hi);
   const int lo = uniform(seg_start[t0]), ss_i = seg_start[i_ld];
-  const float lse2 = LSE[(size_t)h * N + i_ld] * 1.4426950408889634f;
+  const float lse = LSE[(size_t)h * N + i_ld];
   const size_t kv_row = (size_t)hkv * d, q_off = ((size_t)i_ld * hq + h) * d;
   const T *Kh = K + (size_t)g * d, *Vh = V + (size_t)g * d;
   float qf[kDh / 4], gf[kDh / 4], dl = 0.f;
@@ -355,18 +388,13 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       if constexpr (!Ahead<kDh>::value) rows(b);
-      f32x4 dp = {-dl, -dl, -dl, -dl};
-      s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < kDh / 4; ++i) {
-        s[b] = mfma16(kf[b][i], qf[i], s[b]);
-        dp = mfma16(vf[b][i], gf[i], dp);
-      }
+      s[b] = row_product<kDh>(kf[b], qf);
+      const f32x4 dp = grad_product<kDh>(vf[b], gf, f32x4{dl, dl, dl, dl});
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int j = j0 + 16 * b + 4 * kq + v;
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[b][v], scale_log2, -lse2));
-        s[b][v] = (j < ss_i || j > i_abs) ? 0.f : p * dp[v];
+        const float p = prob(s[b][v], scale, lse);
+        s[b][v] = (j < ss_i || j > i_abs) ? 0.f : p * (kLessD<kDh> ? dp[v] : dp[v] - dl);
       }
     }
 #pragma unroll
@@ -388,7 +416,7 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
         const T *Kj = Kh + (size_t)j * kv_row;
         const float s = dot_token(Q + q_off, Kj, kq, d), dp = dot_token(dO + q_off, Vh + (size_t)j * kv_row, kq, d) - dl;
         if (j < ss_i || j > i_abs) continue;
-        add_token<T, kDh>(sums, Kj, kq, d, 1.f, __builtin_amdgcn_exp2f(fmaf(s, scale_log2, -lse2)) * dp);
+        add_token<T, kDh>(sums, Kj, kq, d, 1.f, prob(s, scale, lse) * dp);
       }
   };
   merge_store<kVec, kDh>(acc, f, red, dQ, gdt, q_off, i_abs <= hi, d, met_not_finite(z), redo);
@@ -402,7 +430,7 @@ __global__ void __launch_bounds__(64 * kWaves)
 f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                 const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK, void *__restrict__ dV,
                 const int32_t *__restrict__ seg_end, float *__restrict__ partial, int parts, int N, int hq, int hkv, int d, va_dtype gdt,
-                float scale_log2, float scale) {
+                float scale) {
   __shared__ float red[kWaves * (kDh / 4) * 64];
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
   const int part = blockIdx.y;
@@ -455,18 +483,13 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       if constexpr (!Ahead<kDh>::value) rows(b);
-      f32x4 s = {0.f, 0.f, 0.f, 0.f}, dp = {-dl[b][0], -dl[b][1], -dl[b][2], -dl[b][3]};
-#pragma unroll
-      for (int i = 0; i < kDh / 4; ++i) {
-        s = mfma16(qf[b][i], kf[i], s);
-        dp = mfma16(gf[b][i], vf[i], dp);
-      }
+      const f32x4 s = row_product<kDh>(qf[b], kf), dp = grad_product<kDh>(gf[b], vf, f32x4{dl[b][0], dl[b][1], dl[b][2], dl[b][3]});
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = i0 + 16 * b + 4 * kq + v;
         const bool masked = i < j_abs || i >= se_j;
-        p[b][v] = masked ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[v], scale_log2, lse[b][v] * -1.4426950408889634f));
-        ds[b][v] = masked ? 0.f : p[b][v] * dp[v];
+        p[b][v] = masked ? 0.f : prob(s[v], scale, lse[b][v]);
+        ds[b][v] = masked ? 0.f : p[b][v] * (kLessD<kDh> ? dp[v] : dp[v] - dl[b][v]);
       }
     }
 #pragma unroll
@@ -501,7 +524,7 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
         const float s = dot_token(K + kv_off, Qi, kq, d);
         const float dp = dot_token(V + kv_off, Gi, kq, d) - delta[(size_t)h * N + i];
         if (i < j_abs || i >= se_j) continue;
-        const float p = __builtin_amdgcn_exp2f(fmaf(s, scale_log2, LSE[(size_t)h * N + i] * -1.4426950408889634f));
+        const float p = prob(s, scale, LSE[(size_t)h * N + i]);
         add_token<T, kDh>(sums, keys ? Qi : Gi, kq, d, 1.f, keys ? p * dp : p);
       }
     }
@@ -597,17 +620,16 @@ long long dkdv_parts(int N, int T, int hq, int hkv) {
 template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
   const long long gq = (long long)ceil_div(a.N, kRows) * a.hq, gkv = (long long)ceil_div(a.N, kRows) * a.hkv;
   if (gq > 0x7fffffffll) return hipErrorInvalidValue;
-  const float scale_log2 = a.scale * 1.4426950408889634f;
   if (a.stages & VA_STAGE_DQ)
     f32_dq_kernel<T, kVec, kDh><<<(unsigned)gq, 64 * kWaves, 0, a.stream>>>(
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, (const T *)a.O, a.LSE, a.delta, a.out,
-        a.seg->seg_start, a.N, a.hq, a.hkv, a.d, a.out_dt, scale_log2, a.scale);
+        a.seg->seg_start, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
   if (a.stages & VA_STAGE_DKDV) {
     const size_t n = (size_t)a.N * a.hkv * a.d;
     const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv), (long long)(a.partial.bytes / 8 / n)));
     f32_dkdv_kernel<T, kVec, kDh><<<dim3((unsigned)gkv, (unsigned)parts), 64 * kWaves, 0, a.stream>>>(
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
-        a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, scale_log2, a.scale);
+        a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
     if (parts > 1)
       f32_add_parts_kernel<<<(unsigned)((2 * n + 255) / 256), 256, 0, a.stream>>>(a.partial.p, (int)parts, n, a.dK, a.dV, a.out_dt);
   }

@@ -78,3 +78,22 @@ def test_not_finite_tokens_stay_in_their_example(lengths, t, hq, hkv, d, dtype, 
                 got[key][list(r)] = ref[key][list(r)]
         print(f"case: {tensor}[{t}] = {value}", flush=True)
         assert_close(got, ref, dtype)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n", [(4, 2, 16, 300), (8, 1, 32, 700), (4, 2, 64, 700), (2, 1, 128, 500), (2, 1, 256, 300)])
+def test_large_scores(hq, hkv, d, n):
+    # Scores of about 100.  Every score carries the rounding of its sum: of d products, whose absolute sum is A, in chains of
+    # d / 8 and three levels of pairs; of d products in pairs alone it would be log2 d levels.  A rounding is 2^-24 at most,
+    # 2^-24 / sqrt(3) in the mean, of a partial sum that grows to A / sqrt(d): what remains of a chain of d / 8 at random is
+    # below 2^-24 A.  The LSE adds its own store's rounding.  One chain of all d products misses it at each of these d.
+    w = wl.make_custom([[n]], hq, hkv, d, "f32", seed=94)
+    w.q *= 30.0
+    got, ref = run_gpu(w, grad_dtype=torch.float32), run_oracle(w)
+    a = np.einsum("ihc,ihc->hi", np.abs(w.q).astype(np.float64), np.abs(np.repeat(w.k, hq // hkv, axis=1)).astype(np.float64)) / d ** 0.5
+    bound = 2.0 ** -24 * np.sqrt((a ** 2).mean())
+    err = np.sqrt(((got["LSE"] - ref["LSE"]) ** 2).mean())
+    print(f"   LSE rms error {err:.2e}, bound {bound:.2e}", {k: f"{rel_l2(got[k], ref[k]):.2e}" for k in ("O", "dQ", "dK", "dV")}, flush=True)
+    assert err <= bound
+    # probabilities carry the error of the exponent, score - LSE: twice the bound, and dQ, dK sum differences of them
+    for key in ("O", "dQ", "dK", "dV"):
+        assert rel_l2(got[key], ref[key]) <= 2 * bound, key
