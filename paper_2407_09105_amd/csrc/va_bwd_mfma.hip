@@ -293,13 +293,7 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
         const bool interior = wave_full && jl >= ss_max && jl + 31 <= iw0;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], scale_log2, -lse2));  // P^T
-        if (!interior) {  // one wave-uniform branch around all 16 tests (inside the loop above it stays 16 branches)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int j = jl + acc_row(v, half);
-            if (j < ss_i || j > i_abs) s[v] = 0.f;
-          }
-        }
+        if (!interior) hide(s, visible_rows(ss_i - jl, i_abs - jl + 1, half), 0.f);
         x8 pf0, pf1;  // P^T as an operand, where the whole correction is kept
         if constexpr (kHasPk) {
           if (pk_on) { pf0 = pack_x8<E>(s, 0); pf1 = pack_x8<E>(s, 8); }
@@ -380,11 +374,8 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
       for (int ks = 0; ks < kKs; ++ks)
         sc = mfma32(swz_read_row<E>(Kb + (ks >> 3) * kBlk, row_lane, ks & 7, row0), qf[ks], sc);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int j = jl + acc_row(v, half);
-        const float p = __builtin_amdgcn_exp2f(fmaf(sc[v], scale_log2, -lse2));
-        sc[v] = (j < ss_i || j > i_abs) ? 0.f : -c_row * p;
-      }
+      for (int v = 0; v < 16; ++v) sc[v] = -c_row * __builtin_amdgcn_exp2f(fmaf(sc[v], scale_log2, -lse2));
+      hide(sc, visible_rows(ss_i - jl, i_abs - jl + 1, half), 0.f);
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) {
         const x8 cf = pack_x8<E>(sc, 8 * s2);
@@ -842,13 +833,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
 #pragma unroll
     for (int v = 0; v < 16; ++v) x[v] = __builtin_amdgcn_exp2f(x[v] * scale_log2);  // P
     const bool interior = wave_full && il >= jw1 && il + 31 < se_min;
-    if (!interior) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int i = il + acc_row(v, half);
-        if (i < j_abs || i >= se_j) x[v] = 0.f;
-      }
-    }
+    if (!interior) hide(x, visible_rows(j_abs - il, se_j - il, half), 0.f);
     // P goes to the K side as fp16 whatever the inputs' type: probabilities lie in [0, 1], where fp16
     // keeps 11 significant bits (bf16: 8) down to 6e-5 and absolute 2^-25 below
     ex[pw * 128] = __builtin_bit_cast(u32x4, pack_x8<F16>(x, 0));

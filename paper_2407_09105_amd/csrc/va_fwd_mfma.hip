@@ -145,13 +145,7 @@ fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
 #pragma unroll
         for (int ks = 0; ks < kKs; ++ks) s = mfma32(swz_read_row<E>(Kb + (ks >> 3) * kBlk, row_lane, ks & 7, sb * 32), qf[ks], s);
         const bool interior = wave_full && jl >= ss_max && jl + 31 <= iw0;
-        if (!interior) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int j = jl + acc_row(v, half);
-            if (j < ss_i || j > i_abs) s[v] = -INFINITY;
-          }
-        }
+        if (!interior) hide(s, visible_rows(ss_i - jl, i_abs - jl + 1, half), -INFINITY);
         // ---- online softmax with a lazily moved reference maximum ----
         float mx = fmaxf(s[0], s[1]);
 #pragma unroll

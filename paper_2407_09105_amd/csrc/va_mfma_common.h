@@ -52,6 +52,27 @@ template <class E> __device__ __forceinline__ typename E::x8 as_x8(u32x4 x) {
 // Row (register axis) index of accumulator element v for a lane of the given half.
 __device__ __forceinline__ int acc_row(int v, int half) { return 8 * (v >> 2) + 4 * half + (v & 3); }
 
+// The streamed rows of a 32-row sub-block that a lane's own row sees, as bits: rows lo .. n - 1 (those of them that exist),
+// shifted so that accumulator element v of the lane is bit acc_row(v, 0).
+__device__ __forceinline__ uint32_t visible_rows(int lo, int n, int half) {
+  lo = max(lo, 0);
+  n = min(n, 32) - lo;
+  return n > 0 ? ((0xffffffffu >> (32 - n)) << lo) >> (4 * half) : 0u;
+}
+// x[v] where its row is visible, `hidden` elsewhere, whatever x[v] holds.  Two vector instructions per element.  Comparing
+// each row with the lane's two bounds takes four, and a stall as the two results meet in scalar registers: 600 clocks per
+// sub-block of a wave, against 1500 for everything else.  A wave whose rows belong to two examples pays that in every
+// sub-block, and the waves of its workgroup wait for it: with compares the forward of 1255 tokens in four examples, 32/8
+// heads of 128, took 20.8 us (with bits 18.2), of 8192 in fifteen 100.5 (97.5), of 3000 tokens, 40/8, 69 (61); dK/dV
+// of 16384 in four rows 311 (298); dQ 1 to 5 % less.
+__device__ __forceinline__ void hide(f32x16 &x, uint32_t rows, float hidden) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)rows, acc_row(v, 0), 1);  // all bits or none
+    x[v] = __uint_as_float((keep & __float_as_uint(x[v])) | (~keep & __float_as_uint(hidden)));
+  }
+}
+
 // Eight consecutive accumulator floats v0..v0+7 -> one B operand (8 bf16).  With the layout
 // above these are rows {8a + 4 half + b : a in {2s2, 2s2+1}, b in 0..3} of a 16-row k-step.
 template <class E> __device__ __forceinline__ typename E::x8 pack_x8(const f32x16 &x, int v0) {
