@@ -32,13 +32,19 @@ constexpr int kBN = 32;           // key rows per LDS block
 constexpr int kBlk = kBN * kD;    // elements of one swizzled [32][128] LDS block (8 KB)
 constexpr int kStagingElems = 4 * kStageFloatsPerWave * 2;  // the result staging of four waves, in 16-bit units
 constexpr float kLazyLog2 = 8.f;  // keep a stale row maximum while probabilities stay <= 2^8
+// LDS fragment reads that are requested before the instructions whose results they wait for: k-steps of K ahead of their
+// matrix instructions, and column blocks of V ahead of the softmax.  Left alone the compiler requests a pair right before its
+// use, which three waves per SIMD hide from each other but one or two do not.  4 and 4 are no faster and spill at head_dim 96.
+// Forward, 1255 tokens in four examples, 32/8 heads of 128, 17.7 -> 17.2 us; 2048 in one 48.0 -> 46.6; 4096 tokens, 16
+// heads of 256, 69.6 -> 61.7; from 8192 tokens of 128 on within 1 %.
+constexpr int kAheadK = 3, kAheadV = 2;
 
 // E: element type (Bf16 / F16); kDh: head_dim rounded up to 64, 96, 128 or 256 (k-steps and column
 // blocks the kernel is unrolled for); d: the tensors' head_dim (a multiple of 8, <= kDh).  With
 // kDh = 256 a block of K or V is two swizzled [32][128] sub-blocks (columns 0..127 and 128..255),
-// the stages are twice as large and two workgroups share a CU instead of three.
+// the stages are twice as large and two workgroups share a CU instead of three; up to 96 four do.
 template <class E, int kDh>
-__global__ void __launch_bounds__(256, kDh > 128 ? 2 : 3)
+__global__ void __launch_bounds__(256, kDh > 128 ? 2 : kDh > 96 ? 3 : 4)
 fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                 const uint16_t *__restrict__ V, uint16_t *__restrict__ O, float *__restrict__ LSE,
                 const int32_t *__restrict__ seg_start, const int32_t *__restrict__ q_tile_order,
@@ -142,8 +148,20 @@ fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         f32x16 s;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        x8 kf[kAheadK], vf[kAheadV];
 #pragma unroll
-        for (int ks = 0; ks < kKs; ++ks) s = mfma32(swz_read_row<E>(Kb + (ks >> 3) * kBlk, row_lane, ks & 7, sb * 32), qf[ks], s);
+        for (int ks = 0; ks < kAheadK; ++ks) kf[ks] = swz_read_row<E>(Kb + (ks >> 3) * kBlk, row_lane, ks & 7, sb * 32);
+        __builtin_amdgcn_sched_barrier(0);  // these keep the order
+#pragma unroll
+        for (int ks = 0; ks < kKs; ++ks) {
+          s = mfma32(kf[ks % kAheadK], qf[ks], s);
+          const int kn = ks + kAheadK;
+          if (kn < kKs) kf[ks % kAheadK] = swz_read_row<E>(Kb + (kn >> 3) * kBlk, row_lane, kn & 7, sb * 32);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int cb = 0; cb < kAheadV; ++cb) vf[cb] = swz_read_tr<E>(Vb + (cb >> 2) * kBlk, tr_lane, cb & 3, sb * 32);
+        __builtin_amdgcn_sched_barrier(0);
         const bool interior = wave_full && jl >= ss_max && jl + 31 <= iw0;
         if (!interior) hide(s, visible_rows(ss_i - jl, i_abs - jl + 1, half), -INFINITY);
         // ---- online softmax with a lazily moved reference maximum ----
@@ -176,8 +194,10 @@ fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
         for (int s2 = 0; s2 < 2; ++s2) {
           const x8 pf = pack_x8<E>(s, 8 * s2);
 #pragma unroll
-          for (int cb = 0; cb < kCb; ++cb)
-            o_acc[cb] = mfma32(swz_read_tr<E>(Vb + (cb >> 2) * kBlk, tr_lane, cb & 3, sb * 32 + s2 * 16), pf, o_acc[cb]);
+          for (int cb = 0; cb < kCb; ++cb) {
+            const bool ahead = s2 == 0 && cb < kAheadV;
+            o_acc[cb] = mfma32(ahead ? vf[cb % kAheadV] : swz_read_tr<E>(Vb + (cb >> 2) * kBlk, tr_lane, cb & 3, sb * 32 + s2 * 16), pf, o_acc[cb]);
+          }
         }
       }
     }
