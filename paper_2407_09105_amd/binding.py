@@ -1,9 +1,12 @@
-"""Thin ctypes binding of libvarlen_attn.so (include/varlen_attn.h).
+"""Thin binding of libvarlen_attn.so (include/varlen_attn.h).
 
 Argument marshalling only: every step of the path (boundary scan, tile schedule,
 forward, backward) runs in the library's HIP kernels.  PyTorch supplies device
 memory and the stream.  There is no fallback: if the library is missing, or a
 call returns a non-zero status, an exception is raised.
+
+The plain calls of boundaries, forward and backward (outputs not given) marshal in C++
+(_va_native.so, which returns None where it leaves a call to the code here); everything else goes through ctypes.
 """
 from __future__ import annotations
 
@@ -37,11 +40,12 @@ class VaSegments(C.Structure):
 
 
 _lib = None
+_native = None  # set by lib()
 
 
 def lib() -> C.CDLL:
     """Load the built library (build it first with `python -m paper_2407_09105_amd.build`)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -78,6 +82,11 @@ def lib() -> C.CDLL:
     L.va_status_string.restype = C.c_char_p
     L.va_status_string.argtypes = [C.c_int]
     L.va_version.restype = C.c_char_p
+    from . import _va_native
+    _va_native.connect(*[C.cast(getattr(L, name), C.c_void_p).value for name in (
+        "va_plan_bytes", "va_segments_bind", "va_pack_to_cu_seqlens", "va_attn_workspace_bytes", "va_varlen_attn_fwd",
+        "va_varlen_attn_bwd")])
+    _native = _va_native
     _lib = L
     return L
 
@@ -134,6 +143,13 @@ class Segments:
         _check("va_segments_bind", lib().va_segments_bind(self.plan.data_ptr(), nbytes, self.rows,
                                                           self.tokens_per_row, C.byref(self.c)))
 
+    @classmethod
+    def _of(cls, rows: int, tokens_per_row: int, plan: torch.Tensor, c: VaSegments) -> "Segments":
+        """Around a plan buffer that `c` is bound to."""
+        seg = cls.__new__(cls)
+        seg.rows, seg.tokens_per_row, seg.n_tokens, seg.plan, seg.c = rows, tokens_per_row, rows * tokens_per_row, plan, c
+        return seg
+
     def _view(self, ptr: int, count: int) -> torch.Tensor:
         off = (ptr - self.plan.data_ptr()) // 4
         return self.plan[off: off + count]
@@ -175,6 +191,13 @@ class Segments:
 
 def pack_to_cu_seqlens(position_ids: torch.Tensor, seg: Optional[Segments] = None) -> Segments:
     """position_ids [R, T] (int32 or int64, GPU) -> Segments.  Enqueues kernels only."""
+    lib()
+    if seg is None and position_ids.is_cuda:
+        c = VaSegments()
+        got = _native.pack(position_ids, C.addressof(c), _stream())
+        if got.__class__ is tuple:
+            return Segments._of(*got, c)
+        _check("va_pack_to_cu_seqlens", got or VA_OK)
     _need_cuda(position_ids)
     if position_ids.dim() != 2:
         raise ValueError("position_ids must be [rows, tokens_per_row]")
@@ -268,6 +291,12 @@ def _shapes(q, k, v, seg):
 def varlen_attn_fwd(q, k, v, seg: Segments, softmax_scale: float = 0.0, out=None, lse=None
                     ) -> Tuple[torch.Tensor, torch.Tensor]:
     """-> O [N, Hq, d] (dtype of q), LSE [Hq, N] float32."""
+    lib()
+    if out is None and lse is None and q.is_cuda:
+        got = _native.fwd(q, k, v, C.addressof(seg.c), seg.rows, seg.tokens_per_row, float(softmax_scale), _stream())
+        if got.__class__ is tuple:
+            return got
+        _check("va_varlen_attn_fwd", got or VA_OK)
     _need_cuda(q, k, v)
     N, hq, hkv, d = _shapes(q, k, v, seg)
     if not (q.dtype == k.dtype == v.dtype):
@@ -293,6 +322,14 @@ def varlen_attn_bwd(do, q, k, v, o, lse, seg: Segments, softmax_scale: float = 0
     """-> dQ [N, Hq, d], dK, dV [N, Hkv, d] in grad_dtype (default: dtype of q).
     `stages` (an OR of STAGE_D, STAGE_DKDV, STAGE_DQ, optionally with HINT_LONG_EXAMPLES or
     HINT_SHORT_EXAMPLES) runs only those kernels of the backward."""
+    lib()
+    if dq is None and dk is None and dv is None and workspace is None and stages is None and q.is_cuda and (
+            grad_dtype is None or grad_dtype is torch.float32 or grad_dtype is q.dtype):
+        got = _native.bwd(do, q, k, v, o, lse, C.addressof(seg.c), seg.rows, seg.tokens_per_row, float(softmax_scale),
+                          grad_dtype is torch.float32, _stream())
+        if got.__class__ is tuple:
+            return got
+        _check("va_varlen_attn_bwd", got or VA_OK)
     _need_cuda(do, q, k, v, o, lse)
     N, hq, hkv, d = _shapes(q, k, v, seg)
     if not (q.dtype == k.dtype == v.dtype == o.dtype == do.dtype):

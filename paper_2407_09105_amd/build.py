@@ -1,9 +1,11 @@
 """Build the HIP libraries (gfx950) in-tree with hipcc: libvarlen_attn.so, the attention library
-(csrc/*.hip), and libva_probes.so, the benchmark's measurement aids (probes/*.hip)."""
+(csrc/*.hip), and libva_probes.so, the benchmark's measurement aids (probes/*.hip); and with g++ the host
+code of the Python binding, _va_native.so (native/va_native.cpp)."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -11,6 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 PROBES = os.path.join(HERE, "probes")
 LIB = os.path.join(HERE, "libvarlen_attn.so")
 PROBES_LIB = os.path.join(HERE, "libva_probes.so")
+NATIVE_LIB = os.path.join(HERE, "_va_native.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 FLAGS = [
@@ -26,8 +29,16 @@ def sources(src_dir=CSRC):
     return sorted(glob.glob(os.path.join(src_dir, "*.hip")))
 
 
+def native_command():
+    from torch.utils import cpp_extension
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-I" + os.path.join(ROOT, "include"),
+            *["-isystem" + p for p in (*cpp_extension.include_paths(), sysconfig.get_path("include"))],
+            os.path.join(HERE, "native", "va_native.cpp"), "-o", NATIVE_LIB,
+            *["-L" + p for p in cpp_extension.library_paths()], "-ltorch", "-ltorch_cpu", "-ltorch_python", "-lc10"]
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile every .hip source and link both shared libraries; always recompiles."""
+    """Compile every source and link the shared libraries; always recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
     procs = []
@@ -40,6 +51,10 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             if verbose:
                 print(" ".join(cmd), flush=True)
             procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    cmd = native_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append((cmd[0], subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -51,7 +66,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         elif verbose and out.strip():
             print(out)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("a compiler failed")
     for lib, _ in TARGETS:
         subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs[lib], "-o", lib])
     return LIB

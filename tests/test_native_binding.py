@@ -1,0 +1,82 @@
+"""The C++ marshalling of the plain calls: it takes only what it can handle, and gives what the ctypes calls give."""
+import ctypes as C
+import os
+
+import pytest
+import torch
+
+from paper_2407_09105_amd import binding, workloads as wl
+from tests.gpu_util import DEV, to_dev
+
+
+def _lib():
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("library is not built")
+    binding.lib()
+    return binding._native
+
+
+def test_leaves_what_is_not_on_the_gpu():
+    native = _lib()
+    c = binding.VaSegments()
+    q, k = torch.zeros(8, 2, 16), torch.zeros(8, 1, 16)
+    addr = C.addressof(c)
+    assert native.pack(torch.zeros(1, 8, dtype=torch.int64), addr, 0) is None
+    assert native.fwd(q, k, k, addr, 1, 8, 0.0, 0) is None
+    assert native.bwd(q, q, k, k, q, torch.zeros(2, 8), addr, 1, 8, 0.0, False, 0) is None
+    assert native.fwd(None, "k", 3, addr, 1, 8, 0.0, 0) is None
+    assert c.cu_seqlens is None
+    with pytest.raises(ValueError, match="GPU"):
+        binding.pack_to_cu_seqlens(torch.zeros(1, 8, dtype=torch.int64))
+    with pytest.raises(TypeError):
+        native.connect(1, 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,grads,d,lengths", [
+    ("f32", None, 16, [[6, 1, 5, 4]]), ("bf16", None, 80, [[129, 40], [100, 69]]), ("bf16", torch.float32, 64, [[300]]),
+    ("f16", torch.float16, 128, [[1100]]), ("f32", torch.bfloat16, 32, [[33, 7]])])
+def test_same_as_ctypes(dtype, grads, d, lengths):
+    _lib()
+    w = wl.make_custom(lengths, 4, 2, d, dtype, seed=5)
+    q, k, v, do = (to_dev(a, dtype) for a in (w.q, w.k, w.v, w.do))
+    for ids in (torch.int64, torch.int32):
+        pos = torch.from_numpy(w.position_ids).to(DEV).to(ids)
+        seg = binding.pack_to_cu_seqlens(pos)
+        given = binding.pack_to_cu_seqlens(pos, binding.Segments(*pos.shape, pos.device))
+        assert (seg.rows, seg.tokens_per_row, seg.n_tokens) == (given.rows, given.tokens_per_row, given.n_tokens)
+        a, b = seg.host(), given.host()
+        assert all((x == y).all() if hasattr(x, "all") else x == y for x, y in zip(a.values(), b.values()))
+    q.requires_grad_()
+    o, lse = binding.varlen_attn_fwd(q, k, v, seg, 0.2)
+    assert not o.requires_grad and not lse.requires_grad
+    o2, lse2 = binding.varlen_attn_fwd(q, k, v, given, 0.2, out=torch.empty_like(o), lse=torch.empty_like(lse))
+    assert o.dtype == q.dtype and torch.equal(o, o2) and torch.equal(lse, lse2)
+    got = binding.varlen_attn_bwd(do, q, k, v, o, lse, seg, 0.2, grad_dtype=grads)
+    ref = binding.varlen_attn_bwd(do, q, k, v, o, lse, given, 0.2, grad_dtype=grads, workspace=binding.bwd_workspace(q, k))
+    for x, y, like in zip(got, ref, (q, k, v)):
+        assert x.shape == like.shape and x.dtype == (grads or q.dtype) and torch.equal(x, y)
+
+
+@pytest.mark.gpu
+def test_refuses_the_same_calls():
+    _lib()
+    w = wl.make_custom([[20, 12]], 4, 2, 64, "bf16", seed=6)
+    q, k, v, do = (to_dev(a, "bf16") for a in (w.q, w.k, w.v, w.do))
+    pos = torch.from_numpy(w.position_ids).to(DEV)
+    seg = binding.pack_to_cu_seqlens(pos)
+    o, lse = binding.varlen_attn_fwd(q, k, v, seg)
+    fwd = binding.varlen_attn_fwd
+    bwd = binding.varlen_attn_bwd
+    for call, error in [
+            (lambda: binding.pack_to_cu_seqlens(pos[0]), ValueError), (lambda: binding.pack_to_cu_seqlens(pos.float()), TypeError),
+            (lambda: binding.pack_to_cu_seqlens(pos[:, ::2]), ValueError),
+            (lambda: fwd(q, k, v.float(), seg), TypeError), (lambda: fwd(q.transpose(0, 1), k, v, seg), ValueError),
+            (lambda: fwd(q[:16], k[:16], v[:16], seg), ValueError), (lambda: fwd(q, k.cpu(), v, seg), ValueError),
+            (lambda: fwd(q.double(), k.double(), v.double(), seg), TypeError),
+            (lambda: fwd(q[:, :3].contiguous(), k, v, seg), binding.VarlenAttnError),   # 3 query heads on 2 KV heads
+            (lambda: bwd(do.float(), q, k, v, o, lse, seg), TypeError), (lambda: bwd(do, q, k, v, o, lse[:1], seg), ValueError),
+            (lambda: bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float16), binding.VarlenAttnError),
+            (lambda: bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float64), TypeError)]:
+        with pytest.raises(error):
+            call()
