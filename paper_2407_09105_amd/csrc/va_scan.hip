@@ -319,38 +319,49 @@ tile_rank_kernel(const unsigned long long *__restrict__ key_q, const unsigned lo
 }
 
 // ---- one launch for streams of up to kSingleMaxTokens tokens -----------------------------------
-// One workgroup of 1024 threads holds the whole stream: boundary scan without carries (8 consecutive
-// tokens per thread), then tile keys and ranks after a barrier.  All global traffic is coalesced
-// (thread i touches tokens i, i + 1024, ...): the ids' start flags go through LDS to the threads that
-// scan them, and seg_id / seg_start / seg_end come back through LDS to be written out the same way --
-// one compute unit cannot afford 64 cache lines per load or store instruction.  Used when the stream
-// fits, because at this size every extra launch costs as much as the work.
-constexpr int kSingleThreads = 1024;
-constexpr int kSingleMaxTokens = kSingleThreads * kPerThread;  // 8192
+// One workgroup holds the whole stream: boundary scan without carries (8 consecutive tokens per thread),
+// then tile keys and ranks after a barrier.  All global traffic is coalesced (thread i touches tokens i,
+// i + kThreads, ...): the ids' start flags go through LDS to the threads that scan them, and seg_id /
+// seg_start / seg_end come back through LDS to be written out the same way -- one compute unit cannot afford
+// 64 cache lines per load or store instruction.  Used when the stream fits, because at this size every extra
+// launch costs as much as the work.  Bound: a chain of five barriers, which costs more with more waves, so a
+// shorter stream gets a smaller workgroup; with 1024 threads whatever the size and one thread to a tile's rank:
+// 16 tokens 7.0 us (now 6.0), 2048 tokens 7.5 (5.8), 8192 tokens 8.7 (8.3).
+constexpr int kSingleMaxTokens = 1024 * kPerThread;  // 8192
 constexpr int kSingleMaxTiles = 256;
 
-template <typename IdT>
-__global__ void __launch_bounds__(kSingleThreads)
+// The values first .. end - 1 that the waves left in v, combined; `id` is the operation's identity.  All are read together: a
+// loop up to the own wave is a chain of LDS round trips.
+template <int kWaves, class Op> __device__ __forceinline__ int over_waves(const int *v, int first, int end, int id, Op op) {
+  int x = id;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) x = op(x, i >= first && i < end ? v[i] : id);
+  return x;
+}
+
+template <typename IdT, int kThreads>
+__global__ void __launch_bounds__(kThreads)
 pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row, int ntiles,
                    int32_t *__restrict__ cu, int32_t *__restrict__ seg_id, int32_t *__restrict__ seg_start,
                    int32_t *__restrict__ seg_end, int32_t *__restrict__ meta, int32_t *__restrict__ order_q,
                    int32_t *__restrict__ order_kv) {
-  constexpr int kWaves = kSingleThreads / 64;
+  constexpr int kWaves = kThreads / 64, kTokens = kThreads * kPerThread;
+  constexpr int kTiles = kTokens < kSingleMaxTiles ? kTokens : kSingleMaxTiles;  // rows of one token: a tile each
   __shared__ int s_cnt[kWaves], s_last[kWaves], s_first[kWaves];
-  __shared__ __attribute__((aligned(16))) int32_t s_ss[kSingleMaxTokens], s_se[kSingleMaxTokens], s_id[kSingleMaxTokens];
-  __shared__ __attribute__((aligned(8))) uint8_t s_flag[kSingleMaxTokens];
-  __shared__ unsigned long long s_q[kSingleMaxTiles], s_kv[kSingleMaxTiles];
-  __shared__ int s_blocks[kSingleMaxTiles / 64];
+  __shared__ __attribute__((aligned(16))) int32_t s_ss[kTokens], s_se[kTokens], s_id[kTokens];
+  __shared__ __attribute__((aligned(8))) uint8_t s_flag[kTokens];
+  __shared__ unsigned long long s_q[kTiles], s_kv[kTiles];
+  __shared__ int s_blocks[kWaves];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   {  // start flags, coalesced; all loads in flight together
     IdT id[kPerThread];
 #pragma unroll
-    for (int e = 0; e < kPerThread; ++e) id[e] = pos[min(e * kSingleThreads + (int)threadIdx.x, N - 1)];
+    for (int e = 0; e < kPerThread; ++e) id[e] = pos[min(e * kThreads + (int)threadIdx.x, N - 1)];
     int r = threadIdx.x % T;
-    const int step = kSingleThreads % T;
+    const int step = kThreads % T;
 #pragma unroll
     for (int e = 0; e < kPerThread; ++e) {
-      const int t = e * kSingleThreads + threadIdx.x;
+      const int t = e * kThreads + threadIdx.x;
       s_flag[t] = t < N && (id[e] == 0 || r == 0);
       r += step;
       if (r >= T) r -= T;
@@ -377,8 +388,9 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
   int ecnt = __shfl_up(icnt, 1, 64), elast = __shfl_up(ilast, 1, 64), efirst = __shfl_down(sfirst, 1, 64);
   if (lane == 0) { ecnt = 0; elast = -1; }
   if (lane == 63) efirst = N;
-  for (int i = 0; i < w; ++i) { ecnt += s_cnt[i]; elast = max(elast, s_last[i]); }
-  for (int i = w + 1; i < kWaves; ++i) efirst = min(efirst, s_first[i]);
+  ecnt = over_waves<kWaves>(s_cnt, 0, w, 0, [](int x, int y) { return x + y; }) + ecnt;
+  elast = max(elast, over_waves<kWaves>(s_last, 0, w, -1, [](int x, int y) { return max(x, y); }));
+  efirst = min(efirst, over_waves<kWaves>(s_first, w + 1, kWaves, N, [](int x, int y) { return min(x, y); }));
   int nxt[kPerThread];
   int run = efirst;
 #pragma unroll
@@ -413,39 +425,43 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
   }
 #pragma unroll
   for (int e = 0; e < kPerThread; ++e) {  // coalesced write-out
-    const int t = e * kSingleThreads + threadIdx.x;
+    const int t = e * kThreads + threadIdx.x;
     if (t < N) { seg_id[t] = s_id[t]; seg_start[t] = s_ss[t]; seg_end[t] = s_se[t]; }
   }
   // tile keys
   int blocks = 0;
-  if ((int)threadIdx.x < ntiles) {
-    const int tile = threadIdx.x;
+  for (int tile = threadIdx.x; tile < ntiles; tile += kThreads) {
     const int r = tile / tiles_per_row, m = tile % tiles_per_row;
     const int t0 = r * T + m * kTile;
     const int t1 = min(t0 + kTile, (r + 1) * T) - 1;
     const int ss0 = s_ss[t0], se0 = s_se[t0], ss1 = s_ss[t1], se1 = s_se[t1];
     s_q[tile] = tile_key(se0 - ss0, ss0, (t1 >> 6) - (ss0 >> 6) + 1);
-    blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
-    s_kv[tile] = tile_key(se1 - ss1, ss1, blocks);
+    const int n_blocks = ((se1 - 1) >> 6) - (t0 >> 6) + 1;
+    s_kv[tile] = tile_key(se1 - ss1, ss1, n_blocks);
+    blocks += n_blocks;
   }
-  if (w < kSingleMaxTiles / 64) {
-    for (int o = 32; o > 0; o >>= 1) blocks += __shfl_xor(blocks, o, 64);
-    if (lane == 0) s_blocks[w] = blocks;
-  }
+  for (int o = 32; o > 0; o >>= 1) blocks += __shfl_xor(blocks, o, 64);
+  if (lane == 0) s_blocks[w] = blocks;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int i = 1; i < kWaves; ++i) longest = max(longest, s_cnt[i]);
-    meta[1] = longest;
-    meta[2] = s_blocks[0] + s_blocks[1] + s_blocks[2] + s_blocks[3];
+    meta[1] = over_waves<kWaves>(s_cnt, 0, kWaves, 0, [](int x, int y) { return max(x, y); });
+    meta[2] = over_waves<kWaves>(s_blocks, 0, kWaves, 0, [](int x, int y) { return x + y; });
   }
-  if ((int)threadIdx.x < ntiles) {
-    const int tile = threadIdx.x;
-    const unsigned long long cq = s_q[tile], ckv = s_kv[tile];
-    int rq = 0, rkv = 0;
-    for (int o = 0; o < ntiles; ++o) {
-      rq += (s_q[o] > cq) || (s_q[o] == cq && o < tile);
-      rkv += (s_kv[o] > ckv) || (s_kv[o] == ckv && o < tile);
-    }
+  // ranks: `parts` threads to a tile (a power of two, so that they share a wave), each compares every parts-th key
+  static_assert(kThreads >= kSingleMaxTiles, "a thread to a tile, at least");
+  const int parts = min(64, kThreads >> (32 - __clz(max(ntiles - 1, 1))));
+  const int part = threadIdx.x & (parts - 1), tile = threadIdx.x / parts;
+  const unsigned long long cq = s_q[min(tile, ntiles - 1)], ckv = s_kv[min(tile, ntiles - 1)];
+  int rq = 0, rkv = 0;
+  for (int o = part; o < ntiles; o += parts) {
+    rq += (s_q[o] > cq) || (s_q[o] == cq && o < tile);
+    rkv += (s_kv[o] > ckv) || (s_kv[o] == ckv && o < tile);
+  }
+  for (int o = 1; o < parts; o <<= 1) {
+    rq += __shfl_xor(rq, o, 64);
+    rkv += __shfl_xor(rkv, o, 64);
+  }
+  if (part == 0 && tile < ntiles) {
     order_q[rq] = order_entry(tile, cq, rq);
     order_kv[rkv] = order_entry(tile, ckv, rkv);
   }
@@ -459,14 +475,19 @@ hipError_t launch_pack(const void *pos, va_itype it, int rows, int T, const va_s
   const int nchunks = ceil_div(N, kScanChunk);
   const int tiles_per_row = ceil_div(T, kTile), ntiles = rows * tiles_per_row;
   if (N <= kSingleMaxTokens && ntiles <= kSingleMaxTiles) {
-    if (it == VA_I64)
-      pack_single_kernel<int64_t><<<1, kSingleThreads, 0, stream>>>(
-          (const int64_t *)pos, N, T, tiles_per_row, ntiles, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end,
-          seg.meta, seg.q_tile_order, seg.kv_tile_order);
-    else
-      pack_single_kernel<int32_t><<<1, kSingleThreads, 0, stream>>>(
-          (const int32_t *)pos, N, T, tiles_per_row, ntiles, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end,
-          seg.meta, seg.q_tile_order, seg.kv_tile_order);
+    auto launch = [&](auto *ids, auto threads) {
+      typedef std::remove_cv_t<std::remove_pointer_t<decltype(ids)>> IdT;
+      pack_single_kernel<IdT, decltype(threads)::value><<<1, decltype(threads)::value, 0, stream>>>(
+          ids, N, T, tiles_per_row, ntiles, seg.cu_seqlens, seg.seg_id, seg.seg_start, seg.seg_end, seg.meta, seg.q_tile_order,
+          seg.kv_tile_order);
+    };
+    auto by_size = [&](auto *ids) {
+      if (N <= 256 * kPerThread) launch(ids, std::integral_constant<int, 256>());
+      else if (N <= 512 * kPerThread) launch(ids, std::integral_constant<int, 512>());
+      else launch(ids, std::integral_constant<int, 1024>());
+    };
+    if (it == VA_I64) by_size((const int64_t *)pos);
+    else by_size((const int32_t *)pos);
     return hipGetLastError();
   }
   const bool fold = nchunks <= kFoldedCarryChunks;

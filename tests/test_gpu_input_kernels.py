@@ -32,6 +32,13 @@ def test_pack(R, T, maxlen):
         _check_orders(got, pos)
 
 
+@pytest.mark.parametrize("R,T,maxlen", [   # one launch: each size of workgroup, full and one token over, few and many tiles
+    (1, 1, 1), (1, 2048, 90), (1, 2049, 700), (1, 4096, 4096), (1, 4097, 90), (1, 8192, 700), (256, 1, 1), (256, 8, 3), (255, 9, 4),
+    (3, 513, 200), (2, 2048, 2048), (17, 241, 100), (256, 32, 9)])
+def test_pack_in_one_launch(R, T, maxlen):
+    test_pack(R, T, maxlen)
+
+
 @pytest.mark.parametrize("n", [1, 255, 2047, 2048, 2049])  # up to 2048 examples run in one launch
 @pytest.mark.parametrize("cut", [0, 5, -7])
 def test_collate(n, cut):
