@@ -22,7 +22,7 @@
 // run on whole blocks with a masked factor of 0, and a wave that meets another factor in such a block that is not finite
 // (0 * Inf = NaN) forms its sums again, token by token (`redo`).
 // Measured, 1000 tokens, 8 query / 2 KV heads, d = 64, examples of up to 315 tokens, against one wave per output row
-// on the vector units: forward 257 -> 16 us, dQ (with D) 214 -> 23 us, dK/dV 484 -> 32 us.  Bound there by the
+// on the vector units: forward 257 -> 14 us, dQ (with D) 214 -> 19 us, dK/dV 484 -> 27 us.  Bound there by the
 // matrix instructions of the CUs that hold the longest examples' tiles; one example of 8000 tokens runs the
 // forward at 76 TFLOP/s, half of what a large fp32 library product reaches.
 #include <algorithm>
@@ -138,6 +138,14 @@ __device__ __forceinline__ void add_outer(f32x4 (&acc)[Cols<kDh>::kGroups][Cols<
 // at a time and waits: eight memory round trips per block), as far as the registers reach: beyond head_dim 64
 // the columns are loaded where they are used.
 template <int kDh> struct Ahead { static constexpr bool value = kDh <= 64; };
+// Workgroups per CU: two up to head_dim 64.  Without the bound the compiler keeps sums in accumulation registers, which every
+// rescaling moves to and fro, and dK/dV takes 316 registers (one workgroup per CU, 1906 us for one example of 8000 tokens, 8
+// heads of 64; two 1530).  The backward keeps to it by requesting the second sub-block's columns only when the rows have been
+// used, in their registers (kLateCols).  Forward, 1000 tokens in five examples 14.7 -> 13.7 us, 8000 in one 905 -> 767; dQ
+// 19.4 -> 19.0 and 1293 -> 1213, two rows of 1000 tokens, 8 heads of 32, 28.1 -> 18.2.  Not for element-wise loads: dK/dV spills
+// 48 registers and more (900 tokens, 8/4 heads of 30: 70 -> 100 us).
+template <bool kVec, int kDh> constexpr bool kLateCols = kVec && kDh <= 64;
+template <bool kVec, int kDh> constexpr int kPerCu = kLateCols<kVec, kDh> ? 2 : 1;
 template <int kDh> __device__ __forceinline__ void loads_first() {
   if constexpr (Ahead<kDh>::value) __builtin_amdgcn_sched_barrier(0);
 }
@@ -235,7 +243,7 @@ __device__ __forceinline__ void merge_store(const f32x4 (&acc)[Cols<kDh>::kGroup
 }
 
 template <typename T, bool kVec, int kDh>
-__global__ void __launch_bounds__(64 * kWaves)
+__global__ void __launch_bounds__(64 * kWaves, (kPerCu<kVec, kDh>))
 f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, void *__restrict__ O,
                float *__restrict__ LSE, const int32_t *__restrict__ seg_start, int N, int hq, int hkv, int d,
                va_dtype dt, float scale_log2, float scale) {
@@ -338,7 +346,7 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
 
 // dQ; also forms D = dO . O of its rows and leaves it for the dK/dV kernel.
 template <typename T, bool kVec, int kDh>
-__global__ void __launch_bounds__(64 * kWaves)
+__global__ void __launch_bounds__(64 * kWaves, (kPerCu<kVec, kDh>))
 f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
               const T *__restrict__ O, const float *__restrict__ LSE, float *__restrict__ delta, void *__restrict__ dQ,
               const int32_t *__restrict__ seg_start, int N, int hq, int hkv, int d, va_dtype gdt, float scale) {
@@ -380,7 +388,7 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
 #pragma unroll
       for (int b = 0; b < 2; ++b) rows(b);
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < (kLateCols<kVec, kDh> ? 1 : 2); ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) key_cols(b, v);
     }
@@ -396,6 +404,11 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
         const float p = prob(s[b][v], scale, lse);
         s[b][v] = (j < ss_i || j > i_abs) ? 0.f : p * (kLessD<kDh> ? dp[v] : dp[v] - dl);
       }
+    }
+    if constexpr (kLateCols<kVec, kDh>) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) key_cols(1, v);
+      loads_first<kDh>();
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -426,15 +439,15 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
 // the pairs are also shared out over `parts` workgroups per tile: each then stores its sums as fp32 to
 // partial[part] ([2][N, Hkv, d]), and f32_add_parts_kernel adds them in the order of the parts.
 template <typename T, bool kVec, int kDh>
-__global__ void __launch_bounds__(64 * kWaves)
+__global__ void __launch_bounds__(64 * kWaves, (kPerCu<kVec, kDh>))
 f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                 const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK, void *__restrict__ dV,
                 const int32_t *__restrict__ seg_end, float *__restrict__ partial, int parts, int N, int hq, int hkv, int d, va_dtype gdt,
                 float scale) {
   __shared__ float red[kWaves * (kDh / 4) * 64];
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
-  const int part = blockIdx.y;
-  const int g = blockIdx.x % hkv, G = hq / hkv, t0 = (int)(blockIdx.x / hkv) * kRows;
+  const int unit = blockIdx.x / parts, part = (blockIdx.x + unit) % parts;  // moved on from unit to unit: every XCD meets every part
+  const int g = unit % hkv, G = hq / hkv, t0 = unit / hkv * kRows;
   const int t_last = min(t0 + kRows, N) - 1, j_abs = t0 + l16, j_ld = min(j_abs, t_last);
   const int end = uniform(seg_end[t_last]);
   const int se_j = j_abs <= t_last ? seg_end[j_ld] : 0;  // queries j_abs <= i < se_j see key j_abs
@@ -475,7 +488,7 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
 #pragma unroll
       for (int b = 0; b < 2; ++b) rows(b);
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < (kLateCols<kVec, kDh> ? 1 : 2); ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) query_cols(b, v);
     }
@@ -491,6 +504,11 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
         p[b][v] = masked ? 0.f : prob(s[v], scale, lse[b][v]);
         ds[b][v] = masked ? 0.f : p[b][v] * (kLessD<kDh> ? dp[v] : dp[v] - dl[b][v]);
       }
+    }
+    if constexpr (kLateCols<kVec, kDh>) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) query_cols(1, v);
+      loads_first<kDh>();
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -612,10 +630,11 @@ template <typename T, bool kVec, int kDh> hipError_t run_fwd(const Args &a) {
   return hipGetLastError();
 }
 // Parts that the work of a dK/dV tile is shared out to: enough workgroups for two per CU, but at least two rounds of the
-// waves in the longest chain that a row of T tokens allows.
-long long dkdv_parts(int N, int T, int hq, int hkv) {
-  const long long tiles = (N + kRows - 1ll) / kRows, rounds = (T + kStep - 1ll) / kStep * (hq / hkv) / kWaves;
-  return std::max(1ll, std::min(512 / (tiles * hkv), rounds / 2));
+// waves in the longest chain that a row of T tokens allows.  Up to head_dim 64, where two share a CU and begin together, half
+// as many again even out their chains (1000 tokens in examples of up to 676, 8/2 heads of 64: 47 us with 4 parts, 32.5 with 7).
+long long dkdv_parts(int N, int T, int hq, int hkv, int d) {
+  const long long units = (N + kRows - 1ll) / kRows * hkv, rounds = (T + kStep - 1ll) / kStep * (hq / hkv) / kWaves;
+  return std::max(1ll, std::min(d <= 64 ? (767 + units) / units : 512 / units, rounds / 2));
 }
 template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
   const long long gq = (long long)ceil_div(a.N, kRows) * a.hq, gkv = (long long)ceil_div(a.N, kRows) * a.hkv;
@@ -626,8 +645,8 @@ template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
         a.seg->seg_start, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
   if (a.stages & VA_STAGE_DKDV) {
     const size_t n = (size_t)a.N * a.hkv * a.d;
-    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv), (long long)(a.partial.bytes / 8 / n)));
-    f32_dkdv_kernel<T, kVec, kDh><<<dim3((unsigned)gkv, (unsigned)parts), 64 * kWaves, 0, a.stream>>>(
+    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv, a.d), (long long)(a.partial.bytes / 8 / n)));
+    f32_dkdv_kernel<T, kVec, kDh><<<(unsigned)(gkv * parts), 64 * kWaves, 0, a.stream>>>(
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
         a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
     if (parts > 1)
@@ -658,7 +677,7 @@ template <bool kFwd> hipError_t by_type(va_dtype dt, const Args &a) {
 }  // namespace
 
 size_t f32_partial_bytes(int N, int hq, int hkv, int d) {
-  const long long parts = dkdv_parts(N, N, hq, hkv);  // one row: the longest chains
+  const long long parts = dkdv_parts(N, N, hq, hkv, d);  // one row: the longest chains
   return parts > 1 ? (size_t)parts * 8 * N * hkv * d : 0;
 }
 
