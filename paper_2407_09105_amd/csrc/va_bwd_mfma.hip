@@ -17,6 +17,7 @@
 // In both, the streamed index lies on the accumulator's register axis and feeds the last
 // contraction as a B operand straight from registers (see va_mfma_common.h).
 #include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "va_internal.h"
@@ -433,13 +434,18 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
 // query heads per KV head, d = 64..128), 8192 to 32768 tokens: 5 blocks a tile 0.85...1.30 (mean 1.14), 6.5 to 8
 // blocks 0.93...1.17 (1.08), 10 to 11.5 blocks 0.91...1.12 (1.00), 13 blocks and more 0.86...1.03 (0.94).  Where
 // the small shape's tiles may be cut finely (below) no long chain is left for the large one to shorten, and 18 blocks
-// give 0.94...1.09: there the mean alone decides (by_mean).
+// give 0.94...1.09: there the mean alone decides.
 constexpr int kDkdvLongMean = 1024;
 constexpr int kDkdvLongBlocks = 12;
-__device__ __forceinline__ bool dkdv_small(const int32_t *__restrict__ meta, int N, int T, int tiles_per_row, bool by_mean) {
-  const long long n = meta[0], blocks = meta[2];  // examples; 64-query blocks over all key tiles (left by the scan)
-  return (long long)N < kDkdvLongMean * n &&
-         (by_mean || blocks < (long long)kDkdvLongBlocks * (N / T) * tiles_per_row);
+// What a launch asks of the scan's counts, made on the host: nothing but two compares may stand between a workgroup and
+// its first load.
+struct DkdvPick {
+  int select;    // 0: run; 1: run only where the large shape is the better one, 2: only where the small one is
+  int examples;  // the small shape: more examples than this
+  int blocks;    // and fewer 64-query blocks over all key tiles than this
+};
+__device__ __forceinline__ bool dkdv_small(int n_examples, int n_blocks, const DkdvPick &pick) {
+  return n_examples > pick.examples && n_blocks < pick.blocks;
 }
 template <int kDh, bool kSmall> struct DkdvShape {
   static_assert(!(kSmall && kDh > 128), "head_dim above 128 has one shape");
@@ -555,8 +561,6 @@ __device__ __forceinline__ void lds_barrier() {  // LDS traffic of this wave don
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// select: 0 = run; 1 = run only where the large shape is the better one, 2 = only where the small one is;
-// by_mean: see dkdv_small.
 // kCut: tiles may be cut (split.max_chunks > 1).  Without it the chunk arithmetic is not compiled in: it costs
 // scalar registers, in the head_dim 256 shape 29 spilled ones and 1.5 % of the time.
 template <class E, class EOut, int kDh, bool kSmall, bool kCut>
@@ -565,10 +569,9 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
                   const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
                   const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK,
                   void *__restrict__ dV, const int32_t *__restrict__ seg_end,
-                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, int select, bool by_mean,
+                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, DkdvPick pick,
                   DkdvSplit split, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2,
                   float scale) {
-  if (select != 0 && dkdv_small(meta, N, T, tiles_per_row, by_mean) != (select == 2)) return;  // workgroup-uniform
   constexpr int kKs = kDh / 16, kCb = kDh / 32;
   constexpr int kHf = kDh > 128 ? 2 : 1;  // 128-column sub-blocks per block
   constexpr int kBlkT = kBlk * kHf;       // elements of one tensor's streamed block
@@ -609,6 +612,10 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   // ones can all fall to one engine, and are started in order, so that an idle one waits for a place in front of
   // working ones (dK/dV of 2048 tokens in examples of 8 to 60, 32/8 heads: 52 us; numbered last 27; never cut 25).
   int pair = blockIdx.x, chunk = 0;
+  // Requested together with the counts that say whether this shape runs.  With the counts first, and the divisions that
+  // made their bounds here, dK/dV of 8192 tokens, 32 heads of 128, took 213 us (now 209.5), of 2 x 16384, 40/8 heads, 3232 (3210).
+  int entry = kCut ? 0 : uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
+  if (pick.select != 0 && dkdv_small(uniform(meta[0]), uniform(meta[2]), pick) != (pick.select == 2)) return;  // workgroup-uniform
   DkdvPlan plan = {0, 1};
   if constexpr (kCut) {
     plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, tiles_per_row, hq, hq / hkv, split);
@@ -634,7 +641,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
       pair -= level * n_pairs;
     }
   }
-  const int entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
+  if (kCut) entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
   const int tile = order_tile(entry);
   const int sub = (pair / hkv) % kSubTiles;
   const int g = (pair % hkv + head_rotation(entry)) % hkv;
@@ -948,11 +955,11 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
 template <class EOut, int kDh>
 __global__ void __launch_bounds__(256)
 dkdv_merge_kernel(void *__restrict__ dK, void *__restrict__ dV, const int32_t *__restrict__ seg_end,
-                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, int select,
+                  const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, DkdvPick pick,
                   DkdvSplit small, DkdvSplit large, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale) {
   constexpr int kCb = kDh / 32;
   __shared__ __attribute__((aligned(16))) float lds[4 * kStageFloatsPerWave];
-  const bool is_small = kDh <= 128 && (select == 2 || (select == 0 && dkdv_small(meta, N, T, tiles_per_row, small.max_chunks > 1 && small.fine)));
+  const bool is_small = kDh <= 128 && (pick.select == 2 || (pick.select == 0 && dkdv_small(meta[0], meta[2], pick)));
   const DkdvSplit split = is_small ? small : large;
   const int key_groups = is_small || kDh > 128 ? 2 : 4;
   const int sub_tiles = VA_TILE / 32 / key_groups;
@@ -1095,9 +1102,13 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     bool run_small = kDh <= 128 && !(stages & VA_HINT_LONG_EXAMPLES);
     if (run_small && T < kDkdvLongMean) run_large = false;
     const int select_large = run_small ? 1 : 0, select_small = run_large ? 2 : 0;
+    // where tiles may be cut finely the mean decides alone
+    const long long long_blocks = (long long)kDkdvLongBlocks * (N / T) * tiles_per_row;
+    const int blocks = ss.max_chunks > 1 && ss.fine ? INT_MAX : (int)std::min<long long>(long_blocks, INT_MAX);
+    auto pick = [&](int select) { return DkdvPick{select, N / kDkdvLongMean, blocks}; };
     auto launch = [&](auto *kernel, long long pairs, int threads, int select, const DkdvSplit &split) {
       kernel<<<(unsigned)(pairs * split.max_chunks), threads, 0, stream>>>(g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta,
-                                                                           select, ss.max_chunks > 1 && ss.fine, split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
+                                                                           pick(select), split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
     };
     if (run_large)
       launch(sl.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, false, true> : dkdv_mfma_kernel<E, EOut, kDh, false, false>, l.n_large,
@@ -1109,7 +1120,7 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     }
     if ((run_large && sl.max_chunks > 1) || (run_small && ss.max_chunks > 1))
       dkdv_merge_kernel<EOut, kDh><<<(unsigned)(gkv / kSub * (VA_TILE / 32)), 256, 0, stream>>>(
-          dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, run_large && run_small ? 0 : run_small ? 2 : 1, ss, sl, N, T,
+          dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta, pick(run_large && run_small ? 0 : run_small ? 2 : 1), ss, sl, N, T,
           tiles_per_row, hq, hkv, d, scale);
   }
 }
