@@ -83,7 +83,7 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
                const uint16_t *__restrict__ O, const float *__restrict__ LSE,
                float *__restrict__ delta, void *__restrict__ dQ,
                const int32_t *__restrict__ seg_start, const int32_t *__restrict__ q_tile_order, int N,
-               int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2, float scale) {
+               int T, TileMap map, int hq, int hkv, int d, float scale_log2, float scale) {
   constexpr int kKs = kDh / 16, kCb = kDh / 32;
   constexpr int kHf = kDh > 128 ? 2 : 1;   // 128-column sub-blocks per block (head_dim above 128: two)
   constexpr int kBlkT = kBlk * kHf;        // elements of one tensor's streamed block
@@ -96,13 +96,14 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   // schedule tiles hold kSub workgroup tiles; workgroups of one schedule tile are adjacent
-  const int wg = xcd_group_remap(blockIdx.x, hq / hkv, gridDim.x);
-  const int entry = uniform(q_tile_order[wg / (hq * kSub)]);
+  const int wg = xcd_group_remap(blockIdx.x, map);
+  const int at = wg / map.heads;  // workgroup tile, in launch order
+  const int entry = uniform(q_tile_order[at / kSub]);
   const int tile = order_tile(entry);
-  const int sub = (wg / hq) % kSub;
-  const int h = (wg % hq + head_rotation(entry) * (hq / hkv)) % hq;
-  const int g = h / (hq / hkv);
-  const int r = tile / tiles_per_row, m = tile % tiles_per_row;
+  const int sub = at % kSub;
+  const int h = (wg - at * hq + head_rotation(entry) * (int)map.group.d) % map.heads;
+  const int g = h / map.group;
+  const int r = tile / map.tiles, m = tile - r * (int)map.tiles.d;
   const int row_end = (r + 1) * T;
   const int t0 = r * T + m * VA_TILE + sub * kBT;
   if (t0 >= row_end) return;  // workgroup-uniform: the schedule tile is ragged
@@ -570,7 +571,7 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
                   const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK,
                   void *__restrict__ dV, const int32_t *__restrict__ seg_end,
                   const int32_t *__restrict__ kv_tile_order, const int32_t *__restrict__ meta, DkdvPick pick,
-                  DkdvSplit split, int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2,
+                  DkdvSplit split, int N, int T, FastDiv tiles, FastDiv heads, int G, int hq, int hkv, int d, float scale_log2,
                   float scale) {
   constexpr int kKs = kDh / 16, kCb = kDh / 32;
   constexpr int kHf = kDh > 128 ? 2 : 1;  // 128-column sub-blocks per block
@@ -614,11 +615,11 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
   int pair = blockIdx.x, chunk = 0;
   // Requested together with the counts that say whether this shape runs.  With the counts first, and the divisions that
   // made their bounds here, dK/dV of 8192 tokens, 32 heads of 128, took 213 us (now 209.5), of 2 x 16384, 40/8 heads, 3232 (3210).
-  int entry = kCut ? 0 : uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
+  int entry = kCut ? 0 : uniform(kv_tile_order[pair / heads / kSubTiles]);
   if (pick.select != 0 && dkdv_small(uniform(meta[0]), uniform(meta[2]), pick) != (pick.select == 2)) return;  // workgroup-uniform
   DkdvPlan plan = {0, 1};
   if constexpr (kCut) {
-    plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, tiles_per_row, hq, hq / hkv, split);
+    plan = dkdv_plan(meta, kKeys, 256 * Shape::kWgPerCu, N, T, tiles.d, hq, G, split);
     const int most = plan.most;
     if (blockIdx.x * split.max_chunks >= gridDim.x * most) return;
     if (most > 1 && split.fine) {
@@ -641,12 +642,13 @@ dkdv_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q
       pair -= level * n_pairs;
     }
   }
-  if (kCut) entry = uniform(kv_tile_order[pair / (hkv * kSubTiles)]);
+  // (cut tiles: plain divisions, for want of scalar registers)
+  const int at = kCut ? pair / hkv : pair / heads;  // workgroup tile, in launch order
+  if (kCut) entry = uniform(kv_tile_order[at / kSubTiles]);
   const int tile = order_tile(entry);
-  const int sub = (pair / hkv) % kSubTiles;
-  const int g = (pair % hkv + head_rotation(entry)) % hkv;
-  const int G = hq / hkv;
-  const int r = tile / tiles_per_row, m = tile % tiles_per_row;
+  const int sub = at % kSubTiles;
+  const int turned = pair - at * hkv + head_rotation(entry), g = kCut ? turned % hkv : turned % heads;
+  const int tiles_per_row = tiles.d, r = kCut ? tile / tiles_per_row : tile / tiles, m = tile - r * tiles_per_row;
   const int row_end = (r + 1) * T;
   const int t0 = r * T + m * VA_TILE + sub * kKeys;
   if (t0 >= row_end) return;  // workgroup-uniform: the schedule tile is ragged
@@ -1087,7 +1089,7 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
   const float scale_log2 = scale * kLog2e;
   if (stages & VA_STAGE_DQ)  // first: it also produces D for the dK/dV kernel
     dq_mfma_kernel<E, EOut, kDh><<<gq, 256, 0, stream>>>(g, q, k, v, o, LSE, delta, dQ, seg.seg_start,
-                                                         seg.q_tile_order, N, T, tiles_per_row, hq, hkv, d,
+                                                         seg.q_tile_order, N, T, tile_map(hq, hkv, tiles_per_row, gq), hq, hkv, d,
                                                          scale_log2, scale);
   if (stages & VA_STAGE_DKDV) {
     typedef typename DkdvLaunch<kDh>::Large Large;
@@ -1108,7 +1110,8 @@ static void launch_bwd_t(const uint16_t *g, const uint16_t *q, const uint16_t *k
     auto pick = [&](int select) { return DkdvPick{select, N / kDkdvLongMean, blocks}; };
     auto launch = [&](auto *kernel, long long pairs, int threads, int select, const DkdvSplit &split) {
       kernel<<<(unsigned)(pairs * split.max_chunks), threads, 0, stream>>>(g, q, k, v, LSE, delta, dK, dV, seg.seg_end, seg.kv_tile_order, seg.meta,
-                                                                           pick(select), split, N, T, tiles_per_row, hq, hkv, d, scale_log2, scale);
+                                                                           pick(select), split, N, T, fast_div(tiles_per_row), fast_div(hkv), hq / hkv, hq, hkv, d,
+                                                                           scale_log2, scale);
     };
     if (run_large)
       launch(sl.max_chunks > 1 ? dkdv_mfma_kernel<E, EOut, kDh, false, true> : dkdv_mfma_kernel<E, EOut, kDh, false, false>, l.n_large,

@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(256, kDh > 128 ? 2 : kDh > 96 ? 3 : 4)
 fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
                 const uint16_t *__restrict__ V, uint16_t *__restrict__ O, float *__restrict__ LSE,
                 const int32_t *__restrict__ seg_start, const int32_t *__restrict__ q_tile_order,
-                int N, int T, int tiles_per_row, int hq, int hkv, int d, float scale_log2, float scale) {
+                int N, int T, TileMap map, int hq, int hkv, int d, float scale_log2, float scale) {
   constexpr int kKs = kDh / 16, kCb = kDh / 32;
   constexpr int kHf = kDh > 128 ? 2 : 1;  // 128-column sub-blocks per block
   constexpr int kBlkT = kBlk * kHf;       // elements of one tensor's block
@@ -62,13 +62,14 @@ fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
   swz_tr_lane_off(lane, tr_lane);
 
   // heavy schedule tiles first; the workgroups of one schedule tile (sub-tiles x heads) are adjacent
-  const int wg = xcd_group_remap(blockIdx.x, hq / hkv, gridDim.x);
-  const int entry = uniform(q_tile_order[wg / (hq * kSub)]);
+  const int wg = xcd_group_remap(blockIdx.x, map);
+  const int at = wg / map.heads;  // workgroup tile, in launch order
+  const int entry = uniform(q_tile_order[at / kSub]);
   const int tile = order_tile(entry);
-  const int sub = (wg / hq) % kSub;
-  const int h = (wg % hq + head_rotation(entry) * (hq / hkv)) % hq;
-  const int g = h / (hq / hkv);
-  const int r = tile / tiles_per_row, m = tile % tiles_per_row;
+  const int sub = at % kSub;
+  const int h = (wg - at * hq + head_rotation(entry) * (int)map.group.d) % map.heads;
+  const int g = h / map.group;
+  const int r = tile / map.tiles, m = tile - r * (int)map.tiles.d;
   const int row_end = (r + 1) * T;  // one past the last token of this packed row
   const int t0 = r * T + m * VA_TILE + sub * kBM;
   if (t0 >= row_end) return;  // workgroup-uniform: the schedule tile is ragged
@@ -226,12 +227,12 @@ fwd_mfma_kernel(const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
 template <class E>
 static void launch_fwd_e(const void *Q, const void *K, const void *V, void *O, float *LSE, const va_segments &seg,
                          int rows, int T, int hq, int hkv, int d, float scale, unsigned nwg, hipStream_t stream) {
-  const int tiles_per_row = ceil_div(T, VA_TILE);
+  const TileMap map = tile_map(hq, hkv, ceil_div(T, VA_TILE), nwg);
   const float scale_log2 = scale * 1.4426950408889634f;
   const uint16_t *q = (const uint16_t *)Q, *k = (const uint16_t *)K, *v = (const uint16_t *)V;
 #define VA_LAUNCH_FWD(DH)                                                                             \
   fwd_mfma_kernel<E, DH><<<nwg, 256, 0, stream>>>(q, k, v, (uint16_t *)O, LSE, seg.seg_start,          \
-                                                  seg.q_tile_order, rows * T, T, tiles_per_row, hq,   \
+                                                  seg.q_tile_order, rows * T, T, map, hq,             \
                                                   hkv, d, scale_log2, scale)
   if (d <= 64) VA_LAUNCH_FWD(64);
   else if (d <= 96) VA_LAUNCH_FWD(96);

@@ -105,15 +105,41 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 // left at their maxima: 7 << 4, 15 << 8).
 __device__ __forceinline__ void wait_all_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// Division of x < 2^31 by a number that the host knows: m = ceil(2^(31 + s) / d) with s = ceil(log2 d) exceeds 2^(31 + s) / d
+// by less than 1, so that x m 2^-(31 + s) exceeds x / d by less than 2^-s <= 1 / d: too little to reach the next whole
+// number.  Three scalar instructions; dividing by a kernel argument takes some forty, each waiting for the one before, and
+// half a dozen such divisions stood between a workgroup's start and its first loads: forward of 700 tokens in short
+// examples, 32/8 heads of 128, 10.7 -> 9.9 us, dQ 17.8 -> 17.2; of 3 x 5000 tokens, 32 heads of 64, 83.7 -> 81.2 and 135.5 -> 133.4,
+// dK/dV 192 -> 189.
+struct FastDiv {
+  uint32_t d, m, s;
+};
+static inline FastDiv fast_div(int d) {
+  uint32_t s = 0;
+  while ((1u << s) < (uint32_t)d) ++s;
+  return {(uint32_t)d, (uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), s};
+}
+__device__ __forceinline__ int operator/(int x, const FastDiv &f) { return (int)(((uint64_t)(uint32_t)x * f.m) >> (31 + f.s)); }
+__device__ __forceinline__ int operator%(int x, const FastDiv &f) { return x - x / f * (int)f.d; }
+
+// Which tile and head a workgroup of the forward and dQ kernels takes (grid: schedule tiles x workgroup tiles in one x heads).
+struct TileMap {
+  FastDiv heads, group, tiles;  // hq, hq / hkv, schedule tiles per row
+  bool remap;                   // workgroup ids are remapped (xcd_group_remap)
+};
+static inline TileMap tile_map(int hq, int hkv, int tiles_per_row, long long n_wg) {
+  const int G = hq / hkv;
+  return {fast_div(hq), fast_div(G), fast_div(tiles_per_row), G > 1 && n_wg % (8 * G) == 0};
+}
 // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin by workgroup id.  With
 // grouped-query attention the G query heads of one KV head stream the same K/V blocks; this maps
 // workgroup id -> logical index so that G consecutive logical indices (the heads of one group, which
 // are adjacent in the logical order) land on one XCD in consecutive slots, while the logical
 // (longest-first) order is otherwise preserved at a granularity of 8 G workgroups.
-__device__ __forceinline__ int xcd_group_remap(int wg, int G, int n_wg) {
-  if (G == 1 || n_wg % (8 * G) != 0) return wg;
-  const int xcd = wg & 7, slot = wg >> 3;
-  return ((slot / G) * 8 + xcd) * G + slot % G;
+__device__ __forceinline__ int xcd_group_remap(int wg, const TileMap &map) {
+  if (!map.remap) return wg;
+  const int xcd = wg & 7, slot = wg >> 3, G = map.group.d, run = slot / map.group;
+  return (run * 8 + xcd) * G + slot - run * G;
 }
 
 // A tile-order entry of the pack: tile index in bits 0..23, head rotation of the tile above.
