@@ -630,11 +630,13 @@ template <typename T, bool kVec, int kDh> hipError_t run_fwd(const Args &a) {
   return hipGetLastError();
 }
 // Parts that the work of a dK/dV tile is shared out to: enough workgroups for two per CU, but at least two rounds of the
-// waves in the longest chain that a row of T tokens allows.  Up to head_dim 64, where two share a CU and begin together, half
-// as many again even out their chains (1000 tokens in examples of up to 676, 8/2 heads of 64: 47 us with 4 parts, 32.5 with 7).
-long long dkdv_parts(int N, int T, int hq, int hkv, int d) {
+// waves in the longest chain that a row of T tokens allows.  Where two share a CU and begin together (kPerCu), half as many
+// again even out their chains as long as those keep five rounds: 1000 tokens in examples of up to 676, 8/2 heads of 64, 47 us with 4
+// parts, 31.5 with 6; two rows of 1024, 8/4 heads, 112 with one, 82 with two; but 700, 8/8 heads, 28 with one, 40 with two.
+long long dkdv_parts(int N, int T, int hq, int hkv, bool two_per_cu) {
   const long long units = (N + kRows - 1ll) / kRows * hkv, rounds = (T + kStep - 1ll) / kStep * (hq / hkv) / kWaves;
-  return std::max(1ll, std::min(d <= 64 ? (767 + units) / units : 512 / units, rounds / 2));
+  const long long parts = std::max(1ll, std::min(512 / units, rounds / 2));
+  return two_per_cu ? std::max(parts, std::min((767 + units) / units, rounds / 5)) : parts;
 }
 template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
   const long long gq = (long long)ceil_div(a.N, kRows) * a.hq, gkv = (long long)ceil_div(a.N, kRows) * a.hkv;
@@ -645,7 +647,7 @@ template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
         a.seg->seg_start, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
   if (a.stages & VA_STAGE_DKDV) {
     const size_t n = (size_t)a.N * a.hkv * a.d;
-    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv, a.d), (long long)(a.partial.bytes / 8 / n)));
+    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv, kPerCu<kVec, kDh> == 2), (long long)(a.partial.bytes / 8 / n)));
     f32_dkdv_kernel<T, kVec, kDh><<<(unsigned)(gkv * parts), 64 * kWaves, 0, a.stream>>>(
         (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
         a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
@@ -677,7 +679,7 @@ template <bool kFwd> hipError_t by_type(va_dtype dt, const Args &a) {
 }  // namespace
 
 size_t f32_partial_bytes(int N, int hq, int hkv, int d) {
-  const long long parts = dkdv_parts(N, N, hq, hkv, d);  // one row: the longest chains
+  const long long parts = dkdv_parts(N, N, hq, hkv, d <= 64);  // one row: the longest chains; the more of the two
   return parts > 1 ? (size_t)parts * 8 * N * hkv * d : 0;
 }
 

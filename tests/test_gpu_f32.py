@@ -97,3 +97,18 @@ def test_large_scores(hq, hkv, d, n):
     # probabilities carry the error of the exponent, score - LSE: twice the bound, and dQ, dK sum differences of them
     for key in ("O", "dQ", "dK", "dV"):
         assert rel_l2(got[key], ref[key]) <= 2 * bound, key
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d", [   # parts of a dK/dV tile, two workgroups per CU:
+    ([[676, 300, 24]], 8, 2, 64),    # 6, the rounds of the longest chain allow no more
+    ([[160, 1]], 20, 1, 64),         # 15, a last tile of one token
+    ([[640, 17], [600, 57]], 4, 4, 16),   # 1: no query heads share a KV head
+    ([[300]], 6, 3, 36),             # 2, a head_dim between the unrolled ones
+])
+def test_parts_of_shared_tiles(lengths, hq, hkv, d):
+    w = wl.make_custom(lengths, hq, hkv, d, "f32", seed=83)
+    got = run_gpu(w, grad_dtype=torch.float32, nan_fill=True)
+    assert_close(got, run_oracle(w), "f32")
+    again = run_gpu(w, grad_dtype=torch.float32, nan_fill=True)
+    for key in ("dQ", "dK", "dV"):
+        assert np.array_equal(got[key], again[key]), key   # the parts are added in a fixed order
