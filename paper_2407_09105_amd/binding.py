@@ -83,12 +83,17 @@ def lib() -> C.CDLL:
     L.va_status_string.argtypes = [C.c_int]
     L.va_version.restype = C.c_char_p
     from . import _va_native
-    _va_native.connect(*[C.cast(getattr(L, name), C.c_void_p).value for name in (
-        "va_plan_bytes", "va_segments_bind", "va_pack_to_cu_seqlens", "va_attn_workspace_bytes", "va_varlen_attn_fwd",
-        "va_varlen_attn_bwd")])
+    _va_native.connect(*native_addresses(L))
     _native = _va_native
     _lib = L
     return L
+
+
+def native_addresses(L: C.CDLL) -> list:
+    """The functions that the C++ marshalling calls, in the order of its `connect`."""
+    return [C.cast(getattr(L, name), C.c_void_p).value for name in (
+        "va_plan_bytes", "va_segments_bind", "va_pack_to_cu_seqlens", "va_attn_workspace_bytes", "va_varlen_attn_fwd",
+        "va_varlen_attn_bwd")]
 
 
 class VarlenAttnError(RuntimeError):

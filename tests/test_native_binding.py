@@ -59,6 +59,28 @@ def test_same_as_ctypes(dtype, grads, d, lengths):
 
 
 @pytest.mark.gpu
+def test_the_interpreter_is_free_during_the_calls():
+    # Allocations and launches can block: other Python threads run meanwhile, as they do around a ctypes call.  The three
+    # calls reach an interpreter function that says whether the calling thread holds the interpreter lock (1: held, which
+    # arrives as a status; 0 is taken for success) in place of the library's, so nothing is launched.
+    native, L = _lib(), binding.lib()
+    w = wl.make_custom([[20, 12]], 4, 2, 64, "bf16", seed=6)
+    q, k, v, do = (to_dev(a, "bf16") for a in (w.q, w.k, w.v, w.do))
+    pos = torch.from_numpy(w.position_ids).to(DEV)
+    o, lse = torch.empty_like(q), torch.empty((4, 32), device=DEV)
+    c = binding.VaSegments()
+    plan_bytes, segments_bind, _, workspace_bytes, _, _ = binding.native_addresses(L)
+    held = C.cast(C.pythonapi.PyGILState_Check, C.c_void_p).value
+    native.connect(plan_bytes, segments_bind, held, workspace_bytes, held, held)
+    try:
+        assert type(native.pack(pos, C.addressof(c), 0)) is tuple
+        assert type(native.fwd(q, k, v, C.addressof(c), 1, 32, 0.0, 0)) is tuple
+        assert type(native.bwd(do, q, k, v, o, lse, C.addressof(c), 1, 32, 0.0, False, 0)) is tuple
+    finally:
+        native.connect(*binding.native_addresses(L))
+
+
+@pytest.mark.gpu
 def test_refuses_the_same_calls():
     _lib()
     w = wl.make_custom([[20, 12]], 4, 2, 64, "bf16", seed=6)
