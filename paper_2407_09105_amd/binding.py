@@ -315,6 +315,20 @@ def varlen_attn_fwd(q, k, v, seg: Segments, softmax_scale: float = 0.0, out=None
     return o, lse
 
 
+def _bwd_shapes(do, q, k, v, o, lse, seg, stages=None):
+    N, hq, hkv, d = _shapes(q, k, v, seg)
+    if not (q.dtype == k.dtype == v.dtype == o.dtype == do.dtype):
+        raise TypeError("dO, Q, K, V, O must share a dtype")
+    if lse.dtype != torch.float32 or tuple(lse.shape) != (hq, N):
+        raise ValueError("LSE must be float32 [Hq, N]")
+    # dO and O are read as Q's tokens and heads lie; flattened ones will do, shorter ones end before the kernels do (the
+    # dK/dV kernel alone does not look at O)
+    reads_o = stages is None or stages & (STAGE_D | STAGE_DQ)
+    if do.numel() < q.numel() or (reads_o and o.numel() < q.numel()):
+        raise ValueError(f"dO and O must hold Q's {q.numel()} elements, got {do.numel()} and {o.numel()}")
+    return N, hq, hkv, d
+
+
 def bwd_workspace(q, k) -> torch.Tensor:
     N, hq, d = q.shape
     nbytes = lib().va_attn_workspace_bytes(N, hq, k.shape[1], d, 1)
@@ -336,11 +350,7 @@ def varlen_attn_bwd(do, q, k, v, o, lse, seg: Segments, softmax_scale: float = 0
             return got
         _check("va_varlen_attn_bwd", got or VA_OK)
     _need_cuda(do, q, k, v, o, lse)
-    N, hq, hkv, d = _shapes(q, k, v, seg)
-    if not (q.dtype == k.dtype == v.dtype == o.dtype == do.dtype):
-        raise TypeError("dO, Q, K, V, O must share a dtype")
-    if lse.dtype != torch.float32 or tuple(lse.shape) != (hq, N):
-        raise ValueError("LSE must be float32 [Hq, N]")
+    N, hq, hkv, d = _bwd_shapes(do, q, k, v, o, lse, seg, stages)
     given = [t for t in (dq, dk, dv) if t is not None]
     gdt = grad_dtype if grad_dtype is not None else (given[0].dtype if given else q.dtype)
     dq = torch.empty(q.shape, dtype=gdt, device=q.device) if dq is None else _out_like("dq", dq, q.shape, gdt, q.device)
@@ -372,11 +382,7 @@ def varlen_attn_bwd_noalloc(do, q, k, v, o, lse, seg: Segments, dq, dk, dv, soft
     the workspace is the library's own device array (for D, N * Hq * 4 <= NOALLOC_SCRATCH_BYTES).  No tensor is
     created here either."""
     _need_cuda(do, q, k, v, o, lse, dq, dk, dv)
-    N, hq, hkv, d = _shapes(q, k, v, seg)
-    if not (q.dtype == k.dtype == v.dtype == o.dtype == do.dtype):
-        raise TypeError("dO, Q, K, V, O must share a dtype")
-    if lse.dtype != torch.float32 or tuple(lse.shape) != (hq, N):
-        raise ValueError("LSE must be float32 [Hq, N]")
+    N, hq, hkv, d = _bwd_shapes(do, q, k, v, o, lse, seg)
     _out_like("dq", dq, q.shape, dq.dtype, q.device)
     _out_like("dk", dk, k.shape, dq.dtype, q.device)
     _out_like("dv", dv, v.shape, dq.dtype, q.device)

@@ -142,7 +142,7 @@ PyObject *bwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const at::Tensor *g = plain(a[0]), *q = plain(a[1]), *k = plain(a[2]), *v = plain(a[3]), *o = plain(a[4]), *lse = plain(a[5]);
   Sizes s;
   if (!g || !o || !lse || !sizes(q, k, v, rows * T, s) || g->scalar_type() != q->scalar_type() || o->scalar_type() != q->scalar_type() ||
-      lse->scalar_type() != at::kFloat || lse->sizes() != at::IntArrayRef({s.hq, s.n}))
+      lse->scalar_type() != at::kFloat || lse->sizes() != at::IntArrayRef({s.hq, s.n}) || g->numel() < q->numel() || o->numel() < q->numel())
     Py_RETURN_NONE;
   const at::TensorOptions like = q->options(), grads = f32_grads ? like.dtype(at::kFloat) : like;
   at::Tensor dq, dk, dv;

@@ -32,6 +32,36 @@ def test_leaves_what_is_not_on_the_gpu():
         native.connect(1, 2)
 
 
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+@pytest.mark.parametrize("stages", [None, binding.STAGE_D, binding.STAGE_DQ, binding.STAGE_DKDV, "noalloc"])
+def test_short_dO_and_O_are_refused(stages, monkeypatch):
+    # The kernels read as many elements of dO and O as Q has.  The tensors have no memory behind them: a call that passes the
+    # binding's checks ends at the library's, which refuses null pointers.
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("library is not built")
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    seg = binding.Segments._of(2, 16, torch.empty(0), binding.VaSegments())
+    with FakeTensorMode():
+        of = lambda *shape: torch.empty(shape, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+        q, k, lse = of(32, 4, 64), of(32, 2, 64), torch.empty((4, 32), device="cuda")
+
+        def bwd(do, o):
+            if stages == "noalloc":
+                return binding.varlen_attn_bwd_noalloc(do, q, k, k, o, lse, seg, q, k, k)
+            return binding.varlen_attn_bwd(do, q, k, k, o, lse, seg, stages=stages)
+
+        for short in (of(31, 4, 64), of(32, 2, 64), of(0, 4, 64)):
+            with pytest.raises(ValueError, match="must hold"):
+                bwd(short, q)
+            if stages != binding.STAGE_DKDV:   # it reads no O
+                with pytest.raises(ValueError, match="must hold"):
+                    bwd(q, short)
+        for enough in (q, of(32, 256), of(33, 4, 64)):
+            with pytest.raises(binding.VarlenAttnError, match="null pointer"):
+                bwd(enough, enough)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,grads,d,lengths", [
     ("f32", None, 16, [[6, 1, 5, 4]]), ("bf16", None, 80, [[129, 40], [100, 69]]), ("bf16", torch.float32, 64, [[300]]),
@@ -97,6 +127,7 @@ def test_refuses_the_same_calls():
             (lambda: fwd(q[:16], k[:16], v[:16], seg), ValueError), (lambda: fwd(q, k.cpu(), v, seg), ValueError),
             (lambda: fwd(q.double(), k.double(), v.double(), seg), TypeError),
             (lambda: fwd(q[:, :3].contiguous(), k, v, seg), binding.VarlenAttnError),   # 3 query heads on 2 KV heads
+            (lambda: bwd(do[:16], q, k, v, o, lse, seg), ValueError), (lambda: bwd(do, q, k, v, o[:, :2].contiguous(), lse, seg), ValueError),
             (lambda: bwd(do.float(), q, k, v, o, lse, seg), TypeError), (lambda: bwd(do, q, k, v, o, lse[:1], seg), ValueError),
             (lambda: bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float16), binding.VarlenAttnError),
             (lambda: bwd(do, q, k, v, o, lse, seg, grad_dtype=torch.float64), TypeError)]:
