@@ -6,11 +6,13 @@ memory and the stream.  There is no fallback: if the library is missing, or a
 call returns a non-zero status, an exception is raised.
 
 The plain calls of boundaries, forward and backward (outputs not given) marshal in C++
-(_va_native.so, which returns None where it leaves a call to the code here); everything else goes through ctypes.
+(_va_native, which returns None where it leaves a call to the code here); everything else goes through ctypes, and so
+do those where _va_native was not built for the interpreter and torch that run.
 """
 from __future__ import annotations
 
 import ctypes as C
+import logging
 import os
 from typing import Optional, Tuple
 
@@ -40,7 +42,7 @@ class VaSegments(C.Structure):
 
 
 _lib = None
-_native = None  # set by lib()
+_native = None  # set by lib(); stays None where there is no C++ marshalling
 
 
 def lib() -> C.CDLL:
@@ -82,11 +84,28 @@ def lib() -> C.CDLL:
     L.va_status_string.restype = C.c_char_p
     L.va_status_string.argtypes = [C.c_int]
     L.va_version.restype = C.c_char_p
-    from . import _va_native
-    _va_native.connect(*native_addresses(L))
-    _native = _va_native
+    _native = _load_native()
+    if _native is not None:
+        _native.connect(*native_addresses(L))
     _lib = L
     return L
+
+
+def _load_native():
+    """The C++ marshalling, or None (said once, in the log) where it does not fit or is not there: the same calls then go
+    through ctypes, 38 instead of 23 us of host time for a pass of four launches."""
+    try:
+        from . import _va_native as native
+    except ImportError as e:
+        why = str(e)
+    else:
+        built_for = getattr(native, "torch_version", "another version")
+        if built_for == torch.__version__:
+            return native
+        why = f"built for torch {built_for}, this is {torch.__version__}"
+    logging.getLogger(__name__).warning("calls go through ctypes (%s); run __graft_entry__.build() "
+                                        "(python paper_2407_09105_amd/build.py)", why)
+    return None
 
 
 def native_addresses(L: C.CDLL) -> list:
@@ -197,7 +216,7 @@ class Segments:
 def pack_to_cu_seqlens(position_ids: torch.Tensor, seg: Optional[Segments] = None) -> Segments:
     """position_ids [R, T] (int32 or int64, GPU) -> Segments.  Enqueues kernels only."""
     lib()
-    if seg is None and position_ids.is_cuda:
+    if _native is not None and seg is None and position_ids.is_cuda:
         c = VaSegments()
         got = _native.pack(position_ids, C.addressof(c), _stream())
         if got.__class__ is tuple:
@@ -297,7 +316,7 @@ def varlen_attn_fwd(q, k, v, seg: Segments, softmax_scale: float = 0.0, out=None
                     ) -> Tuple[torch.Tensor, torch.Tensor]:
     """-> O [N, Hq, d] (dtype of q), LSE [Hq, N] float32."""
     lib()
-    if out is None and lse is None and q.is_cuda:
+    if _native is not None and out is None and lse is None and q.is_cuda:
         got = _native.fwd(q, k, v, C.addressof(seg.c), seg.rows, seg.tokens_per_row, float(softmax_scale), _stream())
         if got.__class__ is tuple:
             return got
@@ -342,7 +361,7 @@ def varlen_attn_bwd(do, q, k, v, o, lse, seg: Segments, softmax_scale: float = 0
     `stages` (an OR of STAGE_D, STAGE_DKDV, STAGE_DQ, optionally with HINT_LONG_EXAMPLES or
     HINT_SHORT_EXAMPLES) runs only those kernels of the backward."""
     lib()
-    if dq is None and dk is None and dv is None and workspace is None and stages is None and q.is_cuda and (
+    if _native is not None and dq is None and dk is None and dv is None and workspace is None and stages is None and q.is_cuda and (
             grad_dtype is None or grad_dtype is torch.float32 or grad_dtype is q.dtype):
         got = _native.bwd(do, q, k, v, o, lse, C.addressof(seg.c), seg.rows, seg.tokens_per_row, float(softmax_scale),
                           grad_dtype is torch.float32, _stream())

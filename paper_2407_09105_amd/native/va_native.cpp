@@ -169,4 +169,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_va_native", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__va_native() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__va_native() {
+  PyObject *m = PyModule_Create(&module);
+  // the torch whose headers this was compiled with: objects of another one may lie differently in memory
+  if (m && PyModule_AddStringConstant(m, "torch_version", VA_TORCH_VERSION) < 0) Py_CLEAR(m);
+  return m;
+}

@@ -1,19 +1,53 @@
 """The C++ marshalling of the plain calls: it takes only what it can handle, and gives what the ctypes calls give."""
 import ctypes as C
 import os
+import sys
+import types
 
 import pytest
 import torch
 
 from paper_2407_09105_amd import binding, workloads as wl
-from tests.gpu_util import DEV, to_dev
+from tests.gpu_util import DEV, assert_close, run_gpu, run_oracle, to_dev
 
 
 def _lib():
     if not os.path.exists(binding.LIB_PATH):
         pytest.skip("library is not built")
     binding.lib()
+    assert binding._native is not None, "the library is built, its C++ marshalling is not"
     return binding._native
+
+
+@pytest.fixture(params=["absent", "another torch", "older"])
+def without_native(request, monkeypatch):
+    """A binding that finds no C++ marshalling, or one built for another torch, or one that does not say for which."""
+    _lib()
+    package = sys.modules[binding.__package__]
+    other = types.ModuleType("_va_native")
+    if request.param == "another torch":
+        other.torch_version = torch.__version__ + ".1"
+    monkeypatch.delattr(package, "_va_native", raising=False)
+    monkeypatch.setitem(sys.modules, binding.__package__ + "._va_native", None)   # an import of it raises
+    if request.param != "absent":
+        monkeypatch.setattr(package, "_va_native", other, raising=False)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+
+
+def test_library_serves_without_cpp_marshalling(without_native, caplog):
+    assert binding.lib().va_plan_bytes(1, 16) > 0
+    assert binding._native is None and "ctypes" in caplog.text
+    with pytest.raises(ValueError, match="GPU"):
+        binding.pack_to_cu_seqlens(torch.zeros(1, 8, dtype=torch.int64))
+
+
+@pytest.mark.gpu
+def test_same_results_without_cpp_marshalling(without_native):
+    w = wl.make_custom([[129, 40], [100, 69]], 4, 2, 80, "bf16", seed=5)
+    got = run_gpu(w)
+    assert binding._native is None
+    assert_close(got, run_oracle(w), "bf16", bf16_stored=("dQ", "dK", "dV"))
 
 
 def test_leaves_what_is_not_on_the_gpu():
