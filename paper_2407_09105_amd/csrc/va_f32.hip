@@ -22,7 +22,7 @@
 // run on whole blocks with a masked factor of 0, and a wave that meets another factor in such a block that is not finite
 // (0 * Inf = NaN) forms its sums again, token by token (`redo`).
 // Measured, 1000 tokens, 8 query / 2 KV heads, d = 64, examples of up to 315 tokens, against one wave per output row
-// on the vector units: forward 257 -> 14 us, dQ (with D) 214 -> 19 us, dK/dV 484 -> 27 us.  Bound there by the
+// on the vector units: forward 257 -> 14 us, dQ (with D) 214 -> 19 us, dK/dV 484 -> 32 us.  Bound there by the
 // matrix instructions of the CUs that hold the longest examples' tiles; one example of 8000 tokens runs the
 // forward at 76 TFLOP/s, half of what a large fp32 library product reaches.
 #include <algorithm>
@@ -139,13 +139,21 @@ __device__ __forceinline__ void add_outer(f32x4 (&acc)[Cols<kDh>::kGroups][Cols<
 // the columns are loaded where they are used.
 template <int kDh> struct Ahead { static constexpr bool value = kDh <= 64; };
 // Workgroups per CU: two up to head_dim 64.  Without the bound the compiler keeps sums in accumulation registers, which every
-// rescaling moves to and fro, and dK/dV takes 316 registers (one workgroup per CU, 1906 us for one example of 8000 tokens, 8
-// heads of 64; two 1530).  The backward keeps to it by requesting the second sub-block's columns only when the rows have been
+// rescaling moves to and fro.  The backward keeps to it by requesting the second sub-block's columns only when the rows have been
 // used, in their registers (kLateCols).  Forward, 1000 tokens in five examples 14.7 -> 13.7 us, 8000 in one 905 -> 767; dQ
 // 19.4 -> 19.0 and 1293 -> 1213, two rows of 1000 tokens, 8 heads of 32, 28.1 -> 18.2.  Not for element-wise loads: dK/dV spills
 // 48 registers and more (900 tokens, 8/4 heads of 30: 70 -> 100 us).
 template <bool kVec, int kDh> constexpr bool kLateCols = kVec && kDh <= 64;
 template <bool kVec, int kDh> constexpr int kPerCu = kLateCols<kVec, kDh> ? 2 : 1;
+// dK/dV comes in both forms: without the bound it takes 316 registers at head_dim 64, with it it spills 4.  From 768 workgroups
+// on, one and a half times what 256 CUs hold at two each, two per CU are faster whatever the lengths (0.78 of the time up to
+// 1536, 0.69 beyond; of 2000 random shapes one took 1.06, the others at most 1.02); with four and more query heads per KV head,
+// whose chains are longer, from twice as many on (0.82; between 768 and 1536 0.87, but up to 1.16).  With fewer, all are resident
+// at once and long chains that begin on one CU stay together, while one at a time is followed by whichever comes next: 256 to
+// 512 workgroups take 0.7...1.4 of the time by the lengths, which the host does not know.  Up to head_dim 32 (three per CU)
+// the line is at 2048 (0.85; 512 to 768 1.03, up to 1.23) and doubles with two query heads per KV head (2048 to 4096 0.92, up
+// to 1.08); up to 16 there is none (1.00...1.08).
+template <bool kVec, int kDh> constexpr int kTwoPerCuFrom = !kVec || kDh <= 16 || kDh > 64 ? 0 : kDh <= 32 ? 2048 : 768;
 template <int kDh> __device__ __forceinline__ void loads_first() {
   if constexpr (Ahead<kDh>::value) __builtin_amdgcn_sched_barrier(0);
 }
@@ -438,16 +446,16 @@ f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__rest
 // dK, dV of 16 keys: the waves share out the (query head of the group, 32-query block) pairs.  With few tiles
 // the pairs are also shared out over `parts` workgroups per tile: each then stores its sums as fp32 to
 // partial[part] ([2][N, Hkv, d]), and f32_add_parts_kernel adds them in the order of the parts.
-template <typename T, bool kVec, int kDh>
-__global__ void __launch_bounds__(64 * kWaves, (kPerCu<kVec, kDh>))
+template <typename T, bool kVec, int kDh, bool kTwo>
+__global__ void __launch_bounds__(64 * kWaves, kTwo ? 2 : 1)
 f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
                 const float *__restrict__ LSE, const float *__restrict__ delta, void *__restrict__ dK, void *__restrict__ dV,
                 const int32_t *__restrict__ seg_end, float *__restrict__ partial, int parts, int N, int hq, int hkv, int d, va_dtype gdt,
                 float scale) {
   __shared__ float red[kWaves * (kDh / 4) * 64];
   const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
-  const int unit = blockIdx.x / parts, part = (blockIdx.x + unit) % parts;  // moved on from unit to unit: every XCD meets every part
-  const int g = unit % hkv, G = hq / hkv, t0 = unit / hkv * kRows;
+  const int part = blockIdx.y;
+  const int g = blockIdx.x % hkv, G = hq / hkv, t0 = (int)(blockIdx.x / hkv) * kRows;
   const int t_last = min(t0 + kRows, N) - 1, j_abs = t0 + l16, j_ld = min(j_abs, t_last);
   const int end = uniform(seg_end[t_last]);
   const int se_j = j_abs <= t_last ? seg_end[j_ld] : 0;  // queries j_abs <= i < se_j see key j_abs
@@ -488,7 +496,7 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
 #pragma unroll
       for (int b = 0; b < 2; ++b) rows(b);
 #pragma unroll
-      for (int b = 0; b < (kLateCols<kVec, kDh> ? 1 : 2); ++b)
+      for (int b = 0; b < (kTwo ? 1 : 2); ++b)
 #pragma unroll
         for (int v = 0; v < 4; ++v) query_cols(b, v);
     }
@@ -505,7 +513,7 @@ f32_dkdv_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__re
         ds[b][v] = masked ? 0.f : p[b][v] * (kLessD<kDh> ? dp[v] : dp[v] - dl[b][v]);
       }
     }
-    if constexpr (kLateCols<kVec, kDh>) {
+    if constexpr (kTwo) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) query_cols(1, v);
       loads_first<kDh>();
@@ -630,13 +638,12 @@ template <typename T, bool kVec, int kDh> hipError_t run_fwd(const Args &a) {
   return hipGetLastError();
 }
 // Parts that the work of a dK/dV tile is shared out to: enough workgroups for two per CU, but at least two rounds of the
-// waves in the longest chain that a row of T tokens allows.  Where two share a CU and begin together (kPerCu), half as many
-// again even out their chains as long as those keep five rounds: 1000 tokens in examples of up to 676, 8/2 heads of 64, 47 us with 4
-// parts, 31.5 with 6; two rows of 1024, 8/4 heads, 112 with one, 82 with two; but 700, 8/8 heads, 28 with one, 40 with two.
-long long dkdv_parts(int N, int T, int hq, int hkv, bool two_per_cu) {
+// waves in the longest chain that a row of T tokens allows.  More parts help long chains (1000 tokens in examples of up to 676,
+// 8/2 heads of 64: six instead of four -5 us) and cost short ones, which the host cannot tell apart (1788 tokens in examples of
+// up to 28, 4/2 heads: four instead of two +9 us; 2374 of up to 17, 16/4 heads: two instead of one +10).
+long long dkdv_parts(int N, int T, int hq, int hkv) {
   const long long units = (N + kRows - 1ll) / kRows * hkv, rounds = (T + kStep - 1ll) / kStep * (hq / hkv) / kWaves;
-  const long long parts = std::max(1ll, std::min(512 / units, rounds / 2));
-  return two_per_cu ? std::max(parts, std::min((767 + units) / units, rounds / 5)) : parts;
+  return std::max(1ll, std::min(512 / units, rounds / 2));
 }
 template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
   const long long gq = (long long)ceil_div(a.N, kRows) * a.hq, gkv = (long long)ceil_div(a.N, kRows) * a.hkv;
@@ -647,10 +654,15 @@ template <typename T, bool kVec, int kDh> hipError_t run_bwd(const Args &a) {
         a.seg->seg_start, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
   if (a.stages & VA_STAGE_DKDV) {
     const size_t n = (size_t)a.N * a.hkv * a.d;
-    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv, kPerCu<kVec, kDh> == 2), (long long)(a.partial.bytes / 8 / n)));
-    f32_dkdv_kernel<T, kVec, kDh><<<(unsigned)(gkv * parts), 64 * kWaves, 0, a.stream>>>(
-        (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
-        a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
+    const long long parts = std::max(1ll, std::min(dkdv_parts(a.N, a.T, a.hq, a.hkv), (long long)(a.partial.bytes / 8 / n)));
+    auto launch = [&](auto *kernel) {
+      kernel<<<dim3((unsigned)gkv, (unsigned)parts), 64 * kWaves, 0, a.stream>>>(
+          (const T *)a.dO, (const T *)a.Q, (const T *)a.K, (const T *)a.V, a.LSE, a.delta, a.dK, a.dV, a.seg->seg_end,
+          a.partial.p, (int)parts, a.N, a.hq, a.hkv, a.d, a.out_dt, a.scale);
+    };
+    constexpr int kFrom = kTwoPerCuFrom<kVec, kDh>;
+    const bool two = kFrom > 0 && gkv >= (a.hq < (kDh <= 32 ? 2 : 4) * a.hkv ? kFrom : 2 * kFrom);
+    launch(two ? f32_dkdv_kernel<T, kVec, kDh, (kFrom > 0)> : f32_dkdv_kernel<T, kVec, kDh, false>);
     if (parts > 1)
       f32_add_parts_kernel<<<(unsigned)((2 * n + 255) / 256), 256, 0, a.stream>>>(a.partial.p, (int)parts, n, a.dK, a.dV, a.out_dt);
   }
@@ -679,7 +691,7 @@ template <bool kFwd> hipError_t by_type(va_dtype dt, const Args &a) {
 }  // namespace
 
 size_t f32_partial_bytes(int N, int hq, int hkv, int d) {
-  const long long parts = dkdv_parts(N, N, hq, hkv, d <= 64);  // one row: the longest chains; the more of the two
+  const long long parts = dkdv_parts(N, N, hq, hkv);  // one row: the longest chains
   return parts > 1 ? (size_t)parts * 8 * N * hkv * d : 0;
 }
 

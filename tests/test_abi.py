@@ -164,6 +164,19 @@ def test_attn_validation(L):
     assert L.va_attn_workspace_bytes(0, 2, 2, 16, 1) == 0
 
 
+@pytest.mark.parametrize("n,hq,hkv,d,parts", [
+    (1788, 4, 2, 60, 2), (2374, 16, 4, 60, 1), (1000, 8, 2, 60, 4), (161, 20, 1, 60, 15), (1314, 4, 4, 12, 1), (300, 6, 3, 36, 2),
+    (1000, 8, 2, 100, 4), (512, 8, 8, 60, 2), (528, 8, 8, 60, 1)])
+def test_parts_of_fp32_tiles(L, n, hq, hkv, d, parts):
+    """Room behind D for the parts that a key tile of the fp32-arithmetic dK/dV is shared out to: as many as make 512 workgroups,
+    but two rounds of four 32-query blocks for each in the longest chain (head dims that the 16-bit kernels do not take)."""
+    tiles = (n + 15) // 16 * hkv
+    rounds = (n + 31) // 32 * (hq // hkv) // 4
+    assert parts == max(1, min(512 // tiles, rounds // 2))
+    behind = L.va_attn_workspace_bytes(n, hq, hkv, d, 1) - (n * hq * 4 + 255) // 256 * 256
+    assert behind == (parts * 2 * n * hkv * d * 4 if parts > 1 else 0)
+
+
 def test_noalloc_backward_validation(L):
     """The backward that allocates nothing validates on the host before it touches the GPU: bad
     arguments and sizes beyond its device array are refused with nothing looked up or launched."""

@@ -52,6 +52,7 @@ def test_unaligned_fp32_tensors():
     ([[37, 150, 9]], 100, 8, 1, 128, "f32"),       # columns loaded where they are used; dK/dV in parts
     ([[37, 50, 9]], 60, 2, 1, 200, "f32"),
     ([[21, 40, 30]], 44, 4, 1, 20, "bf16"),        # element-wise loads
+    ([[21, 340, 23]], 44, 32, 32, 64, "f32"),      # the dK/dV form for many tiles
 ])
 def test_not_finite_tokens_stay_in_their_example(lengths, t, hq, hkv, d, dtype, value):
     # one token of an example is not finite in one tensor: what does not depend on it is as if it were
@@ -99,11 +100,17 @@ def test_large_scores(hq, hkv, d, n):
         assert rel_l2(got[key], ref[key]) <= 2 * bound, key
 
 
-@pytest.mark.parametrize("lengths,hq,hkv,d", [   # parts of a dK/dV tile, two workgroups per CU:
-    ([[676, 300, 24]], 8, 2, 64),    # 6, the rounds of the longest chain allow no more
+@pytest.mark.parametrize("lengths,hq,hkv,d", [   # parts of a dK/dV tile (their number: test_parts_of_fp32_tiles)
+    ([[676, 300, 24]], 8, 2, 64),    # 4
     ([[160, 1]], 20, 1, 64),         # 15, a last tile of one token
     ([[640, 17], [600, 57]], 4, 4, 16),   # 1: no query heads share a KV head
     ([[300]], 6, 3, 36),             # 2, a head_dim between the unrolled ones
+    # workgroups, from 768 on two per CU (head_dim up to 32: 2048; from four query heads per KV head on twice as many):
+    ([[367, 1]], 32, 32, 64),        # 736
+    ([[300, 68]] + [[368]], 33, 33, 60),   # 1518: two rows whose tiles meet
+    ([[400, 368]], 128, 32, 36),     # 1536, four query heads per KV head
+    ([[700, 67]], 128, 32, 64),      # 1536, the last tile one short
+    ([[1000, 24]], 32, 32, 20),      # 2048
 ])
 def test_parts_of_shared_tiles(lengths, hq, hkv, d):
     w = wl.make_custom(lengths, hq, hkv, d, "f32", seed=83)
