@@ -142,9 +142,10 @@ template <int kDh> struct Ahead { static constexpr bool value = kDh <= 64; };
 // rescaling moves to and fro.  The backward keeps to it by requesting the second sub-block's columns only when the rows have been
 // used, in their registers (kLateCols).  Forward, 1000 tokens in five examples 14.7 -> 13.7 us, 8000 in one 905 -> 767; dQ
 // 19.4 -> 19.0 and 1293 -> 1213, two rows of 1000 tokens, 8 heads of 32, 28.1 -> 18.2.  Not for element-wise loads: dK/dV spills
-// 48 registers and more (900 tokens, 8/4 heads of 30: 70 -> 100 us).
-template <bool kVec, int kDh> constexpr bool kLateCols = kVec && kDh <= 64;
-template <bool kVec, int kDh> constexpr int kPerCu = kLateCols<kVec, kDh> ? 2 : 1;
+// 48 registers and more (900 tokens, 8/4 heads of 30: 70 -> 100 us).  Not in dQ up to head_dim 16, where four fit without it
+// and the later columns are a second wait: 1105 tokens, 8 heads of 16, 14.3 -> 16.3, 2273 tokens, 2/1, 23.2 -> 26.0.
+template <bool kVec, int kDh> constexpr int kPerCu = kVec && kDh <= 64 ? 2 : 1;
+template <bool kVec, int kDh> constexpr bool kLateCols = kVec && kDh > 16 && kDh <= 64;
 // dK/dV comes in both forms: without the bound it takes 316 registers at head_dim 64, with it it spills 4.  From 768 workgroups
 // on, one and a half times what 256 CUs hold at two each, two per CU are faster whatever the lengths (0.78 of the time up to
 // 1536, 0.69 beyond; of 2000 random shapes one took 1.06, the others at most 1.02); with four and more query heads per KV head,
@@ -354,7 +355,7 @@ f32_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K, const T *__rest
 
 // dQ; also forms D = dO . O of its rows and leaves it for the dK/dV kernel.
 template <typename T, bool kVec, int kDh>
-__global__ void __launch_bounds__(64 * kWaves, (kPerCu<kVec, kDh>))
+__global__ void __launch_bounds__(64 * kWaves, (kLateCols<kVec, kDh> ? 2 : 1))
 f32_dq_kernel(const T *__restrict__ dO, const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
               const T *__restrict__ O, const float *__restrict__ LSE, float *__restrict__ delta, void *__restrict__ dQ,
               const int32_t *__restrict__ seg_start, int N, int hq, int hkv, int d, va_dtype gdt, float scale) {
