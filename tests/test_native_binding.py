@@ -2,6 +2,7 @@
 import ctypes as C
 import os
 import sys
+import threading
 import types
 
 import pytest
@@ -96,12 +97,41 @@ def test_short_dO_and_O_are_refused(stages, monkeypatch):
                 bwd(enough, enough)
 
 
+@pytest.fixture
+def taken(monkeypatch):
+    """What the C++ functions returned to the binding, in order: "tuple", "NoneType" or "int" after the function's name."""
+    native, calls = _lib(), []
+
+    def spy(name):
+        def call(*args):
+            got = getattr(native, name)(*args)
+            calls.append((name, type(got).__name__))
+            return got
+        return call
+
+    monkeypatch.setattr(binding, "_native", types.SimpleNamespace(**{name: spy(name) for name in ("pack", "fwd", "bwd")}))
+    return calls
+
+
+TAKEN = [(name, "tuple") for name in ("pack", "fwd", "bwd")]
+
+
+def _inputs(dtype="bf16", lengths=((300, 45, 1, 1, 200, 93),), hq=4, hkv=2, d=128, seed=41):
+    w = wl.make_custom([list(row) for row in lengths], hq, hkv, d, dtype, seed=seed)
+    return (torch.from_numpy(w.position_ids).to(DEV), *(to_dev(a, dtype) for a in (w.do, w.q, w.k, w.v)))
+
+
+def _pass(pos, do, q, k, v):
+    seg = binding.pack_to_cu_seqlens(pos)
+    o, lse = binding.varlen_attn_fwd(q, k, v, seg)
+    return [seg.seg_start, seg.q_tile_order, o, lse, *binding.varlen_attn_bwd(do, q, k, v, o, lse, seg)]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,grads,d,lengths", [
     ("f32", None, 16, [[6, 1, 5, 4]]), ("bf16", None, 80, [[129, 40], [100, 69]]), ("bf16", torch.float32, 64, [[300]]),
     ("f16", torch.float16, 128, [[1100]]), ("f32", torch.bfloat16, 32, [[33, 7]])])
-def test_same_as_ctypes(dtype, grads, d, lengths):
-    _lib()
+def test_same_as_ctypes(dtype, grads, d, lengths, taken):
     w = wl.make_custom(lengths, 4, 2, d, dtype, seed=5)
     q, k, v, do = (to_dev(a, dtype) for a in (w.q, w.k, w.v, w.do))
     for ids in (torch.int64, torch.int32):
@@ -120,6 +150,125 @@ def test_same_as_ctypes(dtype, grads, d, lengths):
     ref = binding.varlen_attn_bwd(do, q, k, v, o, lse, given, 0.2, grad_dtype=grads, workspace=binding.bwd_workspace(q, k))
     for x, y, like in zip(got, ref, (q, k, v)):
         assert x.shape == like.shape and x.dtype == (grads or q.dtype) and torch.equal(x, y)
+    # one call of each went to C++ (two of pack), but gradients in a third type are left to ctypes
+    left = grads is torch.bfloat16
+    assert taken == [("pack", "tuple"), *TAKEN[:2]] + ([] if left else TAKEN[2:])
+
+
+@pytest.mark.gpu
+def test_on_another_stream(taken):
+    args = _inputs()
+    ref = _pass(*args)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        # the inputs arrive on this stream only: a launch on another one would read the old values
+        late = [torch.zeros_like(x) for x in args]
+        torch.cuda._sleep(20_000_000)
+        for x, y in zip(late, args):
+            x.copy_(y)
+        got = _pass(*late)
+    side.synchronize()
+    assert taken == 2 * TAKEN
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.gpu
+def test_under_capture(taken):
+    args = _inputs(lengths=((513, 31, 480),), hq=5, hkv=1, seed=42)
+    pos, do, q, k, v = args
+    _pass(*args)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        outs = _pass(*args)   # outputs and workspace come from the graph's pool
+    assert taken == 2 * TAKEN
+    for rep in range(3):
+        if rep:
+            q.mul_(-1.0)
+            do.mul_(0.5)
+        eager = _pass(*args)
+        for x in outs[2:]:
+            x.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(outs, eager):
+            assert torch.equal(x, y), rep
+
+
+@pytest.mark.gpu
+def test_from_two_threads(taken):
+    work = [_inputs(), _inputs("f16", ((700, 60), (1, 759)), 8, 2, 64, seed=43)]
+    ref = [_pass(*args) for args in work]
+    torch.cuda.synchronize()
+    wrong = [None, None]
+
+    def run(i):
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            for _ in range(50):
+                got = _pass(*work[i])
+                side.synchronize()
+                wrong[i] = (wrong[i] or 0) + sum(not torch.equal(x, y) for x, y in zip(got, ref[i]))
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert wrong == [0, 0]
+    assert len(taken) == 3 * 102 and {kind for _, kind in taken} == {"tuple"}
+
+
+@pytest.mark.gpu
+def test_modes_that_ask_for_the_python_calls_see_them(taken):
+    from torch.overrides import TorchFunctionMode
+
+    class Record(TorchFunctionMode):
+        def __init__(self):
+            super().__init__()
+            self.seen = []
+
+        def __torch_function__(self, func, types_, args=(), kwargs=None):
+            self.seen.append(func)
+            return func(*args, **(kwargs or {}))
+
+    args = _inputs()
+    ref = _pass(*args)
+    with Record() as mode:
+        got = _pass(*args)
+    assert mode.seen.count(torch.empty) >= 5 and torch.empty_like in mode.seen   # plan, LSE, gradients; O
+    assert taken == TAKEN + [(name, "NoneType") for name in ("pack", "fwd", "bwd")]
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.gpu
+def test_what_is_left_to_python_and_what_the_library_refuses():
+    native = _lib()
+    pos, do, q, k, v = _inputs(lengths=((20, 12),), d=64)
+    seg = binding.pack_to_cu_seqlens(pos)
+    o, lse = binding.varlen_attn_fwd(q, k, v, seg)
+    at, s = (C.addressof(seg.c), 1, 32, 0.0), binding._stream()
+    class Sub(torch.Tensor):
+        pass
+    fwd = lambda *qkv: native.fwd(*qkv, *at, s)  # noqa: E731
+    bwd = lambda *t: native.bwd(*t, *at, False, s)  # noqa: E731
+    c = binding.VaSegments()   # written by pack: it has to outlive the calls
+    pack = lambda x: native.pack(x, C.addressof(c), s)  # noqa: E731
+    assert [type(pack(x)) for x in (pos, pos.to(torch.int32))] == [tuple, tuple]
+    for x in (pos[0], pos.float(), pos[:, ::2], pos.as_subclass(Sub), pos.cpu()):
+        assert pack(x) is None
+    assert type(fwd(q, k, v)) is tuple and type(bwd(do, q, k, v, o, lse)) is tuple
+    for qkv in ((q, k, v.float()), (q.transpose(0, 1), k, v), (q[:16], k[:16], v[:16]), (q.double(), k.double(), v.double()),
+                (q.as_subclass(Sub), k, v), (q, k, v[:, :1].contiguous())):
+        assert fwd(*qkv) is None
+    for t in ((do.float(), q, k, v, o, lse), (do[:16], q, k, v, o, lse), (do, q, k, v, o[:, :2].contiguous(), lse),
+              (do, q, k, v, o, lse[:1]), (do, q, k, v, o, lse.double())):
+        assert bwd(*t) is None
+    assert fwd(q[:, :3].contiguous(), k, v) == 2   # 3 query heads on 2 KV heads: VA_ERR_SHAPE
 
 
 @pytest.mark.gpu
