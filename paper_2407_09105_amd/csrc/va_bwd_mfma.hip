@@ -434,7 +434,8 @@ dq_mfma_kernel(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ Q,
 // the work, which the mean does not show.  Time of the large over the small shape, 8 head layouts (1 to 9
 // query heads per KV head), 8192 to 32768 tokens, d = 64 to 96: 8 to 9 blocks a tile 0.95...1.09 (mean 1.03), 9.5 to 10.5
 // blocks 0.98...1.06 (1.01), 12 blocks and more 0.86...1.03 (0.94).  d = 128: 8 to 10.5 blocks 1.02...1.19 (1.10), 12 to 15.5 blocks
-// 0.91...1.12 (1.01; long chains cut 0.91...0.94), 18 to 22 blocks 0.98...1.02, beyond 0.89...1.03 (0.94).  Where
+// 0.91...1.12 (1.01; long chains cut 0.91...0.94), 18 to 22 blocks 0.98...1.02, beyond 0.89...1.03 (0.94): even between 12 and
+// 22, where a later line would gain on some batches (8192 tokens, 32 heads, -6 %) what it loses on others.  Where
 // the small shape's tiles may be cut finely (below) no long chain is left for the large one to shorten, and 18 blocks
 // give 0.94...1.09: there the mean alone decides.
 constexpr int kDkdvLongMean = 1024;

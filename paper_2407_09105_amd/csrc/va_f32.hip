@@ -16,7 +16,7 @@
 // Tiles are 16 tokens (of the flat stream) x one head; the four waves of a workgroup share out the streamed blocks
 // of 32 tokens and add their results through LDS in a fixed order.  Small tiles and that split make short chains
 // and many workgroups: fp32 runs are checks of a few hundred to a few thousand tokens and few heads.  (Eight waves
-// per workgroup: the dQ kernel 28 instead of 22 us below, one workgroup per CU instead of two.)
+// per workgroup, one workgroup per CU instead of two: the dQ kernel below took 28 us when with four it took 22.)
 // The mask is "seg_start[i] <= j <= i" (forward, dQ) or "j <= i < seg_end[j]" (dK/dV) -- Table 1's correct
 // cross-attention for contiguous examples.  Tokens outside it leave no trace, whatever they hold: the matrix products
 // run on whole blocks with a masked factor of 0, and a wave that meets another factor in such a block that is not finite

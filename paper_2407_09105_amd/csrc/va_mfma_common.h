@@ -110,7 +110,8 @@ __device__ __forceinline__ void wait_all_loads() { __builtin_amdgcn_s_waitcnt(0x
 // number.  Three scalar instructions; dividing by a kernel argument takes some forty, each waiting for the one before, and
 // half a dozen such divisions stood between a workgroup's start and its first loads: forward of 700 tokens in short
 // examples, 32/8 heads of 128, 10.7 -> 9.9 us, dQ 17.8 -> 17.2; of 3 x 5000 tokens, 32 heads of 64, 83.7 -> 81.2 and 135.5 -> 133.4,
-// dK/dV 192 -> 189.
+// dK/dV 192 -> 189.  Their multipliers take scalar registers: the forward 3 more, dQ 16, of which it spills 4 (at head_dim 256
+// 8 to 10 instead of 4 to 6); the dK/dV kernel that cuts tiles has none to spare and divides.
 struct FastDiv {
   uint32_t d, m, s;
 };

@@ -324,7 +324,7 @@ tile_rank_kernel(const unsigned long long *__restrict__ key_q, const unsigned lo
 // i + kThreads, ...): the ids' start flags go through LDS to the threads that scan them, and seg_id /
 // seg_start / seg_end come back through LDS to be written out the same way -- one compute unit cannot afford
 // 64 cache lines per load or store instruction.  Used when the stream fits, because at this size every extra
-// launch costs as much as the work.  Bound: a chain of five barriers, which costs more with more waves, so a
+// launch costs as much as the work.  Bound: a chain of four barriers, which costs more with more waves, so a
 // shorter stream gets a smaller workgroup; with 1024 threads whatever the size and one thread to a tile's rank:
 // 16 tokens 7.0 us (now 6.0), 2048 tokens 7.5 (5.8), 8192 tokens 8.7 (8.3).
 constexpr int kSingleMaxTokens = 1024 * kPerThread;  // 8192
@@ -346,11 +346,10 @@ pack_single_kernel(const IdT *__restrict__ pos, int N, int T, int tiles_per_row,
                    int32_t *__restrict__ seg_end, int32_t *__restrict__ meta, int32_t *__restrict__ order_q,
                    int32_t *__restrict__ order_kv) {
   constexpr int kWaves = kThreads / 64, kTokens = kThreads * kPerThread;
-  constexpr int kTiles = kTokens < kSingleMaxTiles ? kTokens : kSingleMaxTiles;  // rows of one token: a tile each
   __shared__ int s_cnt[kWaves], s_last[kWaves], s_first[kWaves];
   __shared__ __attribute__((aligned(16))) int32_t s_ss[kTokens], s_se[kTokens], s_id[kTokens];
   __shared__ __attribute__((aligned(8))) uint8_t s_flag[kTokens];
-  __shared__ unsigned long long s_q[kTiles], s_kv[kTiles];
+  __shared__ unsigned long long s_q[kSingleMaxTiles], s_kv[kSingleMaxTiles];
   __shared__ int s_blocks[kWaves];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   {  // start flags, coalesced; all loads in flight together

@@ -2,7 +2,7 @@
 // the library call of one pass in one C++ call each.
 //
 // A pass over 16 tokens (boundaries, forward, backward: four kernels of 3 to 6 us) took 38 us of host time: 14 us for the
-// launches themselves, the rest in Python checks, seven torch.empty of 1.3 us and ctypes calls of up to 24 arguments.
+// launches themselves, the rest in Python checks, seven torch.empty of 1.3 us and ctypes calls of up to 21 arguments.
 //
 // Each function handles the plain case - exact torch.Tensor arguments that satisfy every check of its counterpart in
 // binding.py, outputs not given - and returns None for anything else before it has done anything; the caller then goes on
@@ -31,7 +31,8 @@ struct Library {
 Library lib = {};
 
 // Other Python threads run while a tensor is allocated (which can wait for the GPU) and kernels are launched (which can wait
-// for room in their queue), as they do around torch's own allocations and around ctypes calls.  A 16-token pass takes 23.0 us with it and without.
+// for room in their queue), as they do around torch's own allocations and around ctypes calls.  A 16-token pass takes 23.0 us
+// with it and without.
 struct WithoutGil {
   PyThreadState *state = PyEval_SaveThread();
   ~WithoutGil() { PyEval_RestoreThread(state); }
